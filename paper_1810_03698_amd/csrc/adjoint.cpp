@@ -68,11 +68,11 @@ void Runtime::apply_transpose(const double *x, double *y, bool f64) {
   if (use_tree())
     tree_apply_transpose(*tree_, s_, use64, ru_.nf, N_, geo_.p, src64_.p, src32_.p, tgt32_.p,
                          x, o.kappa, part_.p, trow_.p, tcol_.p, tent_.p, val,
-                         o.eps_in / o.eps_out, y);
+                         o.eps_in / o.eps_out, y, floor_r2_);
   else
     launch_transpose(s_, use64, ru_.nf, N_, src64_.p, src32_.p, geo_.p, tgt32_.p, x, o.kappa,
                      p2p_chunks_, part_.p, trow_.p, tcol_.p, tent_.p, val,
-                     o.eps_in / o.eps_out, y);
+                     o.eps_in / o.eps_out, y, floor_r2_);
   ++matvecs_;
 }
 
@@ -163,10 +163,10 @@ int Runtime::backward(double dGbar, double *g_xyz, double *g_q, double *g_d, dou
   };
   // pack the forward solution's strengths again (the last products may have
   // packed other vectors)
-  launch_pack_strengths(s_, N, ru_.nf, geo_.p, x_.p, src64_.p, src32_.p);
+  launch_pack_strengths(s_, N, ru_.nf, o.eps_in / o.eps_out, geo_.p, x_.p, src64_.p, src32_.p);
   relax(false, lv, wv);
   relax(true, ld, wd);
-  launch_pack_strengths(s_, N, ru_.nf, geo_.p, x_.p, src64_.p, src32_.p);
+  launch_pack_strengths(s_, N, ru_.nf, o.eps_in / o.eps_out, geo_.p, x_.p, src64_.p, src32_.p);
   // ---- explicit derivatives at fixed states
   Dbuf<double> gr1, gr2, gr3, gq1, gq3, gd1, gd3, gQ1, gQ3;
   for (auto *b : {&gr1, &gr2, &gr3, &gd1, &gd3}) b->alloc(3 * (size_t)M);

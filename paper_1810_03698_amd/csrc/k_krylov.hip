@@ -159,8 +159,10 @@ __global__ void k_precond_pack(int N, int nf, const double *__restrict__ diag, d
   const double sv = wA * z2, sk = wA * z1;
   src64[16 * (size_t)i + 13] = sv;
   src64[16 * (size_t)i + 14] = sk;
+  src64[16 * (size_t)i + 15] = e * sv;
   src32[16 * (size_t)i + 13] = (float)sv;
   src32[16 * (size_t)i + 14] = (float)sk;
+  src32[16 * (size_t)i + 15] = (float)(e * sv);
 }
 
 __global__ void k_update_solution(int N, int nv, const double *__restrict__ V,

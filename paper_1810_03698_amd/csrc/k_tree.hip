@@ -396,10 +396,9 @@ __device__ void p2p_task_body(const T *__restrict__ src, const T *__restrict__ t
       py[k] = tgt[N + tl];
       pz[k] = tgt[2 * N + tl];
     }
-    double S[TPT][4];
+    double S[TPT][2];
 #pragma unroll
-    for (int k = 0; k < TPT; ++k)
-      for (int c = 0; c < 4; ++c) S[k][c] = 0.0;
+    for (int k = 0; k < TPT; ++k) S[k][0] = S[k][1] = 0.0;
     for (int l = lb; l < le; ++l) {
       const int s0 = ranges[2 * l], s1 = ranges[2 * l + 1];
       for (int jt = s0; jt < s1; jt += kTileT) {
@@ -407,52 +406,18 @@ __device__ void p2p_task_body(const T *__restrict__ src, const T *__restrict__ t
         __syncthreads();
         stage_records<T, kTileT>(src + (size_t)jt * 16, sh, nj, lane);
         __syncthreads();
-        T a[TPT][4];
+        T a[TPT][2];
 #pragma unroll
-        for (int k = 0; k < TPT; ++k)
-          for (int c = 0; c < 4; ++c) a[k][c] = T(0);
+        for (int k = 0; k < TPT; ++k) a[k][0] = a[k][1] = T(0);
         for (int jj = active ? gi : nj; jj < nj; jj += G) {
           const T *r = sh + 16 * jj;
 #pragma unroll
-          for (int k = 0; k < TPT; ++k) {
-            if constexpr (sizeof(T) == 4) {
-              // as the direct FP32 product: single layer per node with the
-              // strength, double layer per panel through the shared n.R
-              float kl = 0.f, A = 0.f, B = 0.f, d0[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-              for (int q = 0; q < NF; ++q) {
-                const float dx = px[k] - r[3 * q], dy = py[k] - r[3 * q + 1],
-                            dz = pz[k] - r[3 * q + 2];
-                if (q == 0) {
-                  d0[0] = dx;
-                  d0[1] = dy;
-                  d0[2] = dz;
-                }
-                float ri, er;
-                node_core<FLOOR>(dx, dy, dz, nk, ri, er);
-                const float ri2 = ri * ri;
-                a[k][0] = fmaf(r[13], ri, a[k][0]);
-                a[k][2] = fmaf(r[13], er, a[k][2]);
-                kl = fmaf(ri2, ri, kl);
-                A = fmaf(er, ri2, A);
-                B = fmaf(er, ri, B);
-              }
-              const float skn = r[14] * normal_dist(r[9], r[10], r[11], d0[0], d0[1], d0[2]);
-              a[k][1] = fmaf(skn, kl, a[k][1]);
-              a[k][3] = fmaf(skn, fmaf(kappa, B, A), a[k][3]);
-            } else {
-              T t4[4];
-              panel_terms<T>(r, NF, px[k], py[k], pz[k], kappa, nk, t4);
-              a[k][0] += r[13] * t4[0];
-              a[k][1] += r[14] * t4[1];
-              a[k][2] += r[13] * t4[2];
-              a[k][3] += r[14] * t4[3];
-            }
-          }
+          for (int k = 0; k < TPT; ++k)
+            panel_rows<NF, FLOOR>(r, px[k], py[k], pz[k], kappa, nk, a[k][0], a[k][1]);
         }
 #pragma unroll
         for (int k = 0; k < TPT; ++k)
-          for (int c = 0; c < 4; ++c) S[k][c] += (double)a[k][c];
+          for (int c = 0; c < 2; ++c) S[k][c] += (double)a[k][c];
       }
     }
     if (G > 1) {
@@ -460,7 +425,7 @@ __device__ void p2p_task_body(const T *__restrict__ src, const T *__restrict__ t
       // li + g L); every lane takes part in the shuffles
 #pragma unroll
       for (int k = 0; k < TPT; ++k)
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < 2; ++c) {
           const double v = S[k][c];
           double acc = v;
           for (int g = 1; g < G; ++g) acc += __shfl(v, li + g * L, 64);
@@ -471,7 +436,7 @@ __device__ void p2p_task_body(const T *__restrict__ src, const T *__restrict__ t
 #pragma unroll
       for (int k = 0; k < TPT; ++k)
         if (ti[k] < t1)
-          for (int c = 0; c < 4; ++c) part[((size_t)slot * 4 + c) * N + ti[k]] = S[k][c];
+          for (int c = 0; c < 2; ++c) part[((size_t)slot * 2 + c) * N + ti[k]] = S[k][c];
   }
 }
 
@@ -526,7 +491,7 @@ __global__ __launch_bounds__(64) void k_m2p_tasks(int ntask, const int *__restri
                                                   const double *__restrict__ center,
                                                   const T *__restrict__ mom,
                                                   const T *__restrict__ tgt, int N,
-                                                  T kappa, T nk,
+                                                  T kappa, T nk, double eps_ratio,
                                                   double *__restrict__ part) {
   constexpr Multi<P + 1> mi{};
   constexpr int NC = Orders<P>::NV, NK = Orders<P>::NK, NM = Orders<P>::NM;
@@ -636,8 +601,10 @@ __global__ __launch_bounds__(64) void k_m2p_tasks(int ntask, const int *__restri
         const double v = sum[c];
         for (int g = 1; g < G; ++g) sum[c] += __shfl(v, li + g * L, 64);
       }
-    if (gi == 0 && t < t1)
-      for (int c = 0; c < 4; ++c) part[((size_t)slot * 4 + c) * N + t] = sum[c];
+    if (gi == 0 && t < t1) {
+      part[(size_t)slot * 2 * N + t] = sum[1] - sum[0];
+      part[((size_t)slot * 2 + 1) * N + t] = eps_ratio * sum[2] - sum[3];
+    }
   }
 }
 
@@ -659,51 +626,49 @@ __global__ __launch_bounds__(kFinBlock) void k_finish_slots(
   const int i = t / kFinLanes, u = t % kFinLanes;
   const bool live = i < N;
   const int il = live ? i : N - 1;
-  double S[4] = {0.0, 0.0, 0.0, 0.0};
+  double S[2] = {0.0, 0.0};
   const int ns = tslots[il];
   for (int c = u; c < ns; c += kFinLanes)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) S[k] += part[((size_t)c * 4 + k) * N + il];
+    for (int k = 0; k < 2; ++k) S[k] += part[((size_t)c * 2 + k) * N + il];
   const int e1 = rowptr[il + 1];
   for (int e = rowptr[il] + u; e < e1; e += kFinLanes) {
     const int j = col[e];
     const double ph = x[j], dp = x[N + j];
     const double *v = val + 4 * (size_t)e;
-    S[0] += v[0] * dp;
-    S[1] += v[1] * ph;
-    S[2] += v[2] * dp;
-    S[3] += v[3] * ph;
+    S[0] += v[1] * ph - v[0] * dp;
+    S[1] += eps_ratio * v[2] * dp - v[3] * ph;
   }
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
+  for (int k = 0; k < 2; ++k) {
     S[k] += __shfl_xor(S[k], 1, kFinLanes);
     S[k] += __shfl_xor(S[k], 2, kFinLanes);
   }
   if (!live || u != 0) return;
   const double ph = x[i];
-  y[i] = 0.5 * ph + S[1] - S[0];
-  y[N + i] = 0.5 * ph - S[3] + eps_ratio * S[2];
+  y[i] = 0.5 * ph + S[0];
+  y[N + i] = 0.5 * ph + S[1];
 }
 
 template <class T, int P>
 void launch_m2p_p(Tree &t, hipStream_t s, const T *mom, const T *tgt, int N, T kappa,
-                  T nk, double *part) {
+                  T nk, double eps_ratio, double *part) {
   const int nb = ((t.n_m2p_tasks + 7) / 8) * 8;
   hipLaunchKernelGGL((k_m2p_tasks<T, P>), dim3(nb), dim3(64), 0, s, t.n_m2p_tasks,
                      t.d_m2p_task.p, t.d_m2p_slot.p, t.d_m2p_box.p, t.d_center.p, mom,
-                     tgt, N, kappa, nk, part);
+                     tgt, N, kappa, nk, eps_ratio, part);
 }
 
 template <class T>
 void launch_m2p(Tree &t, hipStream_t s, const T *mom, const T *tgt, int N, T kappa, T nk,
-                double *part) {
+                double eps_ratio, double *part) {
   switch (t.prm.order) {
-    case 1: launch_m2p_p<T, 1>(t, s, mom, tgt, N, kappa, nk, part); break;
-    case 2: launch_m2p_p<T, 2>(t, s, mom, tgt, N, kappa, nk, part); break;
-    case 3: launch_m2p_p<T, 3>(t, s, mom, tgt, N, kappa, nk, part); break;
-    case 4: launch_m2p_p<T, 4>(t, s, mom, tgt, N, kappa, nk, part); break;
-    case 5: launch_m2p_p<T, 5>(t, s, mom, tgt, N, kappa, nk, part); break;
-    case 6: launch_m2p_p<T, 6>(t, s, mom, tgt, N, kappa, nk, part); break;
+    case 1: launch_m2p_p<T, 1>(t, s, mom, tgt, N, kappa, nk, eps_ratio, part); break;
+    case 2: launch_m2p_p<T, 2>(t, s, mom, tgt, N, kappa, nk, eps_ratio, part); break;
+    case 3: launch_m2p_p<T, 3>(t, s, mom, tgt, N, kappa, nk, eps_ratio, part); break;
+    case 4: launch_m2p_p<T, 4>(t, s, mom, tgt, N, kappa, nk, eps_ratio, part); break;
+    case 5: launch_m2p_p<T, 5>(t, s, mom, tgt, N, kappa, nk, eps_ratio, part); break;
+    case 6: launch_m2p_p<T, 6>(t, s, mom, tgt, N, kappa, nk, eps_ratio, part); break;
     default: throw Error(PBMP_EARG, "treecode order must be 1..6");
   }
 }
@@ -757,28 +722,27 @@ void launch_moments(Tree &t, hipStream_t s, int nf, const double *src64, float *
 //   V^T: sum_k L_k h^k,   K^T: n . grad_h sum_k L_k h^k,
 // the transpose of forming every box's moments from its nodes.
 
-template <class T, int NF, int SPT>
+template <class T, int NF, int SPT, bool FLOOR>
 __device__ void p2pT_body(const T *__restrict__ src, const T *__restrict__ tgt,
                           const double *__restrict__ z, const double *__restrict__ geo, int N,
                           int s0, int s1, const int *__restrict__ ranges, int lb, int le,
-                          T kappa, T nk, int slot, double *__restrict__ part, T *sh, int G,
-                          int L) {
+                          T kappa, T nk, double eps_ratio, int slot, double *__restrict__ part,
+                          T *sh, int G, int L) {
   const int lane = (int)threadIdx.x;
   const int gi = lane / L, li = lane - gi * L;
   const bool active = gi < G;
   for (int sb = s0; sb < s1; sb += L * SPT) {
-    T rec[SPT][16];
+    T rec[SPT][12];
     int sj[SPT];
 #pragma unroll
     for (int k = 0; k < SPT; ++k) {
       sj[k] = sb + k * L + li;
       const int jl = min(sj[k], s1 - 1);
-      for (int c = 0; c < 16; ++c) rec[k][c] = src[16 * (size_t)jl + c];
+      for (int c = 0; c < 12; ++c) rec[k][c] = src[16 * (size_t)jl + c];
     }
-    double S[SPT][4];
+    double S[SPT][2];
 #pragma unroll
-    for (int k = 0; k < SPT; ++k)
-      for (int c = 0; c < 4; ++c) S[k][c] = 0.0;
+    for (int k = 0; k < SPT; ++k) S[k][0] = S[k][1] = 0.0;
     for (int l = lb; l < le; ++l) {
       const int a0 = ranges[2 * l], a1 = ranges[2 * l + 1];
       for (int it = a0; it < a1; it += 64) {
@@ -786,38 +750,33 @@ __device__ void p2pT_body(const T *__restrict__ src, const T *__restrict__ tgt,
         __syncthreads();
         if (lane < nt) {
           const int i = it + lane;
-          sh[5 * lane] = tgt[i];
-          sh[5 * lane + 1] = tgt[N + i];
-          sh[5 * lane + 2] = tgt[2 * N + i];
-          sh[5 * lane + 3] = (T)z[i];
-          sh[5 * lane + 4] = (T)z[N + i];
+          sh[8 * lane] = tgt[i];
+          sh[8 * lane + 1] = tgt[N + i];
+          sh[8 * lane + 2] = tgt[2 * N + i];
+          sh[8 * lane + 3] = (T)z[i];
+          sh[8 * lane + 4] = (T)z[N + i];
+          sh[8 * lane + 5] = (T)(eps_ratio * z[N + i]);
         }
         __syncthreads();
-        T a[SPT][4];
+        T a[SPT][2];
 #pragma unroll
-        for (int k = 0; k < SPT; ++k)
-          for (int c = 0; c < 4; ++c) a[k][c] = T(0);
+        for (int k = 0; k < SPT; ++k) a[k][0] = a[k][1] = T(0);
         for (int e = active ? gi : nt; e < nt; e += G) {
-          const T *r = sh + 5 * e;
+          const T *r = sh + 8 * e;
 #pragma unroll
-          for (int k = 0; k < SPT; ++k) {
-            T t4[4];
-            panel_terms<T>(rec[k], NF, r[0], r[1], r[2], kappa, nk, t4);
-            a[k][0] += r[3] * t4[0];
-            a[k][1] += r[3] * t4[1];
-            a[k][2] += r[4] * t4[2];
-            a[k][3] += r[4] * t4[3];
-          }
+          for (int k = 0; k < SPT; ++k)
+            panel_columns<NF, FLOOR>(rec[k], r[0], r[1], r[2], r[3], r[4], r[5], kappa, nk,
+                                     a[k][0], a[k][1]);
         }
 #pragma unroll
         for (int k = 0; k < SPT; ++k)
-          for (int c = 0; c < 4; ++c) S[k][c] += (double)a[k][c];
+          for (int c = 0; c < 2; ++c) S[k][c] += (double)a[k][c];
       }
     }
     if (G > 1) {
 #pragma unroll
       for (int k = 0; k < SPT; ++k)
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < 2; ++c) {
           const double v = S[k][c];
           double acc = v;
           for (int g = 1; g < G; ++g) acc += __shfl(v, li + g * L, 64);
@@ -829,12 +788,12 @@ __device__ void p2pT_body(const T *__restrict__ src, const T *__restrict__ tgt,
       for (int k = 0; k < SPT; ++k)
         if (sj[k] < s1) {
           const double wA = geo[6 * (size_t)N + sj[k]] * kInv4PiT / NF;
-          for (int c = 0; c < 4; ++c) part[((size_t)slot * 4 + c) * N + sj[k]] = wA * S[k][c];
+          for (int c = 0; c < 2; ++c) part[((size_t)slot * 2 + c) * N + sj[k]] = wA * S[k][c];
         }
   }
 }
 
-template <class T, int NF>
+template <class T, int NF, bool FLOOR>
 __global__ __launch_bounds__(64) void k_p2pT_tasks(int ntask, const int *__restrict__ tasks,
                                                    const int *__restrict__ range,
                                                    const int *__restrict__ subs,
@@ -842,8 +801,9 @@ __global__ __launch_bounds__(64) void k_p2pT_tasks(int ntask, const int *__restr
                                                    const T *__restrict__ tgt,
                                                    const double *__restrict__ z,
                                                    const double *__restrict__ geo, int N,
-                                                   T kappa, T nk, double *__restrict__ part) {
-  __shared__ T sh[64 * 5];
+                                                   T kappa, T nk, double eps_ratio,
+                                                   double *__restrict__ part) {
+  __shared__ __align__(16) T sh[64 * 8];
   const int task = xcd_task(ntask);
   if (task < 0) return;
   const int B = tasks[4 * task], lb = tasks[4 * task + 1], le = tasks[4 * task + 2];
@@ -864,11 +824,11 @@ __global__ __launch_bounds__(64) void k_p2pT_tasks(int ntask, const int *__restr
     }
   }
   if (spt == 1)
-    p2pT_body<T, NF, 1>(src, tgt, z, geo, N, s0, s1, subs, lb, le, kappa, nk, slot, part, sh,
-                        G, 64 / G);
+    p2pT_body<T, NF, 1, FLOOR>(src, tgt, z, geo, N, s0, s1, subs, lb, le, kappa, nk, eps_ratio, slot,
+                        part, sh, G, 64 / G);
   else
-    p2pT_body<T, NF, 2>(src, tgt, z, geo, N, s0, s1, subs, lb, le, kappa, nk, slot, part, sh,
-                        G, 64 / G);
+    p2pT_body<T, NF, 2, FLOOR>(src, tgt, z, geo, N, s0, s1, subs, lb, le, kappa, nk, eps_ratio, slot,
+                        part, sh, G, 64 / G);
 }
 
 // M2P^T: per task (box B, target sub-ranges) the partial local coefficients
@@ -985,7 +945,7 @@ __global__ __launch_bounds__(64) void k_l2p(const int *__restrict__ leaves,
                                             const double *__restrict__ src64,
                                             const double *__restrict__ geo,
                                             const int *__restrict__ tslotsT, int N,
-                                            double *__restrict__ part) {
+                                            double eps_ratio, double *__restrict__ part) {
   constexpr Multi<P> mi{};
   constexpr Multi<P + 1> miK{};
   constexpr int NC = Orders<P>::NV, NK = Orders<P>::NK;
@@ -1004,14 +964,16 @@ __global__ __launch_bounds__(64) void k_l2p(const int *__restrict__ leaves,
   const int nc = nchain;
   for (int e = threadIdx.x; e < nc * 2 * NK; e += 64) {
     const int a = e / (2 * NK), k = e % (2 * NK);
-    lp[a][k] = Lb[(size_t)chain[a] * 2 * NK + k];
+    // the two sums a node takes: K_L - K_Y and eps V_Y - V_L
+    const double *Lc = Lb + (size_t)chain[a] * 2 * NK;
+    lp[a][k] = k < NK ? Lc[k] - Lc[NK + k] : eps_ratio * Lc[k] - Lc[k - NK];
   }
   for (int e = threadIdx.x; e < nc * 3; e += 64) lc[e / 3][e % 3] = center[3 * chain[e / 3] + e % 3];
   __syncthreads();
   for (int j = range[2 * B] + (int)threadIdx.x; j < range[2 * B + 1]; j += 64) {
     const double *r = src64 + 16 * (size_t)j;
     const double n[3] = {r[9], r[10], r[11]};
-    double out[4] = {0.0, 0.0, 0.0, 0.0};
+    double out[2] = {0.0, 0.0};
     for (int a = 0; a < nc; ++a) {
       for (int q = 0; q < NF; ++q) {
         const double h[3] = {r[3 * q] - lc[a][0], r[3 * q + 1] - lc[a][1],
@@ -1029,18 +991,14 @@ __global__ __launch_bounds__(64) void k_l2p(const int *__restrict__ leaves,
 #pragma unroll
           for (int d = 0; d < 3; ++d)
             if (miK.m1[k][d] >= 0) dn += miK.e[k][d] * n[d] * mono[miK.m1[k][d]];
-          if (k < NC) {
-            out[0] += lp[a][k] * mono[k];
-            out[2] += lp[a][NK + k] * mono[k];
-          }
-          out[1] += lp[a][k] * dn;
-          out[3] += lp[a][NK + k] * dn;
+          if (k < NC) out[1] += lp[a][NK + k] * mono[k];
+          out[0] += lp[a][k] * dn;
         }
       }
     }
     const double wA = geo[6 * (size_t)N + j] * kInv4PiT / NF;
     const int slot = tslotsT[j] - 1;
-    for (int k = 0; k < 4; ++k) part[((size_t)slot * 4 + k) * N + j] = wA * out[k];
+    for (int k = 0; k < 2; ++k) part[((size_t)slot * 2 + k) * N + j] = wA * out[k];
   }
 }
 
@@ -1053,37 +1011,37 @@ __global__ void k_finish_T_slots(int N, const int *__restrict__ tslotsT,
                                  double eps_ratio, double *__restrict__ y) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= N) return;
-  double S[4] = {0.0, 0.0, 0.0, 0.0};
+  double S[2] = {0.0, 0.0};
   const int ns = tslotsT[j];
   for (int c = 0; c < ns; ++c)
-    for (int k = 0; k < 4; ++k) S[k] += part[((size_t)c * 4 + k) * N + j];
+    for (int k = 0; k < 2; ++k) S[k] += part[((size_t)c * 2 + k) * N + j];
   for (int t = trow[j]; t < trow[j + 1]; ++t) {
     const int i = tcol[t];
     const size_t e = tent[t];
-    S[0] += val[4 * e] * z[i];
-    S[1] += val[4 * e + 1] * z[i];
-    S[2] += val[4 * e + 2] * z[N + i];
-    S[3] += val[4 * e + 3] * z[N + i];
+    S[0] += val[4 * e + 1] * z[i] - val[4 * e + 3] * z[N + i];
+    S[1] += eps_ratio * val[4 * e + 2] * z[N + i] - val[4 * e] * z[i];
   }
-  y[j] = 0.5 * z[j] + S[1] + 0.5 * z[N + j] - S[3];
-  y[N + j] = -S[0] + eps_ratio * S[2];
+  y[j] = 0.5 * z[j] + 0.5 * z[N + j] + S[0];
+  y[N + j] = S[1];
 }
 
 template <class T, int P>
 void tree_T_far(Tree &t, hipStream_t s, int nf, int N, const double *geo,
                 const double *src64, const T *src, const T *tgt, const double *z, T kappa,
-                T nk, double *part) {
+                T nk, double eps_ratio, double *part, bool floor_r2) {
   constexpr int NK = Orders<P>::NK;
   // P2P^T
   const int nbp = ((t.n_p2pT_tasks + 7) / 8) * 8;
-  if (nf == 3)
-    hipLaunchKernelGGL((k_p2pT_tasks<T, 3>), dim3(nbp), dim3(64), 0, s, t.n_p2pT_tasks,
-                       t.d_p2pT_task.p, t.d_range.p, t.d_p2pT_sub.p, src, tgt, z, geo, N,
-                       kappa, nk, part);
-  else
-    hipLaunchKernelGGL((k_p2pT_tasks<T, 1>), dim3(nbp), dim3(64), 0, s, t.n_p2pT_tasks,
-                       t.d_p2pT_task.p, t.d_range.p, t.d_p2pT_sub.p, src, tgt, z, geo, N,
-                       kappa, nk, part);
+#define PBMP_TPT(NFV, FL)                                                                 \
+  hipLaunchKernelGGL((k_p2pT_tasks<T, NFV, (FL) || sizeof(T) == 8>), dim3(nbp), dim3(64), 0, s, \
+                     t.n_p2pT_tasks, t.d_p2pT_task.p, t.d_range.p, t.d_p2pT_sub.p, src, tgt, z, geo, N,     \
+                     kappa, nk, eps_ratio, part)
+  // (the FP64 pair terms carry their own cut-off)
+  if (nf == 3 && floor_r2) PBMP_TPT(3, true);
+  else if (nf == 3) PBMP_TPT(3, false);
+  else if (floor_r2) PBMP_TPT(1, true);
+  else PBMP_TPT(1, false);
+#undef PBMP_TPT
   // M2P^T, per-box sums, L2L down the levels, L2P at the leaves
   t.d_Lpart.reserve((size_t)std::max(1, t.n_m2pT_tasks) * 2 * NK);
   t.d_L.reserve((size_t)t.nbox * 2 * NK);
@@ -1102,25 +1060,30 @@ void tree_T_far(Tree &t, hipStream_t s, int nf, int N, const double *geo,
   if (nf == 3)
     hipLaunchKernelGGL((k_l2p<P, 3>), dim3(t.nleaf), dim3(64), 0, s, t.d_leaves.p,
                        t.d_range.p, t.d_parent.p, t.d_m2pT_count.p, t.d_center.p, t.d_L.p,
-                       src64, geo, t.d_tslotsT.p, N, part);
+                       src64, geo, t.d_tslotsT.p, N, eps_ratio, part);
   else
     hipLaunchKernelGGL((k_l2p<P, 1>), dim3(t.nleaf), dim3(64), 0, s, t.d_leaves.p,
                        t.d_range.p, t.d_parent.p, t.d_m2pT_count.p, t.d_center.p, t.d_L.p,
-                       src64, geo, t.d_tslotsT.p, N, part);
+                       src64, geo, t.d_tslotsT.p, N, eps_ratio, part);
   PBMP_HIP(hipGetLastError());
 }
 
 template <class T>
 void tree_T_far_p(Tree &t, hipStream_t s, int nf, int N, const double *geo,
                   const double *src64, const T *src, const T *tgt, const double *z, T kappa,
-                  T nk, double *part) {
+                  T nk, double eps_ratio, double *part, bool floor_r2) {
   switch (t.prm.order) {
-    case 1: tree_T_far<T, 1>(t, s, nf, N, geo, src64, src, tgt, z, kappa, nk, part); break;
-    case 2: tree_T_far<T, 2>(t, s, nf, N, geo, src64, src, tgt, z, kappa, nk, part); break;
-    case 3: tree_T_far<T, 3>(t, s, nf, N, geo, src64, src, tgt, z, kappa, nk, part); break;
-    case 4: tree_T_far<T, 4>(t, s, nf, N, geo, src64, src, tgt, z, kappa, nk, part); break;
-    case 5: tree_T_far<T, 5>(t, s, nf, N, geo, src64, src, tgt, z, kappa, nk, part); break;
-    case 6: tree_T_far<T, 6>(t, s, nf, N, geo, src64, src, tgt, z, kappa, nk, part); break;
+#define PBMP_TF(P)                                                                          \
+  case P:                                                                                   \
+    tree_T_far<T, P>(t, s, nf, N, geo, src64, src, tgt, z, kappa, nk, eps_ratio, part, floor_r2); \
+    break;
+    PBMP_TF(1)
+    PBMP_TF(2)
+    PBMP_TF(3)
+    PBMP_TF(4)
+    PBMP_TF(5)
+    PBMP_TF(6)
+#undef PBMP_TF
     default: throw Error(PBMP_EARG, "treecode order must be 1..6");
   }
 }
@@ -1570,7 +1533,7 @@ void tree_upload_exponents(Tree &t, hipStream_t s) {
 
 void tree_apply(Tree &t, hipStream_t s, bool fp64, int nf, int N, const double *geo,
                 const double *src64, const float *src32, const float *tgt32,
-                double kappa, double *part, KernelClock &clk, bool floor_r2) {
+                double kappa, double eps_ratio, double *part, KernelClock &clk, bool floor_r2) {
   hipEvent_t e0 = clk.on ? clk.begin(s) : nullptr;
   launch_moments(t, s, nf, src64, fp64 ? nullptr : t.d_mom32.p);
   PBMP_HIP(hipGetLastError());
@@ -1600,9 +1563,9 @@ void tree_apply(Tree &t, hipStream_t s, bool fp64, int nf, int N, const double *
   if (t.n_m2p_tasks > 0 && t.n_m2p_entries > 0) {
     e0 = clk.on ? clk.begin(s) : nullptr;
     if (fp64)
-      launch_m2p<double>(t, s, t.d_mom64.p, geo, N, kappa, 0.0, part);
+      launch_m2p<double>(t, s, t.d_mom64.p, geo, N, kappa, 0.0, eps_ratio, part);
     else
-      launch_m2p<float>(t, s, t.d_mom32.p, tgt32, N, (float)kappa, nk32, part);
+      launch_m2p<float>(t, s, t.d_mom32.p, tgt32, N, (float)kappa, nk32, eps_ratio, part);
     PBMP_HIP(hipGetLastError());
     if (clk.on) clk.end(s, e0, KernelClock::M2P, t.m2p_pairs);
   }
@@ -1642,12 +1605,13 @@ void tree_apply_transpose(Tree &t, hipStream_t s, bool fp64, int nf, int N, cons
                           const double *src64, const float *src32, const float *tgt32,
                           const double *z, double kappa, double *part, const int *trow,
                           const int *tcol, const int *tent, const double *val, double eps_ratio,
-                          double *y) {
+                          double *y, bool floor_r2) {
   if (fp64)
-    tree_T_far_p<double>(t, s, nf, N, geo, src64, src64, geo, z, kappa, 0.0, part);
+    tree_T_far_p<double>(t, s, nf, N, geo, src64, src64, geo, z, kappa, 0.0, eps_ratio, part,
+                         floor_r2);
   else
     tree_T_far_p<float>(t, s, nf, N, geo, src64, src32, tgt32, z, (float)kappa,
-                        (float)(-kappa * 1.4426950408889634), part);
+                        (float)(-kappa * 1.4426950408889634), eps_ratio, part, floor_r2);
   hipLaunchKernelGGL(k_finish_T_slots, dim3((N + 255) / 256), dim3(256), 0, s, N,
                      t.d_tslotsT.p, part, trow, tcol, tent, val, z, eps_ratio, y);
   PBMP_HIP(hipGetLastError());

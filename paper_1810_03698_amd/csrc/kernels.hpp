@@ -32,15 +32,20 @@ void launch_winding(hipStream_t s, int N, int M, const double *verts,
                     const int *tri, const double *pts, double *wind);
 
 // Strengths of the product: s_V = w_q A phi'/(4 pi), s_K = w_q A phi/(4 pi)
-// written into slots 13, 14 of src64 and src32.  x = [phi; dphi] [2N].
-void launch_pack_strengths(hipStream_t s, int N, int nf, const double *geo,
-                           const double *x, double *src64, float *src32);
+// and eps_ratio s_V written into slots 13, 14, 15 of src64 and src32.
+// x = [phi; dphi] [2N].
+void launch_pack_strengths(hipStream_t s, int N, int nf, double eps_ratio,
+                           const double *geo, const double *x, double *src64,
+                           float *src32);
 
 // Direct far-field sums over all panels of the source range, per target:
-// part[(chunk*4 + k)*Nt + i], k = V_L, K_L, V_Y, K_Y.
+// part[(chunk*2 + k)*Nt + i], the far field of the two rows of y = A x:
+// k = 0: K_L - V_L, k = 1: eps V_Y - K_Y.
 // floor_r2: FP32 pairs closer than 1e-4 A add nothing (needed only for the
 // one-node rule, or panels small enough for a node and a centroid to
 // coincide in FP32).
+// nchunk: source chunks, direct_chunks(fp64, N).
+int direct_chunks(bool fp64, int N);
 void launch_p2p_direct(hipStream_t s, bool fp64, int nf, int N, int Nt,
                        const double *src64, const float *src32,
                        const double *geo, const float *tgt32, double kappa,
@@ -59,7 +64,7 @@ void launch_transpose(hipStream_t s, bool fp64, int nf, int N,
                       const double *geo, const float *tgt32, const double *z,
                       double kappa, int nchunk, double *part,
                       const int *trow, const int *tcol, const int *tent,
-                      const double *val, double eps_ratio, double *y);
+                      const double *val, double eps_ratio, double *y, bool floor_r2);
 
 // Right-hand side f[N] (eq. rhs_multipole) from sites (xyz[3M], q[M],
 // p[3M], Q9[9M]); fp64 selects FP64 pair terms, else FP32 pair terms with
@@ -164,11 +169,11 @@ void launch_scale(hipStream_t s, int n, double a, const double *x, double *y);
 class Tree;
 struct KernelClock;
 // Treecode far field: P2M/M2M moments, P2P over near leaves and M2P over
-// accepted boxes, into part[slot][4][N].
+// accepted boxes, into part[slot][2][N] (the two rows of y = A x).
 void tree_apply(Tree &t, hipStream_t s, bool fp64, int nf, int N,
                 const double *geo, const double *src64, const float *src32,
-                const float *tgt32, double kappa, double *part, KernelClock &clk,
-                bool floor_r2);
+                const float *tgt32, double kappa, double eps_ratio, double *part,
+                KernelClock &clk, bool floor_r2);
 // finish with a per-target number of partial slots
 // A^T z with the treecode (transposed P2P, M2P^T + L2L + L2P, transposed
 // near/self correction)
@@ -176,7 +181,7 @@ void tree_apply_transpose(Tree &t, hipStream_t s, bool fp64, int nf, int N, cons
                           const double *src64, const float *src32, const float *tgt32,
                           const double *z, double kappa, double *part, const int *trow,
                           const int *tcol, const int *tent, const double *val, double eps_ratio,
-                          double *y);
+                          double *y, bool floor_r2);
 // Far-field part of the mesh adjoint with the treecode: d/d(collocation
 // points) gc [3N] and d/d(far nodes, normals, areas) gy [9N], gn [3N],
 // gA [N] of lambda . A x (assigned, not accumulated); part: the product's

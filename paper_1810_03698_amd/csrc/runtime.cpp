@@ -459,9 +459,7 @@ void Runtime::alloc_work() {
   const int n = 2 * N;
   const int m = o.gmres_restart;
   // direct-product chunking: enough blocks to fill the device
-  const int tpt = fp64() ? 1 : 2;
-  const int bx = (N + 256 * tpt - 1) / (256 * tpt);
-  p2p_chunks_ = std::max(1, std::min((2048 + bx - 1) / bx, (N + 127) / 128));
+  p2p_chunks_ = direct_chunks(fp64(), N);
   int slots = p2p_chunks_;
   if (tree_active_) slots = std::max({slots, tree_->max_slots, tree_->max_slots_T});
   part_.alloc((size_t)slots * 4 * N);
@@ -611,10 +609,10 @@ void Runtime::apply(const double *x, double *y, bool f64, bool packed) {
   // refinement products are FP64 by request: kept out of the kernel timers
   const bool timed = clock.on;
   if (f64 && !fp64()) clock.on = false;
-  if (!packed) launch_pack_strengths(s_, N, ru_.nf, geo_.p, x, src64_.p, src32_.p);
+  if (!packed) launch_pack_strengths(s_, N, ru_.nf, o.eps_in / o.eps_out, geo_.p, x, src64_.p, src32_.p);
   if (use_tree()) {
     tree_apply(*tree_, s_, use64, ru_.nf, N, geo_.p, src64_.p, src32_.p,
-               tgt32_.p, o.kappa, part_.p, clock, floor_r2_);
+               tgt32_.p, o.kappa, o.eps_in / o.eps_out, part_.p, clock, floor_r2_);
     launch_finish_slots(s_, N, tree_->d_tslots.p, part_.p, nrow_.p, ncol_.p,
                         val, x, o.eps_in / o.eps_out, y);
   } else {
@@ -869,7 +867,7 @@ int Runtime::gmres_generic(int n, const KOp &op, const KPrec &prec, const double
 
 // ------------------------------------------------------------- readout
 void Runtime::readout(const double *x, bool full, double *out) {
-  launch_pack_strengths(s_, N_, ru_.nf, geo_.p, x, src64_.p, src32_.p);
+  launch_pack_strengths(s_, N_, ru_.nf, o.eps_in / o.eps_out, geo_.p, x, src64_.p, src32_.p);
   launch_readout(s_, fp64(), full, N_, M_, src64_.p, src32_.p, geo_.p, verts_.p,
                  tri_.p, ru_, x, sxyz_.p, srow_.p, scol_.p, ro_chunks_, rpart_.p,
                  out);
