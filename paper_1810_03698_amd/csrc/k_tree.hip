@@ -22,6 +22,7 @@
 
 #include <type_traits>
 
+#include "harmonic.hpp"
 #include "kernels.hpp"
 #include "pair.hpp"
 #include "runtime.hpp"
@@ -79,6 +80,8 @@ template <int P> struct Orders {
   static constexpr int NV = Multi<P>::n;
   static constexpr int NK = Multi<P + 1>::n;
   static constexpr int NM = NV + NK;
+  static constexpr int L = P + 1;       // degree of the harmonic form
+  static constexpr int NS = Harm<L>::S; // its words per box
 };
 
 // blockIdx -> task: consecutive tasks (neighbouring target leaves, similar
@@ -109,14 +112,13 @@ constexpr int kP2MTile = 64;  // panels per LDS tile (64 and 192 nodes: multiple
 static_assert(kP2MThreads % 64 == 0 && kP2MTile % kP2MThreads == 0, "P2M tiling");
 
 // direct: every leaf is one task, so the task's sums are the leaf's moments
-// and go straight to mom64 (and mom32 when not null) instead of part
+// and go straight to mom64 instead of part
 template <int P>
 __global__ __launch_bounds__(kP2MThreads) void k_p2m_tasks(int nf, const int *__restrict__ tasks,
                                                    const double *__restrict__ center,
                                                    const double *__restrict__ src,
                                                    double *__restrict__ part, int direct,
-                                                   double *__restrict__ mom64,
-                                                   float *__restrict__ mom32) {
+                                                   double *__restrict__ mom64) {
   constexpr Multi<P> mi{};
   constexpr Multi<P + 1> miK{};
   constexpr int NC = Orders<P>::NV, NK = Orders<P>::NK, NM = Orders<P>::NM;
@@ -202,23 +204,17 @@ __global__ __launch_bounds__(kP2MThreads) void k_p2m_tasks(int nf, const int *__
   for (int k = threadIdx.x; k < NM; k += kP2MThreads) {
     double v = red[0][k];
     for (int w = 1; w < NW; ++w) v += red[w][k];
-    if (direct) {
-      mom64[(size_t)B * NM + k] = v;
-      if (mom32) mom32[(size_t)B * NM + k] = (float)v;
-    } else {
-      part[(size_t)blockIdx.x * NM + k] = v;
-    }
+    if (direct) mom64[(size_t)B * NM + k] = v;
+    else part[(size_t)blockIdx.x * NM + k] = v;
   }
 }
 
 // mom[B] = sum of the partial moments of B's slices, in slice order
-// (mom32: the FP32 copy the mixed-precision M2P reads, or null; boxes with
-// fewer than min_tasks tasks are skipped: not this pass's, or written by
-// their single task)
+// (boxes with fewer than min_tasks tasks are skipped: not this pass's, or
+// written by their single task)
 __global__ void k_mom_reduce(int nbox, int ncoef2, const int *__restrict__ first,
                              const int *__restrict__ count, const double *__restrict__ part,
-                             double *__restrict__ mom, float *__restrict__ mom32,
-                             int min_tasks) {
+                             double *__restrict__ mom, int min_tasks) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= nbox * ncoef2) return;
   const int B = e / ncoef2, k = e % ncoef2;
@@ -227,7 +223,6 @@ __global__ void k_mom_reduce(int nbox, int ncoef2, const int *__restrict__ first
   double v = 0.0;
   for (int t = t0; t < t0 + nt; ++t) v += part[(size_t)t * ncoef2 + k];
   mom[e] = v;
-  if (mom32) mom32[e] = (float)v;
 }
 
 // Moments of the accepted boxes with children from the leaf moments: with
@@ -246,7 +241,7 @@ __global__ __launch_bounds__(kShiftThreads) void k_shift_tasks(
     const int *__restrict__ tasks, const int *__restrict__ leaves,
     const double *__restrict__ center, const int *__restrict__ monos,
     const int *__restrict__ toff, const int *__restrict__ tjq,
-    const double *__restrict__ tc, double *__restrict__ mom, float *__restrict__ mom32,
+    const double *__restrict__ tc, double *__restrict__ mom,
     const int *__restrict__ count, double *__restrict__ part) {
   // single-layer moments k < NC, double-layer k < NK (the terms of a
   // coefficient reach only coefficients of lower or equal degree, so one
@@ -322,10 +317,6 @@ __global__ __launch_bounds__(kShiftThreads) void k_shift_tasks(
     if (count[B] == 1) {  // the box's only task: its moments
       if (hasV) mom[(size_t)B * NM + k] = aV;
       mom[(size_t)B * NM + NC + k] = aK;
-      if (mom32) {
-        if (hasV) mom32[(size_t)B * NM + k] = (float)aV;
-        mom32[(size_t)B * NM + NC + k] = (float)aK;
-      }
     } else {
       if (hasV) part[(size_t)blockIdx.x * NM + k] = aV;
       part[(size_t)blockIdx.x * NM + NC + k] = aK;
@@ -484,128 +475,150 @@ template <> __device__ inline double expneg_t<double>(double, double kappa, doub
   return exp_fp64(-kappa * r);
 }
 
+// Harmonic words of every box from its Cartesian moments, merged into the two
+// rows of the product: Laplace mK - mV, Yukawa eps mV - mK.  One wave per box,
+// a lane per harmonic (at most 64), its terms (k, C for Laplace, C for Yukawa)
+// from a table; of the order of ten terms each, so latency bound.
 template <class T, int P>
-__global__ __launch_bounds__(64) void k_m2p_tasks(int ntask, const int *__restrict__ tasks,
+__global__ __launch_bounds__(64) void k_harmonics(const double *__restrict__ mom,
+                                                  const int *__restrict__ hoff,
+                                                  const int *__restrict__ hk,
+                                                  const double *__restrict__ hc,
+                                                  const int *__restrict__ hpos,
+                                                  double eps_ratio, T *__restrict__ out) {
+  constexpr int NC = Orders<P>::NV, NM = Orders<P>::NM, NS = Orders<P>::NS;
+  constexpr int NH = Harm<P + 1>::NH;
+  static_assert(NH <= 64, "a lane per harmonic");
+  __shared__ double sm[NM];
+  const double *m = mom + (size_t)blockIdx.x * NM;
+  for (int e = threadIdx.x; e < NM; e += 64) sm[e] = m[e];
+  __syncthreads();
+  T *o = out + (size_t)blockIdx.x * NS;
+  if (threadIdx.x < NH) {
+    double a = 0.0, b = 0.0;
+    for (int t = hoff[threadIdx.x]; t < hoff[threadIdx.x + 1]; ++t) {
+      const int k = hk[t];
+      const double mv = k < NC ? sm[k] : 0.0, mk = sm[NC + k];
+      a += hc[2 * t] * (mk - mv);
+      b += hc[2 * t + 1] * (eps_ratio * mv - mk);
+    }
+    const int pos = hpos[threadIdx.x];
+    o[pos] = (T)a;
+    o[pos + 1] = (T)b;
+  }
+}
+
+// M2P.  A task is a target leaf against a run of its accepted boxes, one wave,
+// TPT targets per lane (the fewest passes): the words of up to kStage boxes
+// pass through LDS and every read serves TPT targets.  VALU issue bound: 220
+// instructions per (target, box) pair at P 5 where the Cartesian recurrences
+// (three families of 84 coefficients) took about 2000: 814 -> 149 us in FP32
+// and 1829 -> 326 us in FP64 on 144500 panels at P 5, 120 -> 44 us in FP32 on
+// 28880 at P 4.  FP32 sums span the boxes of one stage and are added in FP64.
+template <class T, int P> constexpr int m2p_stage() {
+  constexpr int n = kM2PStageBytes / (Orders<P>::NS * (int)sizeof(T));
+  return n < kM2PChunkBoxes ? n : kM2PChunkBoxes;
+}
+
+template <class T, int P, int TPT>
+__device__ void m2p_body(int t0, int t1, int lb, int le, const int *__restrict__ boxes,
+                         const double *__restrict__ center, const T *__restrict__ words,
+                         const T *__restrict__ tgt, int N, T kappa, T nk, int slot,
+                         double *__restrict__ part, T *sh, T *scen, int *sbox) {
+  constexpr int NS = Orders<P>::NS;
+  constexpr int kStage = m2p_stage<T, P>();
+  typedef T v2 __attribute__((ext_vector_type(16 / sizeof(T))));
+  constexpr int UN = NS * (int)sizeof(T) / 16;  // 16-byte units per box
+  const int lane = (int)threadIdx.x;
+  for (int tb = t0; tb < t1; tb += 64 * TPT) {
+    T p[TPT][3];
+    double S[TPT][2];
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) {
+      const int tl = min(tb + 64 * k + lane, t1 - 1);
+      for (int d = 0; d < 3; ++d) p[k][d] = tgt[(size_t)d * N + tl];
+      S[k][0] = S[k][1] = 0.0;
+    }
+    for (int cb = lb; cb < le; cb += kStage) {
+      const int nb = min(kStage, le - cb);
+      if (tb == t0 || le - lb > kStage) {
+        __syncthreads();
+        if (lane < nb) sbox[lane] = boxes[cb + lane];
+        __syncthreads();
+        const v2 *g = reinterpret_cast<const v2 *>(words);
+        v2 *d = reinterpret_cast<v2 *>(sh);
+        for (int e0 = lane; e0 < nb * UN; e0 += 4 * 64) {
+          v2 v[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int e = e0 + 64 * u;
+            if (e < nb * UN) v[u] = g[(size_t)sbox[e / UN] * UN + e % UN];
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int e = e0 + 64 * u;
+            if (e < nb * UN) d[e] = v[u];
+          }
+        }
+        for (int e = lane; e < nb * 3; e += 64) scen[e] = (T)center[3 * sbox[e / 3] + e % 3];
+        __syncthreads();
+      }
+      T acc[TPT][2];
+#pragma unroll
+      for (int k = 0; k < TPT; ++k) acc[k][0] = acc[k][1] = T(0);
+      for (int b = 0; b < nb; ++b) {
+        T D[TPT][3], ri[TPT], ek[TPT];
+#pragma unroll
+        for (int k = 0; k < TPT; ++k) {
+          for (int d = 0; d < 3; ++d) D[k][d] = p[k][d] - scen[3 * b + d];
+          const T R2 = D[k][0] * D[k][0] + D[k][1] * D[k][1] + D[k][2] * D[k][2];
+          ri[k] = rsqrt_t<T>(R2);
+          ek[k] = expneg_t<T>(nk, kappa, R2 * ri[k]);
+        }
+        harmonic_m2p<T, P + 1, TPT>(sh + b * NS, D, ri, ek, kappa, acc);
+      }
+#pragma unroll
+      for (int k = 0; k < TPT; ++k)
+        for (int c = 0; c < 2; ++c) S[k][c] += (double)acc[k][c];
+    }
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) {
+      const int t = tb + 64 * k + lane;
+      if (t < t1)
+        for (int c = 0; c < 2; ++c) part[((size_t)slot * 2 + c) * N + t] = S[k][c];
+    }
+  }
+}
+
+template <class T, int P>
+__global__ __launch_bounds__(64, sizeof(T) == 4 ? 3 : 2) void k_m2p_tasks(int ntask, const int *__restrict__ tasks,
                                                   const int *__restrict__ slots,
                                                   const int *__restrict__ boxes,
                                                   const double *__restrict__ center,
-                                                  const T *__restrict__ mom,
+                                                  const T *__restrict__ words,
                                                   const T *__restrict__ tgt, int N,
-                                                  T kappa, T nk, double eps_ratio,
-                                                  double *__restrict__ part) {
-  constexpr Multi<P + 1> mi{};
-  constexpr int NC = Orders<P>::NV, NK = Orders<P>::NK, NM = Orders<P>::NM;
-  __shared__ T smom[kM2PChunkBoxes * NM];
-  __shared__ T scen[kM2PChunkBoxes * 3];
+                                                  T kappa, T nk, double *__restrict__ part) {
+  constexpr int kStage = m2p_stage<T, P>();
+  __shared__ __align__(16) T sh[kStage * Orders<P>::NS];
+  __shared__ T scen[kStage * 3];
+  __shared__ int sbox[kStage];
   const int task = xcd_task(ntask);
   if (task < 0) return;
   const int t0 = tasks[4 * task], t1 = tasks[4 * task + 1];
   const int lb = tasks[4 * task + 2], le = tasks[4 * task + 3];
   const int slot = slots[task];
-  const int nb = le - lb;
-  const int nt = t1 - t0;
-  // box ids first, then the moments with eight loads in flight per lane
-  __shared__ int sbox[kM2PChunkBoxes];
-  if (threadIdx.x < nb) sbox[threadIdx.x] = boxes[lb + threadIdx.x];
-  __syncthreads();
-  for (int e0 = threadIdx.x; e0 < nb * NM; e0 += 8 * 64) {
-    T v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = e0 + 64 * u;
-      if (e < nb * NM) v[u] = mom[(size_t)sbox[e / NM] * NM + e % NM];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = e0 + 64 * u;
-      if (e < nb * NM) smom[e] = v[u];
-    }
-  }
-  for (int e = threadIdx.x; e < nb * 3; e += 64) scen[e] = (T)center[3 * sbox[e / 3] + e % 3];
-  // optionally lanes in G groups of L = 64 / G (PBMP_M2P_GROUPS): a group
-  // takes every G-th box for all targets, G maximising the useful fraction
-  // nt nb / (64 ceil(nt/L) ceil(nb/G)); off by default (measured slower)
-  int G = 1;
-  {
-    float be = 0.0f;
-    for (int g = 1; g <= 16 * PBMP_M2P_GROUPS; ++g) {
-      const int L = 64 / g;
-      const float e = (float)nt * nb / (64.0f * ((nt + L - 1) / L) * ((nb + g - 1) / g));
-      if (e > be) {
-        be = e;
-        G = g;
-      }
-    }
-  }
-  const int L = 64 / G;
-  const int gi = (int)threadIdx.x / L, li = (int)threadIdx.x - gi * L;
-  const bool active = gi < G;
-  __syncthreads();
-  const int iters = (nt + L - 1) / L;
-  for (int it = 0; it < iters; ++it) {
-    const int t = t0 + it * L + li;
-    const int tl = min(t, t1 - 1);
-    const T x = tgt[tl], y = tgt[N + tl], z = tgt[2 * N + tl];
-    T acc[4] = {T(0), T(0), T(0), T(0)};
-    for (int b = active ? gi : nb; b < nb; b += G) {
-      const T D[3] = {x - scen[3 * b], y - scen[3 * b + 1], z - scen[3 * b + 2]};
-      const T R2 = D[0] * D[0] + D[1] * D[1] + D[2] * D[2];
-      const T ri = rsqrt_t<T>(R2);
-      const T iR2 = ri * ri;
-      const T ek = expneg_t<T>(nk, kappa, R2 * ri);
-      const T *m = smom + b * NM;
-      // coefficients degree by degree, each contracted as soon as it is
-      // formed (single layer k < NC, double layer k < NK), so that only the
-      // two previous degrees stay live for the recurrence
-      T a[NK], ay[NK], by[NK];
-      a[0] = ri;
-      by[0] = ek;
-      ay[0] = ek * ri;
-      acc[0] += a[0] * m[0];
-      acc[1] += a[0] * m[NC];
-      acc[2] += ay[0] * m[0];
-      acc[3] += ay[0] * m[NC];
-#pragma unroll
-      for (int k = 1; k < NK; ++k) {
-        const int s = mi.deg[k];
-        T S1 = T(0), S2 = T(0), Y1 = T(0), Y2 = T(0), B1 = T(0), B2 = T(0);
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          if (mi.m1[k][d] >= 0) {
-            S1 += D[d] * a[mi.m1[k][d]];
-            Y1 += D[d] * ay[mi.m1[k][d]];
-            B1 += D[d] * by[mi.m1[k][d]];
-          }
-          if (mi.m2[k][d] >= 0) {
-            S2 += a[mi.m2[k][d]];
-            Y2 += ay[mi.m2[k][d]];
-            B2 += by[mi.m2[k][d]];
-          }
-        }
-        const T c1 = T(2 * s - 1) / T(s), c2 = T(s - 1) / T(s);
-        const T ks = kappa / T(s);
-        a[k] = (c1 * S1 - c2 * S2) * iR2;
-        by[k] = ks * (Y1 - Y2);
-        ay[k] = (c1 * Y1 - c2 * Y2 + ks * (B1 - B2)) * iR2;
-        if (k < NC) {
-          acc[0] += a[k] * m[k];
-          acc[2] += ay[k] * m[k];
-        }
-        acc[1] += a[k] * m[NC + k];
-        acc[3] += ay[k] * m[NC + k];
-      }
-    }
-    double sum[4] = {(double)acc[0], (double)acc[1], (double)acc[2], (double)acc[3]};
-    if (G > 1)
-      for (int c = 0; c < 4; ++c) {
-        const double v = sum[c];
-        for (int g = 1; g < G; ++g) sum[c] += __shfl(v, li + g * L, 64);
-      }
-    if (gi == 0 && t < t1) {
-      part[(size_t)slot * 2 * N + t] = sum[1] - sum[0];
-      part[((size_t)slot * 2 + 1) * N + t] = eps_ratio * sum[2] - sum[3];
-    }
-  }
+  // TPT up to 3 in FP32 and 2 in FP64 (on 144500 panels at P 5, bounds of 1, 2
+  // and 3: 155, 159, 149 us and 333, 326, 375 us; three FP64 targets spill)
+  constexpr int kMax = sizeof(T) == 4 ? 3 : 2;
+  const int nt = t1 - t0, passes = (nt + 64 * kMax - 1) / (64 * kMax);
+  const int tpt = (nt + 64 * passes - 1) / (64 * passes);
+#define PBMP_MB(K)                                                                             \
+  m2p_body<T, P, K>(t0, t1, lb, le, boxes, center, words, tgt, N, kappa, nk, slot, part, sh,   \
+                    scen, sbox)
+  if (tpt <= 1) PBMP_MB(1);
+  else if (tpt == 2) PBMP_MB(2);
+  else PBMP_MB(kMax);
+#undef PBMP_MB
 }
 
 // y = A x from the far-field slots and the near/self corrections.  Four
@@ -651,63 +664,63 @@ __global__ __launch_bounds__(kFinBlock) void k_finish_slots(
 }
 
 template <class T, int P>
-void launch_m2p_p(Tree &t, hipStream_t s, const T *mom, const T *tgt, int N, T kappa,
-                  T nk, double eps_ratio, double *part) {
+void launch_m2p_p(Tree &t, hipStream_t s, T *words, const T *tgt, int N, T kappa, T nk,
+                  double eps_ratio, double *part) {
+  hipLaunchKernelGGL((k_harmonics<T, P>), dim3(t.nbox), dim3(64), 0, s, t.d_mom64.p,
+                     t.d_hoff.p, t.d_hk.p, t.d_hc.p, t.d_hpos.p, eps_ratio, words);
   const int nb = ((t.n_m2p_tasks + 7) / 8) * 8;
   hipLaunchKernelGGL((k_m2p_tasks<T, P>), dim3(nb), dim3(64), 0, s, t.n_m2p_tasks,
-                     t.d_m2p_task.p, t.d_m2p_slot.p, t.d_m2p_box.p, t.d_center.p, mom,
-                     tgt, N, kappa, nk, eps_ratio, part);
-}
-
-template <class T>
-void launch_m2p(Tree &t, hipStream_t s, const T *mom, const T *tgt, int N, T kappa, T nk,
-                double eps_ratio, double *part) {
-  switch (t.prm.order) {
-    case 1: launch_m2p_p<T, 1>(t, s, mom, tgt, N, kappa, nk, eps_ratio, part); break;
-    case 2: launch_m2p_p<T, 2>(t, s, mom, tgt, N, kappa, nk, eps_ratio, part); break;
-    case 3: launch_m2p_p<T, 3>(t, s, mom, tgt, N, kappa, nk, eps_ratio, part); break;
-    case 4: launch_m2p_p<T, 4>(t, s, mom, tgt, N, kappa, nk, eps_ratio, part); break;
-    case 5: launch_m2p_p<T, 5>(t, s, mom, tgt, N, kappa, nk, eps_ratio, part); break;
-    case 6: launch_m2p_p<T, 6>(t, s, mom, tgt, N, kappa, nk, eps_ratio, part); break;
-    default: throw Error(PBMP_EARG, "treecode order must be 1..6");
-  }
+                     t.d_m2p_task.p, t.d_m2p_slot.p, t.d_m2p_box.p, t.d_center.p, words,
+                     tgt, N, kappa, nk, part);
 }
 
 template <int P>
-void launch_moments_p(Tree &t, hipStream_t s, int nf, const double *src64, float *mom32) {
+void launch_moments_p(Tree &t, hipStream_t s, int nf, const double *src64) {
   constexpr int NM = Orders<P>::NM;
   if (t.n_mom_tasks == 0) return;
   const int direct = t.n_mom_tasks == t.nleaf;  // no leaf split into slices
   hipLaunchKernelGGL(k_p2m_tasks<P>, dim3(t.n_mom_tasks), dim3(kP2MThreads), 0, s, nf,
-                     t.d_mom_task.p, t.d_center.p, src64, t.d_mom_part.p, direct, t.d_mom64.p,
-                     mom32);
+                     t.d_mom_task.p, t.d_center.p, src64, t.d_mom_part.p, direct, t.d_mom64.p);
   const int n = t.nbox * NM;
   if (!direct)
     hipLaunchKernelGGL(k_mom_reduce, dim3((n + 255) / 256), dim3(256), 0, s, t.nbox, NM,
-                       t.d_mom_first.p, t.d_mom_count.p, t.d_mom_part.p, t.d_mom64.p, mom32, 1);
+                       t.d_mom_first.p, t.d_mom_count.p, t.d_mom_part.p, t.d_mom64.p, 1);
   if (t.n_shift_tasks > 0) {
     hipLaunchKernelGGL(k_shift_tasks<P>, dim3(t.n_shift_tasks), dim3(kShiftThreads), 0, s,
                        t.d_shift_task.p, t.d_leaves.p, t.d_center.p, t.d_monos.p,
-                       t.d_shift_toff.p, t.d_shift_tjq.p, t.d_shift_tc.p, t.d_mom64.p, mom32,
+                       t.d_shift_toff.p, t.d_shift_tjq.p, t.d_shift_tc.p, t.d_mom64.p,
                        t.d_shift_count.p, t.d_shift_part.p);
     if (t.shift_multi)
       hipLaunchKernelGGL(k_mom_reduce, dim3((n + 255) / 256), dim3(256), 0, s, t.nbox, NM,
                          t.d_shift_first.p, t.d_shift_count.p, t.d_shift_part.p, t.d_mom64.p,
-                         mom32, 2);
+                         2);
   }
 }
 
-// moments in FP64, and their FP32 copy when mom32 is not null
-void launch_moments(Tree &t, hipStream_t s, int nf, const double *src64, float *mom32) {
-  switch (t.prm.order) {
-    case 1: launch_moments_p<1>(t, s, nf, src64, mom32); break;
-    case 2: launch_moments_p<2>(t, s, nf, src64, mom32); break;
-    case 3: launch_moments_p<3>(t, s, nf, src64, mom32); break;
-    case 4: launch_moments_p<4>(t, s, nf, src64, mom32); break;
-    case 5: launch_moments_p<5>(t, s, nf, src64, mom32); break;
-    case 6: launch_moments_p<6>(t, s, nf, src64, mom32); break;
-    default: throw Error(PBMP_EARG, "treecode order must be 1..6");
+#define PBMP_BY_ORDER(CALL)                                            \
+  switch (t.prm.order) {                                               \
+    case 1: CALL(1); break;                                            \
+    case 2: CALL(2); break;                                            \
+    case 3: CALL(3); break;                                            \
+    case 4: CALL(4); break;                                            \
+    case 5: CALL(5); break;                                            \
+    case 6: CALL(6); break;                                            \
+    default: throw Error(PBMP_EARG, "treecode order must be 1..6");    \
   }
+
+template <class T>
+void launch_m2p(Tree &t, hipStream_t s, T *words, const T *tgt, int N, T kappa, T nk,
+                double eps_ratio, double *part) {
+#define PBMP_CALL(P) launch_m2p_p<T, P>(t, s, words, tgt, N, kappa, nk, eps_ratio, part)
+  PBMP_BY_ORDER(PBMP_CALL)
+#undef PBMP_CALL
+}
+
+// Cartesian moments of every leaf and accepted box, FP64
+void launch_moments(Tree &t, hipStream_t s, int nf, const double *src64) {
+#define PBMP_CALL(P) launch_moments_p<P>(t, s, nf, src64)
+  PBMP_BY_ORDER(PBMP_CALL)
+#undef PBMP_CALL
 }
 
 
@@ -832,100 +845,93 @@ __global__ __launch_bounds__(64) void k_p2pT_tasks(int ntask, const int *__restr
 }
 
 // M2P^T: per task (box B, target sub-ranges) the partial local coefficients
-// of one kernel family (YUK: Yukawa with z2, else Laplace with z1)
-template <class T, int P, bool YUK>
+// in harmonic form (FAM 0 Laplace with z1, 1 Yukawa with z2, 2 both at once:
+// the FP64 words of both do not leave registers for the rest).
+template <class T, int P, int FAM>
 __global__ __launch_bounds__(64) void k_m2pT_tasks(int ntask, const int *__restrict__ tasks,
                                                    const int *__restrict__ subs,
                                                    const double *__restrict__ center,
                                                    const T *__restrict__ tgt,
                                                    const double *__restrict__ z, int N,
                                                    T kappa, T nk, double *__restrict__ Lpart) {
-  // local coefficients to degree P + 1 (the double layer's transpose
-  // reaches them; the single layer's uses those of degree <= P)
-  constexpr Multi<P + 1> mi{};
-  constexpr int NC = Orders<P>::NK;
+  constexpr int NS = Orders<P>::NS;
+  constexpr int NA = FAM == 2 ? NS : (NS / 2 + 3) / 4 * 4;
   const int task = xcd_task(ntask);
   if (task < 0) return;
   const int B = tasks[4 * task], lb = tasks[4 * task + 1], le = tasks[4 * task + 2];
-  const T cx = (T)center[3 * B], cy = (T)center[3 * B + 1], cz = (T)center[3 * B + 2];
-  T acc[NC];
+  const T c[3] = {(T)center[3 * B], (T)center[3 * B + 1], (T)center[3 * B + 2]};
+  T acc[NA];
 #pragma unroll
-  for (int k = 0; k < NC; ++k) acc[k] = T(0);
+  for (int k = 0; k < NA; ++k) acc[k] = T(0);
   for (int l = lb; l < le; ++l) {
     const int a0 = subs[2 * l], a1 = subs[2 * l + 1];
     for (int t = a0 + (int)threadIdx.x; t < a1; t += 64) {
-      const T D[3] = {tgt[t] - cx, tgt[N + t] - cy, tgt[2 * N + t] - cz};
+      const T D[3] = {tgt[t] - c[0], tgt[N + t] - c[1], tgt[2 * N + t] - c[2]};
       const T R2 = D[0] * D[0] + D[1] * D[1] + D[2] * D[2];
       const T ri = rsqrt_t<T>(R2);
-      const T iR2 = ri * ri;
-      if (!YUK) {
-        const T w = (T)z[t];
-        T a[NC];
-        a[0] = ri;
-#pragma unroll
-        for (int k = 1; k < NC; ++k) {
-          const int s = mi.deg[k];
-          T S1 = T(0), S2 = T(0);
-#pragma unroll
-          for (int d = 0; d < 3; ++d) {
-            if (mi.m1[k][d] >= 0) S1 += D[d] * a[mi.m1[k][d]];
-            if (mi.m2[k][d] >= 0) S2 += a[mi.m2[k][d]];
-          }
-          a[k] = (T(2 * s - 1) / T(s) * S1 - T(s - 1) / T(s) * S2) * iR2;
-        }
-#pragma unroll
-        for (int k = 0; k < NC; ++k) acc[k] += w * a[k];
-      } else {
-        const T w = (T)z[N + t];
-        const T ek = expneg_t<T>(nk, kappa, R2 * ri);
-        T ay[NC], by[NC];
-        by[0] = ek;
-        ay[0] = ek * ri;
-#pragma unroll
-        for (int k = 1; k < NC; ++k) {
-          const int s = mi.deg[k];
-          T Y1 = T(0), Y2 = T(0), B1 = T(0), B2 = T(0);
-#pragma unroll
-          for (int d = 0; d < 3; ++d) {
-            if (mi.m1[k][d] >= 0) {
-              Y1 += D[d] * ay[mi.m1[k][d]];
-              B1 += D[d] * by[mi.m1[k][d]];
-            }
-            if (mi.m2[k][d] >= 0) {
-              Y2 += ay[mi.m2[k][d]];
-              B2 += by[mi.m2[k][d]];
-            }
-          }
-          const T ks = kappa / T(s);
-          by[k] = ks * (Y1 - Y2);
-          ay[k] = (T(2 * s - 1) / T(s) * Y1 - T(s - 1) / T(s) * Y2 + ks * (B1 - B2)) * iR2;
-        }
-#pragma unroll
-        for (int k = 0; k < NC; ++k) acc[k] += w * ay[k];
-      }
+      const T ek = FAM == 0 ? T(0) : expneg_t<T>(nk, kappa, R2 * ri);
+      harmonic_m2p_T<T, P + 1, FAM>(D, ri, ek, kappa, (T)z[t], (T)z[N + t], acc);
     }
   }
-  // wave sums in FP64, lane 0 writes
-  double *out = Lpart + (size_t)task * 2 * NC + (YUK ? NC : 0);
-#pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    double v = (double)acc[k];
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if (threadIdx.x == 0) out[k] = v;
+  double *out = Lpart + (size_t)task * NS;
+  wave_sums(acc, [&](int k, double v) {
+    const int pos = FAM == 2 ? k : 2 * k + FAM;
+    if (pos < NS) out[pos] = v;
+  });
+}
+
+// L_B, Cartesian [Laplace | Yukawa], from the partials of B's tasks (fixed
+// order, through the transposed map of k_harmonics); zero without tasks
+template <int P>
+__global__ __launch_bounds__(128) void k_l_reduce(const int *__restrict__ count,
+                                                  const int *__restrict__ off,
+                                                  const double *__restrict__ Lpart,
+                                                  const int *__restrict__ koff,
+                                                  const int *__restrict__ kpos,
+                                                  const double *__restrict__ kc,
+                                                  double *__restrict__ Lb) {
+  constexpr int NK = Orders<P>::NK, NS = Orders<P>::NS;
+  __shared__ double h[NS];
+  const int B = blockIdx.x, t0 = off[B], nt = count[2 * B + 1];
+  for (int e = threadIdx.x; e < NS; e += 128) {
+    double v = 0.0;
+    for (int t = t0; t < t0 + nt; ++t) v += Lpart[(size_t)t * NS + e];
+    h[e] = v;
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < NK; k += 128) {
+    double a = 0.0, b = 0.0;
+    for (int e = koff[k]; e < koff[k + 1]; ++e) {
+      a += kc[2 * e] * h[kpos[e]];
+      b += kc[2 * e + 1] * h[kpos[e] + 1];
+    }
+    Lb[(size_t)B * 2 * NK + k] = a;
+    Lb[(size_t)B * 2 * NK + NK + k] = b;
   }
 }
 
-// L_B = sum of the partials of B's tasks (fixed order); zero without tasks
-__global__ void k_l_reduce(int nbox, int ncoef2, const int *__restrict__ count,
-                           const int *__restrict__ off, const double *__restrict__ Lpart,
-                           double *__restrict__ Lb) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= nbox * ncoef2) return;
-  const int B = e / ncoef2, k = e % ncoef2;
-  double v = 0.0;
-  const int t0 = off[B], nt = count[2 * B + 1];
-  for (int t = t0; t < t0 + nt; ++t) v += Lpart[(size_t)t * ncoef2 + k];
-  Lb[e] = v;
+// local coefficients of every box for the weights z, in T
+template <class T, int P>
+void launch_locals(Tree &t, hipStream_t s, const T *tgt, const double *z, int N, T kappa, T nk) {
+  constexpr int NK = Orders<P>::NK, NS = Orders<P>::NS;
+  t.d_Lpart.reserve((size_t)std::max(1, t.n_m2pT_tasks) * NS);
+  t.d_L.reserve((size_t)t.nbox * 2 * NK);
+  if (t.n_m2pT_tasks > 0) {
+    const dim3 grid(((t.n_m2pT_tasks + 7) / 8) * 8);
+#define PBMP_ML(FAM)                                                                         \
+  hipLaunchKernelGGL((k_m2pT_tasks<T, P, FAM>), grid, dim3(64), 0, s, t.n_m2pT_tasks,        \
+                     t.d_m2pT_task.p, t.d_m2pT_sub.p, t.d_center.p, tgt, z, N, kappa, nk, \
+                     t.d_Lpart.p)
+    if constexpr (sizeof(T) == 4) {
+      PBMP_ML(2);
+    } else {
+      PBMP_ML(0);
+      PBMP_ML(1);
+    }
+#undef PBMP_ML
+  }
+  hipLaunchKernelGGL(k_l_reduce<P>, dim3(t.nbox), dim3(128), 0, s, t.d_m2pT_count.p,
+                     t.d_m2pT_off.p, t.d_Lpart.p, t.d_koff.p, t.d_kpos.p, t.d_kc.p, t.d_L.p);
 }
 
 // L2P at the leaves: every node takes the local expansions of all boxes
@@ -1042,21 +1048,8 @@ void tree_T_far(Tree &t, hipStream_t s, int nf, int N, const double *geo,
   else if (floor_r2) PBMP_TPT(1, true);
   else PBMP_TPT(1, false);
 #undef PBMP_TPT
-  // M2P^T, per-box sums, L2L down the levels, L2P at the leaves
-  t.d_Lpart.reserve((size_t)std::max(1, t.n_m2pT_tasks) * 2 * NK);
-  t.d_L.reserve((size_t)t.nbox * 2 * NK);
-  if (t.n_m2pT_tasks > 0) {
-    const int nbm = ((t.n_m2pT_tasks + 7) / 8) * 8;
-    hipLaunchKernelGGL((k_m2pT_tasks<T, P, false>), dim3(nbm), dim3(64), 0, s,
-                       t.n_m2pT_tasks, t.d_m2pT_task.p, t.d_m2pT_sub.p, t.d_center.p, tgt, z,
-                       N, kappa, nk, t.d_Lpart.p);
-    hipLaunchKernelGGL((k_m2pT_tasks<T, P, true>), dim3(nbm), dim3(64), 0, s,
-                       t.n_m2pT_tasks, t.d_m2pT_task.p, t.d_m2pT_sub.p, t.d_center.p, tgt, z,
-                       N, kappa, nk, t.d_Lpart.p);
-  }
-  const int nl = t.nbox * 2 * NK;
-  hipLaunchKernelGGL(k_l_reduce, dim3((nl + 255) / 256), dim3(256), 0, s, t.nbox, 2 * NK,
-                     t.d_m2pT_count.p, t.d_m2pT_off.p, t.d_Lpart.p, t.d_L.p);
+  // M2P^T with per-box sums, L2P at the leaves
+  launch_locals<T, P>(t, s, tgt, z, N, kappa, nk);
   if (nf == 3)
     hipLaunchKernelGGL((k_l2p<P, 3>), dim3(t.nleaf), dim3(64), 0, s, t.d_leaves.p,
                        t.d_range.p, t.d_parent.p, t.d_m2pT_count.p, t.d_center.p, t.d_L.p,
@@ -1179,17 +1172,20 @@ __global__ __launch_bounds__(64) void k_m2p_grad_tasks(int ntask, const int *__r
   const int t0 = tasks[4 * task], t1 = tasks[4 * task + 1];
   const int lb = tasks[4 * task + 2], le = tasks[4 * task + 3];
   const int slot = slots[task];
-  const int nb = le - lb;
-  if (threadIdx.x < nb) sbox[threadIdx.x] = boxes[lb + threadIdx.x];
-  __syncthreads();
-  for (int e = threadIdx.x; e < nb * NM; e += 64) smom[e] = mom[(size_t)sbox[e / NM] * NM + e % NM];
-  for (int e = threadIdx.x; e < nb * 3; e += 64) scen[e] = center[3 * sbox[e / 3] + e % 3];
-  __syncthreads();
   for (int tb = t0; tb < t1; tb += 64) {
     const int t = tb + (int)threadIdx.x, tl = min(t, t1 - 1);
     const double x[3] = {geo[tl], geo[N + tl], geo[2 * N + tl]};
     const double l1 = lam[tl], l2 = lam[N + tl];
     double g[3] = {0.0, 0.0, 0.0};
+    for (int cb = lb; cb < le; cb += kM2PChunkBoxes) {
+    const int nb = min(kM2PChunkBoxes, le - cb);
+    __syncthreads();
+    if (threadIdx.x < nb) sbox[threadIdx.x] = boxes[cb + threadIdx.x];
+    __syncthreads();
+    for (int e = threadIdx.x; e < nb * NM; e += 64)
+      smom[e] = mom[(size_t)sbox[e / NM] * NM + e % NM];
+    for (int e = threadIdx.x; e < nb * 3; e += 64) scen[e] = center[3 * sbox[e / 3] + e % 3];
+    __syncthreads();
     for (int b = 0; b < nb; ++b) {
       const double D[3] = {x[0] - scen[3 * b], x[1] - scen[3 * b + 1], x[2] - scen[3 * b + 2]};
       const double R2 = D[0] * D[0] + D[1] * D[1] + D[2] * D[2];
@@ -1238,6 +1234,7 @@ __global__ __launch_bounds__(64) void k_m2p_grad_tasks(int ntask, const int *__r
         }
         g[d] += l1 * (kl - vl) + l2 * (eps_ratio * vy - ky);
       }
+    }
     }
     if (t < t1)
       for (int d = 0; d < 3; ++d) part[((size_t)slot * 4 + d) * N + t] = g[d];
@@ -1467,20 +1464,7 @@ void tree_mesh_adjoint_far_p(Tree &t, hipStream_t s, int nf, int N, const double
     hipLaunchKernelGGL(k_p2pT_grad_tasks<1>, dim3(nbt), dim3(64), 0, s, t.n_p2pT_tasks,
                        t.d_p2pT_task.p, t.d_range.p, t.d_p2pT_sub.p, src64, geo, lam, N,
                        kappa, eps_ratio, partT);
-  t.d_Lpart.reserve((size_t)std::max(1, t.n_m2pT_tasks) * 2 * NK);
-  t.d_L.reserve((size_t)t.nbox * 2 * NK);
-  if (t.n_m2pT_tasks > 0) {
-    const int nbm = ((t.n_m2pT_tasks + 7) / 8) * 8;
-    hipLaunchKernelGGL((k_m2pT_tasks<double, P, false>), dim3(nbm), dim3(64), 0, s,
-                       t.n_m2pT_tasks, t.d_m2pT_task.p, t.d_m2pT_sub.p, t.d_center.p, geo, lam,
-                       N, kappa, 0.0, t.d_Lpart.p);
-    hipLaunchKernelGGL((k_m2pT_tasks<double, P, true>), dim3(nbm), dim3(64), 0, s,
-                       t.n_m2pT_tasks, t.d_m2pT_task.p, t.d_m2pT_sub.p, t.d_center.p, geo, lam,
-                       N, kappa, 0.0, t.d_Lpart.p);
-  }
-  const int nl = t.nbox * 2 * NK;
-  hipLaunchKernelGGL(k_l_reduce, dim3((nl + 255) / 256), dim3(256), 0, s, t.nbox, 2 * NK,
-                     t.d_m2pT_count.p, t.d_m2pT_off.p, t.d_Lpart.p, t.d_L.p);
+  launch_locals<double, P>(t, s, geo, lam, N, kappa, 0.0);
   if (nf == 3)
     hipLaunchKernelGGL((k_l2p_grad<P, 3>), dim3(t.nleaf), dim3(64), 0, s, t.d_leaves.p,
                        t.d_range.p, t.d_parent.p, t.d_m2pT_count.p, t.d_center.p, t.d_L.p,
@@ -1531,11 +1515,181 @@ void tree_upload_exponents(Tree &t, hipStream_t s) {
   t.d_shift_tc.upload(c.data(), c.size(), s);
 }
 
+// Tables of the harmonic form of order P (harmonic.hpp) for degrees up to
+// L = P + 1: per harmonic its terms over the Cartesian indices, and per
+// Cartesian index its terms over the harmonics' word positions (the
+// transposed map of the local coefficients), each with the Laplace and the
+// Yukawa constant.  The split of the degree-n monomials into |xi|^{2j} times
+// harmonics is the inverse of the matrix whose columns are those products'
+// monomial coefficients (at most 36 x 36, extended precision).
+template <int L> static void harmonic_positions(std::vector<int> &pos) {
+  for (int l = 0; l <= L; ++l)
+    for (int m = -l; m <= l; ++m)
+      pos.push_back(m == 0  ? Harm<L>::pole(l)
+                    : m > 0 ? Harm<L>::group(l, m)
+                            : Harm<L>::group(l, -m) + 2);
+}
+
+void tree_upload_harmonics(Tree &t, double kappa, hipStream_t s) {
+  using ld = long double;
+  const int L = t.prm.order + 1, D = L + 1;
+  auto at = [&](int i, int j, int k) { return (i * D + j) * D + k; };
+  using Poly = std::vector<ld>;
+  auto zero = [&] { return Poly((size_t)D * D * D, 0.0L); };
+  auto mul = [&](const Poly &a, int i, int j, int k, ld c, Poly &out) {  // out += c x^i y^j z^k a
+    for (int x = 0; x + i < D; ++x)
+      for (int y = 0; y + j < D; ++y)
+        for (int z = 0; z + k < D; ++z)
+          if (a[at(x, y, z)] != 0.0L) out[at(x + i, y + j, z + k)] += c * a[at(x, y, z)];
+  };
+  auto r2 = [&](const Poly &a, ld c, Poly &out) {
+    mul(a, 2, 0, 0, c, out);
+    mul(a, 0, 2, 0, c, out);
+    mul(a, 0, 0, 2, c, out);
+  };
+  // harm[l][m + l]: the harmonic polynomials, m < 0 the sines
+  std::vector<std::vector<Poly>> harm(L + 1);
+  for (int l = 0; l <= L; ++l) harm[l].resize(2 * l + 1);
+  Poly c = zero(), sn = zero();
+  c[at(0, 0, 0)] = 1.0L;
+  for (int m = 0; m <= L; ++m) {
+    if (m > 0) {
+      Poly nc = zero(), ns = zero();
+      mul(c, 1, 0, 0, 1.0L, nc);
+      mul(sn, 0, 1, 0, -1.0L, nc);
+      mul(sn, 1, 0, 0, 1.0L, ns);
+      mul(c, 0, 1, 0, 1.0L, ns);
+      c = nc;
+      sn = ns;
+    }
+    for (int sg = 0; sg < (m ? 2 : 1); ++sg) {
+      Poly p0 = zero(), p1 = sg ? sn : c;
+      harm[m][sg ? 0 : 2 * m] = p1;
+      for (int l = m; l < L; ++l) {
+        Poly p2 = zero();
+        mul(p1, 0, 0, 1, 1.0L, p2);
+        r2(p0, -(ld)(l * l - m * m) / (ld)(4 * l * l - 1), p2);
+        harm[l + 1][l + 1 + (sg ? -m : m)] = p2;
+        p0 = p1;
+        p1 = p2;
+      }
+    }
+  }
+  std::vector<std::vector<int>> ex;  // Cartesian indices in storage order
+  std::vector<int> first(L + 2, 0);
+  for (int n = 0; n <= L; ++n) {
+    for (int i = n; i >= 0; --i)
+      for (int j = n - i; j >= 0; --j) ex.push_back({i, j, n - i - j});
+    first[n + 1] = (int)ex.size();
+  }
+  auto fact = [](int n) {
+    ld f = 1.0L;
+    for (int i = 2; i <= n; ++i) f *= i;
+    return f;
+  };
+  const int NH = (L + 1) * (L + 1), NK = (int)ex.size();
+  std::vector<std::vector<int>> hk(NH), kh(NK);
+  std::vector<std::vector<double>> hc(NH), kc(NK);
+  for (int n = 0; n <= L; ++n) {
+    const int n0 = first[n], dim = first[n + 1] - n0;
+    struct Col {
+      int l, m, j;
+    };
+    std::vector<Col> cols;
+    std::vector<ld> A((size_t)dim * 2 * dim, 0.0L);  // [products | identity]
+    for (int j = 0; 2 * j <= n; ++j) {
+      const int l = n - 2 * j;
+      for (int m = -l; m <= l; ++m) {
+        Poly p = harm[l][m + l];
+        for (int u = 0; u < j; ++u) {
+          Poly q = zero();
+          r2(p, 1.0L, q);
+          p = q;
+        }
+        for (int k = 0; k < dim; ++k) {
+          const auto &e = ex[n0 + k];
+          A[(size_t)k * 2 * dim + cols.size()] = p[at(e[0], e[1], e[2])];
+        }
+        cols.push_back({l, m, j});
+      }
+    }
+    for (int k = 0; k < dim; ++k) A[(size_t)k * 2 * dim + dim + k] = 1.0L;
+    for (int k = 0; k < dim; ++k) {  // Gauss-Jordan with row pivoting
+      int piv = k;
+      for (int r = k + 1; r < dim; ++r)
+        if (std::fabs(A[(size_t)r * 2 * dim + k]) > std::fabs(A[(size_t)piv * 2 * dim + k])) piv = r;
+      for (int q = 0; q < 2 * dim; ++q)
+        std::swap(A[(size_t)k * 2 * dim + q], A[(size_t)piv * 2 * dim + q]);
+      const ld inv = 1.0L / A[(size_t)k * 2 * dim + k];
+      for (int q = 0; q < 2 * dim; ++q) A[(size_t)k * 2 * dim + q] *= inv;
+      for (int r = 0; r < dim; ++r) {
+        const ld f = A[(size_t)r * 2 * dim + k];
+        if (r == k || f == 0.0L) continue;
+        for (int q = 0; q < 2 * dim; ++q)
+          A[(size_t)r * 2 * dim + q] -= f * A[(size_t)k * 2 * dim + q];
+      }
+    }
+    for (int q = 0; q < dim; ++q) {
+      const Col &cq = cols[q];
+      ld dfact = 1.0L;  // (2l - 1)!!
+      for (int u = 2 * cq.l - 1; u > 1; u -= 2) dfact *= u;
+      const ld kap = std::pow((ld)kappa, 2 * cq.j);
+      for (int k = 0; k < dim; ++k) {
+        const ld v = A[(size_t)q * 2 * dim + dim + k];
+        if (std::fabs(v) < 1e-12L) continue;  // the true ones are simple fractions
+        const auto &e = ex[n0 + k];
+        const ld w = v * dfact / (fact(e[0]) * fact(e[1]) * fact(e[2]));
+        const int h = cq.l * cq.l + cq.m + cq.l;
+        const double cl = cq.j == 0 ? (double)w : 0.0, cy = (double)(w * kap);
+        if (cl == 0.0 && cy == 0.0) continue;
+        hk[h].push_back(n0 + k);
+        hc[h].insert(hc[h].end(), {cl, cy});
+        kh[n0 + k].push_back(h);
+        kc[n0 + k].insert(kc[n0 + k].end(), {cl, cy});
+      }
+    }
+  }
+  std::vector<int> pos;
+  switch (L) {
+    case 2: harmonic_positions<2>(pos); break;
+    case 3: harmonic_positions<3>(pos); break;
+    case 4: harmonic_positions<4>(pos); break;
+    case 5: harmonic_positions<5>(pos); break;
+    case 6: harmonic_positions<6>(pos); break;
+    case 7: harmonic_positions<7>(pos); break;
+    default: throw Error(PBMP_EARG, "treecode order must be 1..6");
+  }
+  auto flat = [&](const std::vector<std::vector<int>> &ix,
+                  const std::vector<std::vector<double>> &co, bool to_pos, Dbuf<int> &off,
+                  Dbuf<int> &idx, Dbuf<double> &coef) {
+    std::vector<int> o(1, 0), f;
+    std::vector<double> v;
+    for (size_t a = 0; a < ix.size(); ++a) {
+      for (int b : ix[a]) f.push_back(to_pos ? pos[b] : b);
+      v.insert(v.end(), co[a].begin(), co[a].end());
+      o.push_back((int)f.size());
+    }
+    off.upload(o.data(), o.size(), s);
+    idx.upload(f.data(), f.size(), s);
+    coef.upload(v.data(), v.size(), s);
+    PBMP_HIP(hipStreamSynchronize(s));
+  };
+  flat(hk, hc, false, t.d_hoff, t.d_hk, t.d_hc);
+  flat(kh, kc, true, t.d_koff, t.d_kpos, t.d_kc);
+  t.d_hpos.upload(pos.data(), pos.size(), s);
+  const size_t words = 4 * (size_t)(L * (L + 1) / 2 + (L + 2) / 2);
+  t.d_harm64.alloc((size_t)t.nbox * words);
+  t.d_harm32.alloc((size_t)t.nbox * words);
+  PBMP_HIP(hipMemsetAsync(t.d_harm64.p, 0, sizeof(double) * t.nbox * words, s));
+  PBMP_HIP(hipMemsetAsync(t.d_harm32.p, 0, sizeof(float) * t.nbox * words, s));
+  PBMP_HIP(hipStreamSynchronize(s));
+}
+
 void tree_apply(Tree &t, hipStream_t s, bool fp64, int nf, int N, const double *geo,
                 const double *src64, const float *src32, const float *tgt32,
                 double kappa, double eps_ratio, double *part, KernelClock &clk, bool floor_r2) {
   hipEvent_t e0 = clk.on ? clk.begin(s) : nullptr;
-  launch_moments(t, s, nf, src64, fp64 ? nullptr : t.d_mom32.p);
+  launch_moments(t, s, nf, src64);
   PBMP_HIP(hipGetLastError());
   if (clk.on) clk.end(s, e0, KernelClock::P2M, 0.0);
 
@@ -1563,9 +1717,9 @@ void tree_apply(Tree &t, hipStream_t s, bool fp64, int nf, int N, const double *
   if (t.n_m2p_tasks > 0 && t.n_m2p_entries > 0) {
     e0 = clk.on ? clk.begin(s) : nullptr;
     if (fp64)
-      launch_m2p<double>(t, s, t.d_mom64.p, geo, N, kappa, 0.0, eps_ratio, part);
+      launch_m2p<double>(t, s, t.d_harm64.p, geo, N, kappa, 0.0, eps_ratio, part);
     else
-      launch_m2p<float>(t, s, t.d_mom32.p, tgt32, N, (float)kappa, nk32, eps_ratio, part);
+      launch_m2p<float>(t, s, t.d_harm32.p, tgt32, N, (float)kappa, nk32, eps_ratio, part);
     PBMP_HIP(hipGetLastError());
     if (clk.on) clk.end(s, e0, KernelClock::M2P, t.m2p_pairs);
   }

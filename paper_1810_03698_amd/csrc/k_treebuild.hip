@@ -286,7 +286,7 @@ __global__ void k_lists(int nleaf, const int *__restrict__ leaves, Boxes b,
   // equal work per task: chunk and mchunk arrive as target-source pairs per
   // task and become sources per task for this leaf's size
   chunk = task_chunk(chunk, t1 - t0, kMinChunk, kMaxChunk);
-  mchunk = task_chunk(mchunk, t1 - t0, 1, kM2PChunkBoxes);
+  mchunk = task_chunk(mchunk, t1 - t0, 1, kM2PTaskBoxes);
   int nm = 0, np = 0, nsub = 0, ntask = 0, nemit = 0, cnt = 0, panels = 0;
   int om = 0, op = 0, os = 0, ot = 0, firstsub = 0;
   if (FILL) {
@@ -681,7 +681,7 @@ void Tree::build_device(int N, int nf, const uint64_t *key, const double *geo,
   lo.count = cnt.p;
   hipLaunchKernelGGL(k_lists<false>, grid_for(nleaf, 64), dim3(64), 0, s, nleaf, d_leaves.p,
                      view(), d_center.p, d_radius.p, prm.theta, kP2PTaskWork,
-                     kM2PTaskWork, lo);
+                     m2p_task_work(N), lo);
   PBMP_HIP(hipGetLastError());
   int tot[5];
   for (int c = 0; c < 5; ++c) {
@@ -719,7 +719,7 @@ void Tree::build_device(int N, int nf, const uint64_t *key, const double *geo,
   lo.slots_of_box = slots_of_box.p;
   hipLaunchKernelGGL(k_lists<true>, grid_for(nleaf, 64), dim3(64), 0, s, nleaf, d_leaves.p,
                      view(), d_center.p, d_radius.p, prm.theta, kP2PTaskWork,
-                     kM2PTaskWork, lo);
+                     m2p_task_work(N), lo);
   d_tslots.alloc(N);
   hipLaunchKernelGGL(k_target_slots, grid_for(N), dim3(256), 0, s, N, owner.p, slots_of_box.p,
                      d_tslots.p);
@@ -788,9 +788,9 @@ void Tree::build_device(int N, int nf, const uint64_t *key, const double *geo,
     PBMP_HIP(hipGetLastError());
   }
   d_mom64.alloc((size_t)nbox * nmom);
-  d_mom32.alloc((size_t)nbox * nmom);
   PBMP_HIP(hipMemsetAsync(d_mom64.p, 0, sizeof(double) * nbox * nmom, s));
   tree_upload_exponents(*this, s);
+  tree_upload_harmonics(*this, prm.kappa, s);
   PBMP_HIP(hipStreamSynchronize(s));
 }
 

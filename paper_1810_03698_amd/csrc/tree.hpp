@@ -18,9 +18,6 @@ namespace pbmp {
 #ifndef PBMP_P2P_GROUPS
 #define PBMP_P2P_GROUPS 1
 #endif
-#ifndef PBMP_M2P_GROUPS
-#define PBMP_M2P_GROUPS 0
-#endif
 
 struct LaneSplit {
   int G, L, tpt;
@@ -47,22 +44,25 @@ __host__ __device__ inline LaneSplit lane_split(int nt) {
   return best;
 }
 
-// boxes per M2P task (one task's moments are staged in LDS)
-#ifndef PBMP_M2P_CHUNK
-#define PBMP_M2P_CHUNK 16
-#endif
-constexpr int kM2PChunkBoxes = PBMP_M2P_CHUNK;
+// boxes of an M2P task at most, and those whose words pass through LDS (and
+// whose FP32 sums run) together, at most kM2PStageBytes of them
+constexpr int kM2PTaskBoxes = 64;
+constexpr int kM2PChunkBoxes = 16;
+constexpr int kM2PStageBytes = 8192;
 // work per task, in target-source pairs: a leaf of nt targets gets tasks of
-// about kP2PTaskWork / nt source panels (P2P) and kM2PTaskWork / nt boxes
-// (M2P, at most kM2PChunkBoxes), so that tasks take about the same time
+// about kP2PTaskWork / nt source panels (P2P) and m2p_task_work(N) / nt boxes
+// (M2P, at most kM2PTaskBoxes), so that tasks take about the same time
 #ifndef PBMP_P2P_WORK
 #define PBMP_P2P_WORK 12288
 #endif
-#ifndef PBMP_M2P_WORK
-#define PBMP_M2P_WORK 1024
-#endif
 constexpr int kP2PTaskWork = PBMP_P2P_WORK;
-constexpr int kM2PTaskWork = PBMP_M2P_WORK;
+// A surface of N panels has 100-200 N M2P pairs: N / 48 per task gives the
+// largest ones some 8000 tasks (eight waves per SIMD, short tail) without more
+// partial-sum slots than that needs (144500 panels: N / 24, 48, 96 took 163,
+// 149, 153 us); below 1024 pairs the staging and the finish kernel's slots
+// cost more than the shorter tasks gain (28880 panels: 59, 56 and 69 us for
+// both kernels at 512, 1024 and 256)
+inline int m2p_task_work(int N) { return N / 48 < 1024 ? 1024 : N / 48 > 4096 ? 4096 : N / 48; }
 // panels per moment task
 // Panels per moment task: one wave per task, so a slice bounds the nodes a
 // lane walks; higher orders carry a longer wave reduction per task and
@@ -78,7 +78,7 @@ constexpr int kShiftLeaves = 16;
 constexpr int kM2PTChunkTargets = 512;
 
 struct TreeParams {
-  double theta = 0.5;
+  double theta = 0.5, kappa = 0.0;
   int order = 4;
   int leaf = 300;
 };
@@ -121,7 +121,7 @@ class Tree {
   Dbuf<int> d_m2pT_sub, d_m2pT_task, d_m2pT_count, d_m2pT_off;  // off: first task of a box
   Dbuf<int> d_tslotsT;    // [N] transposed slots of the panel's leaf (tasks + 1)
   int n_p2pT_tasks = 0, n_m2pT_tasks = 0, max_slots_T = 1;
-  Dbuf<double> d_Lpart, d_L;  // local coefficients: per M2P^T task, per box [2][ncoefK]
+  Dbuf<double> d_Lpart, d_L;  // local coefficients: per M2P^T task (harmonic), per box [2][ncoefK]
   // moment tasks: the panels of every leaf in slices of at most
   // mom_chunk_panels(P); task = (box, s0, s1); a box's slices are consecutive
   int n_mom_tasks = 0;
@@ -136,7 +136,12 @@ class Tree {
   Dbuf<int> d_shift_toff, d_shift_tjq;  // per coefficient k: terms [toff[k], toff[k+1]), (j, k-j)
   Dbuf<double> d_shift_tc;              // C(k, j) of each term
   Dbuf<double> d_mom64;   // [nbox][nmom]
-  Dbuf<float> d_mom32;    // [nbox][nmom]
+  // harmonic form (harmonic.hpp): words per box, and the tables of the maps
+  // from the Cartesian moments and (transposed) to the Cartesian locals
+  Dbuf<double> d_harm64;
+  Dbuf<float> d_harm32;
+  Dbuf<int> d_hoff, d_hk, d_hpos, d_koff, d_kpos;
+  Dbuf<double> d_hc, d_kc;  // (Laplace, Yukawa) constant per term
   Dbuf<int> d_monos;      // [3*ncoefK] exponents up to degree P + 1
 
   // Build from the Morton keys of the panels in internal (sorted) order,
@@ -156,5 +161,7 @@ void morton_order_device(hipStream_t s, int N, const double *verts, const int *t
 
 // upload the multi-index exponent table of the chosen order (d_monos)
 void tree_upload_exponents(Tree &t, hipStream_t s);
+// tables and buffers of the harmonic form for the chosen order and kappa
+void tree_upload_harmonics(Tree &t, double kappa, hipStream_t s);
 
 }  // namespace pbmp
