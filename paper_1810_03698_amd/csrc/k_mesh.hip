@@ -69,6 +69,19 @@ __global__ void k_panel_geometry(int N, const double *__restrict__ verts,
   }
 }
 
+// far-rule value of one panel as the product forms it
+template <class T>
+__device__ inline void coarse_panel(int nf, const T *rec, T px, T py, T pz, const Screen<T> &sc,
+                                    double wA, double out[4]) {
+  T vl, kl, vy, ky, nR;
+  if (nf == 3) panel_sums<3, true>(rec, px, py, pz, sc, vl, kl, vy, ky, nR);
+  else panel_sums<1, true>(rec, px, py, pz, sc, vl, kl, vy, ky, nR);
+  out[0] = wA * (double)vl;
+  out[1] = wA * (double)(nR * kl);
+  out[2] = wA * (double)vy;
+  out[3] = wA * (double)(nR * ky);
+}
+
 __global__ void k_near_values(int fp64, int N, const int *__restrict__ rowptr,
                               const int *__restrict__ col,
                               const double *__restrict__ verts,
@@ -79,6 +92,10 @@ __global__ void k_near_values(int fp64, int N, const int *__restrict__ rowptr,
                               const float *__restrict__ tgt32, RuleArgs ru,
                               double kappa, double *__restrict__ val,
                               double *__restrict__ diag) {
+  __shared__ double etab[64];
+  const Screen<double> s64 = make_screen(kappa, etab);
+  const Screen<float> s32 = make_screen((float)kappa, nullptr);
+  __syncthreads();
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= N) return;
   const double x[3] = {geo[i], geo[N + i], geo[2 * N + i]};
@@ -100,18 +117,11 @@ __global__ void k_near_values(int fp64, int N, const int *__restrict__ rowptr,
     }
     // the far-rule value exactly as the far-field product evaluates it
     const double wA = A * kInv4Pi / ru.nf;
-    if (fp64) {
-      double t[4];
-      panel_terms<double>(src64 + 16 * (size_t)j, ru.nf, x[0], x[1], x[2], kappa,
-                          0.0, t);
-      for (int k = 0; k < 4; ++k) coarse[k] = wA * t[k];
-    } else {
-      float t[4];
-      panel_terms<float>(src32 + 16 * (size_t)j, ru.nf, tgt32[i], tgt32[N + i],
-                         tgt32[2 * N + i], (float)kappa,
-                         (float)(-kappa * 1.4426950408889634), t);
-      for (int k = 0; k < 4; ++k) coarse[k] = wA * (double)t[k];
-    }
+    if (fp64)
+      coarse_panel<double>(ru.nf, src64 + 16 * (size_t)j, x[0], x[1], x[2], s64, wA, coarse);
+    else
+      coarse_panel<float>(ru.nf, src32 + 16 * (size_t)j, tgt32[i], tgt32[N + i],
+                          tgt32[2 * N + i], s32, wA, coarse);
     for (int k = 0; k < 4; ++k) val[4 * (size_t)e + k] = fine[k] - coarse[k];
   }
 }

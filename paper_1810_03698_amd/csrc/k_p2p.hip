@@ -54,13 +54,15 @@ __global__ void k_pack_strengths(int N, int nf, double eps_ratio,
 template <class T, int NF, int TPT, bool FLOOR>
 __global__ __launch_bounds__(kBlock) void k_p2p(const T *__restrict__ src, int N,
                                                 const T *__restrict__ tgt, int Nt, int chunk,
-                                                T kappa, T nk, double *__restrict__ part) {
+                                                T kappa, double *__restrict__ part) {
   constexpr int kWaves = kBlock / 64;
   constexpr int kTileR = sizeof(T) == 4 ? kTile : kTile / 2;  // records per tile (8 KB)
   typedef T v2 __attribute__((ext_vector_type(16 / sizeof(T))));
   constexpr int PER = 16 * sizeof(T) / 16;  // 16-byte units per record
   __shared__ __align__(16) T sh[kTileR * 16];
   __shared__ double red[kWaves - 1][TPT][2][64];
+  __shared__ double etab[sizeof(T) == 8 ? 64 : 1];
+  const Screen<T> sc = make_screen(kappa, etab);
   const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
   const int j0 = blockIdx.y * chunk;
   const int j1 = min(N, j0 + chunk);
@@ -90,7 +92,7 @@ __global__ __launch_bounds__(kBlock) void k_p2p(const T *__restrict__ src, int N
       const T *r = sh + 16 * jj;
 #pragma unroll
       for (int k = 0; k < TPT; ++k)
-        panel_rows<NF, FLOOR>(r, px[k], py[k], pz[k], kappa, nk, a[k][0], a[k][1]);
+        panel_rows<NF, FLOOR>(r, px[k], py[k], pz[k], sc, a[k][0], a[k][1]);
     }
 #pragma unroll
     for (int k = 0; k < TPT; ++k)
@@ -152,12 +154,14 @@ __global__ __launch_bounds__(kBlock) void k_finish(
 template <class T, int NF, int TPT, bool FLOOR>
 __global__ __launch_bounds__(kBlock) void k_p2p_transpose(
     int N, const T *__restrict__ src, const T *__restrict__ tgt, const double *__restrict__ geo,
-    const double *__restrict__ z, int chunk, T kappa, T nk, double eps_ratio,
+    const double *__restrict__ z, int chunk, T kappa, double eps_ratio,
     double *__restrict__ part) {
   constexpr int kWaves = kBlock / 64;
   constexpr int kRec = 8;  // x y z z1 z2 eps z2
   __shared__ __align__(16) T sh[kTile * kRec];
   __shared__ double red[kWaves - 1][TPT][2][64];
+  __shared__ double etab[sizeof(T) == 8 ? 64 : 1];
+  const Screen<T> sc = make_screen(kappa, etab);
   const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
   T rec[TPT][12];
   int sj[TPT];
@@ -193,7 +197,7 @@ __global__ __launch_bounds__(kBlock) void k_p2p_transpose(
       const T *r = sh + kRec * e;
 #pragma unroll
       for (int k = 0; k < TPT; ++k)
-        panel_columns<NF, FLOOR>(rec[k], r[0], r[1], r[2], r[3], r[4], r[5], kappa, nk,
+        panel_columns<NF, FLOOR>(rec[k], r[0], r[1], r[2], r[3], r[4], r[5], sc,
                                  a[k][0], a[k][1]);
     }
 #pragma unroll
@@ -275,24 +279,25 @@ void launch_p2p_direct(hipStream_t s, bool fp64, int nf, int N, int Nt,
   const int chunk = (N + nchunk - 1) / nchunk;
   const int tpt = direct_tpt(fp64, Nt);
   const dim3 grid((Nt + 64 * tpt - 1) / (64 * tpt), nchunk);
-#define PBMP_P2P(TT, NFV, TPT, FL, SRC, TGT, KAP, NK)                                    \
+#define PBMP_P2P(TT, NFV, TPT, FL, SRC, TGT)                                             \
   hipLaunchKernelGGL((k_p2p<TT, NFV, TPT, FL>), grid, dim3(kBlock), 0, s, SRC, N, TGT, Nt, \
-                     chunk, KAP, NK, part)
+                     chunk, (TT)kappa, part)
+#define PBMP_P2P_RULE(CALL)                \
+  if (nf == 3 && floor_r2) CALL(3, true);  \
+  else if (nf == 3) CALL(3, false);        \
+  else if (floor_r2) CALL(1, true);        \
+  else CALL(1, false)
+#define PBMP_P2P64(NFV, FL) PBMP_P2P(double, NFV, 1, FL, src64, geo)
+#define PBMP_P2P32(NFV, FL)                                  \
+  if (tpt == 2) PBMP_P2P(float, NFV, 2, FL, src32, tgt32);   \
+  else PBMP_P2P(float, NFV, 1, FL, src32, tgt32)
   if (fp64) {
-    if (nf == 3) PBMP_P2P(double, 3, 1, true, src64, geo, kappa, 0.0);
-    else PBMP_P2P(double, 1, 1, true, src64, geo, kappa, 0.0);
+    PBMP_P2P_RULE(PBMP_P2P64);
   } else {
-    const float kf = (float)kappa;
-    const float nk = (float)(-kappa * 1.4426950408889634);
-#define PBMP_P2P32(NFV, FL)                                              \
-  if (tpt == 2) PBMP_P2P(float, NFV, 2, FL, src32, tgt32, kf, nk);       \
-  else PBMP_P2P(float, NFV, 1, FL, src32, tgt32, kf, nk)
-    if (nf == 3 && floor_r2) PBMP_P2P32(3, true);
-    else if (nf == 3) PBMP_P2P32(3, false);
-    else if (floor_r2) PBMP_P2P32(1, true);
-    else PBMP_P2P32(1, false);
-#undef PBMP_P2P32
+    PBMP_P2P_RULE(PBMP_P2P32);
   }
+#undef PBMP_P2P64
+#undef PBMP_P2P32
 #undef PBMP_P2P
   PBMP_HIP(hipGetLastError());
 }
@@ -315,25 +320,22 @@ void launch_transpose(hipStream_t s, bool fp64, int nf, int N,
   const int chunk = (N + nchunk - 1) / nchunk;
   const int tpt = direct_tpt(fp64, N);
   const dim3 grid((N + 64 * tpt - 1) / (64 * tpt), nchunk);
-#define PBMP_P2PT(TT, NFV, TPT, FL, SRC, TGT, KAP, NK)                                     \
+#define PBMP_P2PT(TT, NFV, TPT, FL, SRC, TGT)                                              \
   hipLaunchKernelGGL((k_p2p_transpose<TT, NFV, TPT, FL>), grid, dim3(kBlock), 0, s, N, SRC, \
-                     TGT, geo, z, chunk, KAP, NK, eps_ratio, part)
+                     TGT, geo, z, chunk, (TT)kappa, eps_ratio, part)
+#define PBMP_P2PT64(NFV, FL) PBMP_P2PT(double, NFV, 1, FL, src64, geo)
+#define PBMP_P2PT32(NFV, FL)                                  \
+  if (tpt == 2) PBMP_P2PT(float, NFV, 2, FL, src32, tgt32);   \
+  else PBMP_P2PT(float, NFV, 1, FL, src32, tgt32)
   if (fp64) {
-    if (nf == 3) PBMP_P2PT(double, 3, 1, true, src64, geo, kappa, 0.0);
-    else PBMP_P2PT(double, 1, 1, true, src64, geo, kappa, 0.0);
+    PBMP_P2P_RULE(PBMP_P2PT64);
   } else {
-    const float kf = (float)kappa;
-    const float nk = (float)(-kappa * 1.4426950408889634);
-#define PBMP_P2PT32(NFV, FL)                                              \
-  if (tpt == 2) PBMP_P2PT(float, NFV, 2, FL, src32, tgt32, kf, nk);       \
-  else PBMP_P2PT(float, NFV, 1, FL, src32, tgt32, kf, nk)
-    if (nf == 3 && floor_r2) PBMP_P2PT32(3, true);
-    else if (nf == 3) PBMP_P2PT32(3, false);
-    else if (floor_r2) PBMP_P2PT32(1, true);
-    else PBMP_P2PT32(1, false);
-#undef PBMP_P2PT32
+    PBMP_P2P_RULE(PBMP_P2PT32);
   }
+#undef PBMP_P2PT64
+#undef PBMP_P2PT32
 #undef PBMP_P2PT
+#undef PBMP_P2P_RULE
   PBMP_HIP(hipGetLastError());
   const int rows = kBlock / kFinLanes;
   hipLaunchKernelGGL(k_finish_transpose, dim3((N + rows - 1) / rows), dim3(kBlock), 0, s,

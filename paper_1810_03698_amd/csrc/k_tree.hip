@@ -371,7 +371,7 @@ __device__ __forceinline__ void stage_records(const T *__restrict__ src, T *sh, 
 template <class T, int NF, int TPT, bool FLOOR>
 __device__ void p2p_task_body(const T *__restrict__ src, const T *__restrict__ tgt,
                               int N, int t0, int t1, const int *__restrict__ ranges,
-                              int lb, int le, T kappa, T nk, int slot,
+                              int lb, int le, const Screen<T> &sc, int slot,
                               double *__restrict__ part, T *sh, int G, int L) {
   const int lane = (int)threadIdx.x;
   const int gi = lane / L, li = lane - gi * L;
@@ -404,7 +404,7 @@ __device__ void p2p_task_body(const T *__restrict__ src, const T *__restrict__ t
           const T *r = sh + 16 * jj;
 #pragma unroll
           for (int k = 0; k < TPT; ++k)
-            panel_rows<NF, FLOOR>(r, px[k], py[k], pz[k], kappa, nk, a[k][0], a[k][1]);
+            panel_rows<NF, FLOOR>(r, px[k], py[k], pz[k], sc, a[k][0], a[k][1]);
         }
 #pragma unroll
         for (int k = 0; k < TPT; ++k)
@@ -437,8 +437,10 @@ __global__ __launch_bounds__(64) void k_p2p_tasks(int ntask, const int *__restri
                                                   const int *__restrict__ ranges,
                                                   const T *__restrict__ src,
                                                   const T *__restrict__ tgt, int N,
-                                                  T kappa, T nk, double *__restrict__ part) {
+                                                  T kappa, double *__restrict__ part) {
   __shared__ __align__(16) T sh[kTileT * 16];
+  __shared__ double etab[sizeof(T) == 8 ? 64 : 1];
+  const Screen<T> sc = make_screen(kappa, etab);
   const int task = xcd_task(ntask);
   if (task < 0) return;
   const int t0 = tasks[4 * task], t1 = tasks[4 * task + 1];
@@ -446,9 +448,9 @@ __global__ __launch_bounds__(64) void k_p2p_tasks(int ntask, const int *__restri
   const int slot = slots[task];
   const LaneSplit ls = lane_split(t1 - t0);
   switch (ls.tpt) {
-#define PBMP_BODY(K)                                                                          \
-  p2p_task_body<T, NF, K, FLOOR>(src, tgt, N, t0, t1, ranges, lb, le, kappa, nk, slot, part, \
-                                 sh, ls.G, ls.L)
+#define PBMP_BODY(K)                                                                        \
+  p2p_task_body<T, NF, K, FLOOR>(src, tgt, N, t0, t1, ranges, lb, le, sc, slot, part, sh, ls.G, \
+                                 ls.L)
     case 1: PBMP_BODY(1); break;
     case 2: PBMP_BODY(2); break;
 #if PBMP_P2P_MAXTPT >= 4
@@ -739,8 +741,8 @@ template <class T, int NF, int SPT, bool FLOOR>
 __device__ void p2pT_body(const T *__restrict__ src, const T *__restrict__ tgt,
                           const double *__restrict__ z, const double *__restrict__ geo, int N,
                           int s0, int s1, const int *__restrict__ ranges, int lb, int le,
-                          T kappa, T nk, double eps_ratio, int slot, double *__restrict__ part,
-                          T *sh, int G, int L) {
+                          const Screen<T> &sc, double eps_ratio, int slot,
+                          double *__restrict__ part, T *sh, int G, int L) {
   const int lane = (int)threadIdx.x;
   const int gi = lane / L, li = lane - gi * L;
   const bool active = gi < G;
@@ -778,7 +780,7 @@ __device__ void p2pT_body(const T *__restrict__ src, const T *__restrict__ tgt,
           const T *r = sh + 8 * e;
 #pragma unroll
           for (int k = 0; k < SPT; ++k)
-            panel_columns<NF, FLOOR>(rec[k], r[0], r[1], r[2], r[3], r[4], r[5], kappa, nk,
+            panel_columns<NF, FLOOR>(rec[k], r[0], r[1], r[2], r[3], r[4], r[5], sc,
                                      a[k][0], a[k][1]);
         }
 #pragma unroll
@@ -814,9 +816,11 @@ __global__ __launch_bounds__(64) void k_p2pT_tasks(int ntask, const int *__restr
                                                    const T *__restrict__ tgt,
                                                    const double *__restrict__ z,
                                                    const double *__restrict__ geo, int N,
-                                                   T kappa, T nk, double eps_ratio,
+                                                   T kappa, double eps_ratio,
                                                    double *__restrict__ part) {
   __shared__ __align__(16) T sh[64 * 8];
+  __shared__ double etab[sizeof(T) == 8 ? 64 : 1];
+  const Screen<T> sc = make_screen(kappa, etab);
   const int task = xcd_task(ntask);
   if (task < 0) return;
   const int B = tasks[4 * task], lb = tasks[4 * task + 1], le = tasks[4 * task + 2];
@@ -837,10 +841,10 @@ __global__ __launch_bounds__(64) void k_p2pT_tasks(int ntask, const int *__restr
     }
   }
   if (spt == 1)
-    p2pT_body<T, NF, 1, FLOOR>(src, tgt, z, geo, N, s0, s1, subs, lb, le, kappa, nk, eps_ratio, slot,
+    p2pT_body<T, NF, 1, FLOOR>(src, tgt, z, geo, N, s0, s1, subs, lb, le, sc, eps_ratio, slot,
                         part, sh, G, 64 / G);
   else
-    p2pT_body<T, NF, 2, FLOOR>(src, tgt, z, geo, N, s0, s1, subs, lb, le, kappa, nk, eps_ratio, slot,
+    p2pT_body<T, NF, 2, FLOOR>(src, tgt, z, geo, N, s0, s1, subs, lb, le, sc, eps_ratio, slot,
                         part, sh, G, 64 / G);
 }
 
@@ -1035,14 +1039,12 @@ template <class T, int P>
 void tree_T_far(Tree &t, hipStream_t s, int nf, int N, const double *geo,
                 const double *src64, const T *src, const T *tgt, const double *z, T kappa,
                 T nk, double eps_ratio, double *part, bool floor_r2) {
-  constexpr int NK = Orders<P>::NK;
   // P2P^T
   const int nbp = ((t.n_p2pT_tasks + 7) / 8) * 8;
 #define PBMP_TPT(NFV, FL)                                                                 \
-  hipLaunchKernelGGL((k_p2pT_tasks<T, NFV, (FL) || sizeof(T) == 8>), dim3(nbp), dim3(64), 0, s, \
-                     t.n_p2pT_tasks, t.d_p2pT_task.p, t.d_range.p, t.d_p2pT_sub.p, src, tgt, z, geo, N,     \
-                     kappa, nk, eps_ratio, part)
-  // (the FP64 pair terms carry their own cut-off)
+  hipLaunchKernelGGL((k_p2pT_tasks<T, NFV, FL>), dim3(nbp), dim3(64), 0, s, t.n_p2pT_tasks, \
+                     t.d_p2pT_task.p, t.d_range.p, t.d_p2pT_sub.p, src, tgt, z, geo, N,     \
+                     kappa, eps_ratio, part)
   if (nf == 3 && floor_r2) PBMP_TPT(3, true);
   else if (nf == 3) PBMP_TPT(3, false);
   else if (floor_r2) PBMP_TPT(1, true);
@@ -1435,7 +1437,6 @@ void tree_mesh_adjoint_far_p(Tree &t, hipStream_t s, int nf, int N, const double
                              const double *src64, const double *lam, double kappa,
                              double eps_ratio, double *part, double *partT, double *gc,
                              double *gy, double *gn, double *gA) {
-  constexpr int NK = Orders<P>::NK;
   // target side: direct pairs and expansions into the forward slots
   const int nbp = ((t.n_p2p_tasks + 7) / 8) * 8;
   if (nf == 3)
@@ -1696,20 +1697,21 @@ void tree_apply(Tree &t, hipStream_t s, bool fp64, int nf, int N, const double *
   const float nk32 = (float)(-kappa * 1.4426950408889634);
   e0 = clk.on ? clk.begin(s) : nullptr;
   const int nbp = ((t.n_p2p_tasks + 7) / 8) * 8;
-#define PBMP_TP(TT, NFV, FL, SRC, TGT, KAP, NK)                                          \
+#define PBMP_TP(TT, NFV, FL, SRC, TGT)                                                   \
   hipLaunchKernelGGL((k_p2p_tasks<TT, NFV, FL>), dim3(nbp), dim3(64), 0, s, t.n_p2p_tasks, \
-                     t.d_p2p_task.p, t.d_p2p_slot.p, t.d_p2p_src.p, SRC, TGT, N, KAP, NK,  \
-                     part)
+                     t.d_p2p_task.p, t.d_p2p_slot.p, t.d_p2p_src.p, SRC, TGT, N,           \
+                     (TT)kappa, part)
+#define PBMP_TPR(TT, SRC, TGT)                            \
+  if (nf == 3 && floor_r2) PBMP_TP(TT, 3, true, SRC, TGT); \
+  else if (nf == 3) PBMP_TP(TT, 3, false, SRC, TGT);       \
+  else if (floor_r2) PBMP_TP(TT, 1, true, SRC, TGT);       \
+  else PBMP_TP(TT, 1, false, SRC, TGT)
   if (fp64) {
-    if (nf == 3) PBMP_TP(double, 3, true, src64, geo, kappa, 0.0);
-    else PBMP_TP(double, 1, true, src64, geo, kappa, 0.0);
+    PBMP_TPR(double, src64, geo);
   } else {
-    const float kf = (float)kappa;
-    if (nf == 3 && floor_r2) PBMP_TP(float, 3, true, src32, tgt32, kf, nk32);
-    else if (nf == 3) PBMP_TP(float, 3, false, src32, tgt32, kf, nk32);
-    else if (floor_r2) PBMP_TP(float, 1, true, src32, tgt32, kf, nk32);
-    else PBMP_TP(float, 1, false, src32, tgt32, kf, nk32);
+    PBMP_TPR(float, src32, tgt32);
   }
+#undef PBMP_TPR
 #undef PBMP_TP
   PBMP_HIP(hipGetLastError());
   if (clk.on) clk.end(s, e0, KernelClock::P2P, t.direct_pairs);

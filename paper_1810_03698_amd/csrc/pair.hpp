@@ -1,9 +1,8 @@
 // Far-field pair terms of the four boundary-integral kernels, shared by the
 // forward and transposed source-target products and by the near/self
-// correction.  The correction subtracts exactly the value the product added
-// (same inputs, same operation sequence, no contraction), so that for tiny
-// panels the rounding of the pair terms cancels instead of being amplified
-// by 1/r^3.
+// correction.  The correction forms the panel sums that the product formed
+// with the same operation sequence (no contraction), so that for tiny panels
+// the rounding of the pair terms cancels instead of being amplified by 1/r^3.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -37,34 +36,23 @@ __device__ __forceinline__ void node_core(float dx, float dy, float dz, float nk
   er = ek * ri;
 }
 
-// Adds one node's terms: vl += 1/r, vy += e^{-kr}/r, kl += 1/r^3,
-// ky += (1 + k r) e^{-k r}/r^3 (as e/r^3 + k e/r^2).
-__device__ __forceinline__ void node_terms(float dx, float dy, float dz,
-                                           float kappa, float nk, float &vl,
-                                           float &vy, float &kl, float &ky) {
-#pragma clang fp contract(off)
-  float ri, er;
-  node_core<true>(dx, dy, dz, nk, ri, er);
-  const float ri2 = ri * ri;
-  vl = vl + ri;
-  vy = vy + er;
-  kl = fmaf(ri2, ri, kl);
-  ky = fmaf(er, ri2, fmaf(kappa * er, ri, ky));
+// 1/sqrt(rr) in FP64: the hardware estimate y0 (1 - rr y0^2 = e, |e| < 2^-23
+// measured over two binades) and one step of the binomial series
+// y0 (1 + e/2 + 3 e^2/8), whose next term is below 2^-70; also r = sqrt(rr)
+// from the same factors.  Two Newton steps took two more operations.  rr must
+// be positive and normal.
+__device__ __forceinline__ double rsqrt_fp64(double rr, double &r) {
+  const double y = __builtin_amdgcn_rsq(rr);
+  const double t = rr * y;
+  const double e = fma(-t, y, 1.0);
+  const double c = e * fma(0.375, e, 0.5);
+  r = fma(t, c, t);
+  return fma(y, c, y);
 }
 
-// 1/sqrt(rr) in FP64: the hardware estimate (v_rsq_f64) refined by two
-// Newton steps y <- y + y (1 - rr y^2) / 2, each of which squares the
-// relative error, so the result is within an ulp or two of the exact
-// value; a square root and a division would take three times the
-// instructions.  rr must be positive and normal.
 __device__ __forceinline__ double rsqrt_fp64(double rr) {
-  double y = __builtin_amdgcn_rsq(rr);
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const double e = fma(-rr, y * y, 1.0);
-    y = fma(0.5 * y, e, y);
-  }
-  return y;
+  double r;
+  return rsqrt_fp64(rr, r);
 }
 
 // e^x in FP64 for x <= 0 (the screening factor e^{-kappa r}; no overflow
@@ -89,23 +77,69 @@ __device__ __forceinline__ double exp_fp64(double x) {
   return ldexp(p, (int)n);
 }
 
-__device__ __forceinline__ void node_terms(double dx, double dy, double dz,
-                                           double kappa, double, double &vl,
-                                           double &vy, double &kl, double &ky) {
-#pragma clang fp contract(off)
-  const double rr = dx * dx + dy * dy + dz * dz;
-  // a node on the target (the one-node rule on a panel's own centroid)
-  // adds nothing, here and in the correction that removes it again
-  const bool on = rr < kMinR2d;
-  const double y = rsqrt_fp64(on ? 1.0 : rr);
-  const double ri = on ? 0.0 : y;
-  const double rad = rr * y;
-  const double ek = exp_fp64(-kappa * rad);
-  const double ri3 = ri * ri * ri;
-  vl = vl + ri;
-  vy = vy + ek * ri;
-  kl = kl + ri3;
-  ky = ky + (1.0 + kappa * rad) * ek * ri3;
+// 2^(j/64), correctly rounded
+__device__ const double kExp2Table[64] = {
+    0x1.0000000000000p+0, 0x1.02c9a3e778061p+0, 0x1.059b0d3158574p+0,
+    0x1.0874518759bc8p+0, 0x1.0b5586cf9890fp+0, 0x1.0e3ec32d3d1a2p+0,
+    0x1.11301d0125b51p+0, 0x1.1429aaea92de0p+0, 0x1.172b83c7d517bp+0,
+    0x1.1a35beb6fcb75p+0, 0x1.1d4873168b9aap+0, 0x1.2063b88628cd6p+0,
+    0x1.2387a6e756238p+0, 0x1.26b4565e27cddp+0, 0x1.29e9df51fdee1p+0,
+    0x1.2d285a6e4030bp+0, 0x1.306fe0a31b715p+0, 0x1.33c08b26416ffp+0,
+    0x1.371a7373aa9cbp+0, 0x1.3a7db34e59ff7p+0, 0x1.3dea64c123422p+0,
+    0x1.4160a21f72e2ap+0, 0x1.44e086061892dp+0, 0x1.486a2b5c13cd0p+0,
+    0x1.4bfdad5362a27p+0, 0x1.4f9b2769d2ca7p+0, 0x1.5342b569d4f82p+0,
+    0x1.56f4736b527dap+0, 0x1.5ab07dd485429p+0, 0x1.5e76f15ad2148p+0,
+    0x1.6247eb03a5585p+0, 0x1.6623882552225p+0, 0x1.6a09e667f3bcdp+0,
+    0x1.6dfb23c651a2fp+0, 0x1.71f75e8ec5f74p+0, 0x1.75feb564267c9p+0,
+    0x1.7a11473eb0187p+0, 0x1.7e2f336cf4e62p+0, 0x1.82589994cce13p+0,
+    0x1.868d99b4492edp+0, 0x1.8ace5422aa0dbp+0, 0x1.8f1ae99157736p+0,
+    0x1.93737b0cdc5e5p+0, 0x1.97d829fde4e50p+0, 0x1.9c49182a3f090p+0,
+    0x1.a0c667b5de565p+0, 0x1.a5503b23e255dp+0, 0x1.a9e6b5579fdbfp+0,
+    0x1.ae89f995ad3adp+0, 0x1.b33a2b84f15fbp+0, 0x1.b7f76f2fb5e47p+0,
+    0x1.bcc1e904bc1d2p+0, 0x1.c199bdd85529cp+0, 0x1.c67f12e57d14bp+0,
+    0x1.cb720dcef9069p+0, 0x1.d072d4a07897cp+0, 0x1.d5818dcfba487p+0,
+    0x1.da9e603db3285p+0, 0x1.dfc97337b9b5fp+0, 0x1.e502ee78b3ff6p+0,
+    0x1.ea4afa2a490dap+0, 0x1.efa1bee615a27p+0, 0x1.f50765b6e4540p+0,
+    0x1.fa7c1819e90d8p+0};
+
+// Screening constants of the pair kernels.  FP64: e^{-kappa r} =
+// 2^(n/64) 2^(f/64) with n + f = -64 kappa r / ln 2, |f| <= 1/2: 2^(n/64) from
+// the 64-entry table (a copy in LDS, one gather) and a shift of the exponent,
+// 2^(f/64) by its Taylor series to degree 5 (remainder below 4e-17); 11
+// operations where the series over |x| <= ln 2 / 2 to degree 13 takes 20.
+// Results below the smallest subnormal come out as zero; WIDE bounds the
+// argument for kappa r beyond the integers of the reduction (1e7).
+template <class T> struct Screen;
+template <> struct Screen<float> {
+  float kappa, nk;  // nk = -kappa log2(e)
+};
+template <> struct Screen<double> {
+  double kappa, c, far;  // c = -64 kappa / ln 2; e^{-kappa far} = 0
+  const double *table;
+  template <bool WIDE> __device__ __forceinline__ double exp(double r) const {
+    if (WIDE) r = fmin(r, far);
+    constexpr double kShift = 0x1.8p52;  // rounds to an integer in the low word
+    const double t = fma(r, c, kShift);
+    const double f = fma(r, c, kShift - t);
+    const int n = (int)(uint32_t)__builtin_bit_cast(uint64_t, t);
+    constexpr double b = 0.6931471805599453 / 64;
+    double p = fma(f, b * b * b * b * b / 120, b * b * b * b / 24);
+    p = fma(p, f, b * b * b / 6);
+    p = fma(p, f, b * b / 2);
+    p = fma(p, f, b);
+    const double s = table[n & 63];
+    return ldexp(fma(p * f, s, s), n >> 6);
+  }
+};
+
+// one wave or more of a block fills the block's copy of the table; the caller
+// synchronises before the first use
+__device__ __forceinline__ Screen<double> make_screen(double kappa, double *lds_table) {
+  if (threadIdx.x < 64) lds_table[threadIdx.x] = kExp2Table[threadIdx.x];
+  return Screen<double>{kappa, kappa * -92.33248261689366, 1e5 / kappa, lds_table};
+}
+__device__ __forceinline__ Screen<float> make_screen(float kappa, double *) {
+  return Screen<float>{kappa, kappa * -1.44269504f};
 }
 
 // n.(p - y0): the nodes of a flat panel share its plane, so this is n.R
@@ -122,42 +156,21 @@ __device__ __forceinline__ double normal_dist(double nx, double ny, double nz,
   return nx * dx + ny * dy + nz * dz;
 }
 
-// Sums of one panel (nf nodes from a 16-word record) at target p, as the
-// products weight them: out = (vl, n.R kl, vy, n.R ky) before the strengths.
-template <class T>
-__device__ __forceinline__ void panel_terms(const T *rec, int nf, T px, T py,
-                                            T pz, T kappa, T nk, T out[4]) {
-  T vl = T(0), vy = T(0), kl = T(0), ky = T(0);
-  T d0[3] = {T(0), T(0), T(0)};
-  for (int q = 0; q < nf; ++q) {
-    const T dx = px - rec[3 * q], dy = py - rec[3 * q + 1], dz = pz - rec[3 * q + 2];
-    if (q == 0) {
-      d0[0] = dx;
-      d0[1] = dy;
-      d0[2] = dz;
-    }
-    node_terms(dx, dy, dz, kappa, nk, vl, vy, kl, ky);
-  }
-  const T nR = normal_dist(rec[9], rec[10], rec[11], d0[0], d0[1], d0[2]);
-  out[0] = vl;
-  out[1] = nR * kl;
-  out[2] = vy;
-  out[3] = nR * ky;
-}
-
 // Node sums of one panel (NF nodes and the normal of record r) at p:
 // vl = sum 1/r, kl = sum 1/r^3, vy = sum e/r, ky = sum (1 + k r) e/r^3 with
-// e = e^{-k r}, and n.R.
+// e = e^{-k r}, and n.R.  FLOOR: with the cut-offs for coincident points (and
+// for kappa r beyond the FP64 exponential's range), which give the same
+// values where they do not apply.
 template <int NF, bool FLOOR>
 __device__ __forceinline__ void panel_sums(const float *r, float px, float py, float pz,
-                                           float kappa, float nk, float &vl, float &kl,
+                                           const Screen<float> &sc, float &vl, float &kl,
                                            float &vy, float &ky, float &nR) {
   float A, B, d0[3];
 #pragma unroll
   for (int q = 0; q < NF; ++q) {
     const float dx = px - r[3 * q], dy = py - r[3 * q + 1], dz = pz - r[3 * q + 2];
     float ri, er;
-    node_core<FLOOR>(dx, dy, dz, nk, ri, er);
+    node_core<FLOOR>(dx, dy, dz, sc.nk, ri, er);
     const float ri2 = ri * ri;
     if (q == 0) {
       d0[0] = dx;
@@ -176,26 +189,44 @@ __device__ __forceinline__ void panel_sums(const float *r, float px, float py, f
       B = fmaf(er, ri, B);
     }
   }
-  ky = fmaf(kappa, B, A);
+  ky = fmaf(sc.kappa, B, A);
   nR = normal_dist(r[9], r[10], r[11], d0[0], d0[1], d0[2]);
 }
 
 template <int NF, bool FLOOR>
 __device__ __forceinline__ void panel_sums(const double *r, double px, double py, double pz,
-                                           double kappa, double nk, double &vl, double &kl,
+                                           const Screen<double> &sc, double &vl, double &kl,
                                            double &vy, double &ky, double &nR) {
-  vl = vy = kl = ky = 0.0;
-  double d0[3];
+#pragma clang fp contract(off)
+  double A, B, d0[3];
 #pragma unroll
   for (int q = 0; q < NF; ++q) {
     const double dx = px - r[3 * q], dy = py - r[3 * q + 1], dz = pz - r[3 * q + 2];
+    double rr = fma(dx, dx, fma(dy, dy, dz * dz)), rad;
+    const bool on = FLOOR && rr < kMinR2d;  // a node on the target adds nothing
+    if (FLOOR) rr = on ? 1.0 : rr;
+    double ri = rsqrt_fp64(rr, rad);
+    if (FLOOR) ri = on ? 0.0 : ri;
+    const double er = sc.exp<FLOOR>(rad) * ri;
+    const double ri2 = ri * ri;
     if (q == 0) {
       d0[0] = dx;
       d0[1] = dy;
       d0[2] = dz;
+      vl = ri;
+      vy = er;
+      kl = ri2 * ri;
+      A = er * ri2;
+      B = er * ri;
+    } else {
+      vl += ri;
+      vy += er;
+      kl = fma(ri2, ri, kl);
+      A = fma(er, ri2, A);
+      B = fma(er, ri, B);
     }
-    node_terms(dx, dy, dz, kappa, nk, vl, vy, kl, ky);
   }
+  ky = fma(sc.kappa, B, A);
   nR = normal_dist(r[9], r[10], r[11], d0[0], d0[1], d0[2]);
 }
 
@@ -204,10 +235,10 @@ __device__ __forceinline__ void panel_sums(const double *r, double px, double py
 // that each accumulator takes two dependent additions per panel rather than
 // one per node (per node, the direct FP32 product ran 4-7 % slower).
 template <int NF, bool FLOOR, class T>
-__device__ __forceinline__ void panel_rows(const T *r, T px, T py, T pz, T kappa, T nk, T &a0,
-                                           T &a1) {
+__device__ __forceinline__ void panel_rows(const T *r, T px, T py, T pz, const Screen<T> &sc,
+                                           T &a0, T &a1) {
   T vl, kl, vy, ky, nR;
-  panel_sums<NF, FLOOR>(r, px, py, pz, kappa, nk, vl, kl, vy, ky, nR);
+  panel_sums<NF, FLOOR>(r, px, py, pz, sc, vl, kl, vy, ky, nR);
   const T skn = r[14] * nR;
   a0 = fma(-r[13], vl, a0);
   a1 = fma(r[15], vy, a1);
@@ -219,9 +250,9 @@ __device__ __forceinline__ void panel_rows(const T *r, T px, T py, T pz, T kappa
 // two sums of panel r (nodes and normal).
 template <int NF, bool FLOOR, class T>
 __device__ __forceinline__ void panel_columns(const T *r, T px, T py, T pz, T z1, T z2, T ez2,
-                                              T kappa, T nk, T &a0, T &a1) {
+                                              const Screen<T> &sc, T &a0, T &a1) {
   T vl, kl, vy, ky, nR;
-  panel_sums<NF, FLOOR>(r, px, py, pz, kappa, nk, vl, kl, vy, ky, nR);
+  panel_sums<NF, FLOOR>(r, px, py, pz, sc, vl, kl, vy, ky, nR);
   a0 = fma(nR, fma(-z2, ky, z1 * kl), a0);
   a1 = fma(ez2, vy, a1);
   a1 = fma(-z1, vl, a1);

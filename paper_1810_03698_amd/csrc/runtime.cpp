@@ -369,7 +369,10 @@ void Runtime::set_mesh(int64_t nv, const double *verts, int64_t nt,
       }
       min_alt = std::min(min_alt, 2.0 * h_geo_[6 * (size_t)N + j] / std::sqrt(len2));
     }
-    floor_r2_ = o.gauss_far == 1 || !(min_alt / 6.0 > 1e-4 + 1e-6 * max_abs);
+    // (also where kappa r could leave the range of the FP64 exponential's
+    // unguarded argument reduction)
+    floor_r2_ = o.gauss_far == 1 || !(min_alt / 6.0 > 1e-4 + 1e-6 * max_abs) ||
+                !(o.kappa * 4.0 * max_abs < 1e6);
   }
   build_near_lists();
   // --- tree
