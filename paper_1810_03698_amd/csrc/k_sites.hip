@@ -7,6 +7,7 @@
 #include <cmath>
 
 #include "kernels.hpp"
+#include "pair.hpp"
 
 namespace pbmp {
 
@@ -16,72 +17,84 @@ constexpr double kInv4Pi = 0.07957747154594767;
 constexpr double kFourPi = 12.566370614359172;
 
 // ------------------------------------------------------------------ RHS
-// Site record in LDS: x y z q px py pz Qxx Qxy Qxz Qyy Qyz Qzz
-constexpr int kSiteRec = 13;
+// Blocks of 64 TPT panels: lane l holds panels l, l + 64, ...; the block's
+// four waves take every fourth site of the staged tiles, and their sums are
+// added through LDS in wave order (a panel per thread left a 30k-panel surface
+// with fewer waves than SIMDs).  The multipoles are staged in T, once per
+// block instead of once per pair; the differences are formed in FP64 and the
+// sums kept there.  Bound by VALU issue, the FP64 differences and sums about
+// 40 % of it: 1376 -> 650 us on 144500 panels and 5000 sites, 202 -> 37 us on
+// 28880 and 1000 (mixed precision).
 constexpr int kSiteTile = 128;
+constexpr int kRhsVal = 12;  // q px py pz Qxx Qxy Qxz Qyy Qyz Qzz per site
 
-template <bool FP64>
-__global__ __launch_bounds__(256) void k_rhs(int N, int M,
-                                             const double *__restrict__ geo,
+template <class T, int TPT>
+__global__ __launch_bounds__(256) void k_rhs(int N, int M, const double *__restrict__ geo,
                                              const double *__restrict__ xyz,
                                              const double *__restrict__ q,
                                              const double *__restrict__ p,
-                                             const double *__restrict__ Q9,
-                                             double scale,
+                                             const double *__restrict__ Q9, double scale,
                                              double *__restrict__ f) {
-  __shared__ double sh[kSiteTile * kSiteRec];
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int il = min(i, N - 1);
-  const double cx = geo[il], cy = geo[N + il], cz = geo[2 * N + il];
-  double acc = 0.0;
+  __shared__ __align__(16) double spos[kSiteTile * 4];
+  __shared__ __align__(16) T sval[kSiteTile * kRhsVal];
+  __shared__ double red[3][TPT][64];
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+  double c[TPT][3], acc[TPT];
+  int ti[TPT];
+#pragma unroll
+  for (int k = 0; k < TPT; ++k) {
+    ti[k] = blockIdx.x * (64 * TPT) + 64 * k + lane;
+    const int il = min(ti[k], N - 1);
+    for (int d = 0; d < 3; ++d) c[k][d] = geo[(size_t)d * N + il];
+    acc[k] = 0.0;
+  }
   for (int k0 = 0; k0 < M; k0 += kSiteTile) {
     const int nk = min(kSiteTile, M - k0);
     __syncthreads();
-    for (int e = threadIdx.x; e < nk; e += blockDim.x) {
-      const int k = k0 + e;
-      double *r = sh + kSiteRec * e;
-      r[0] = xyz[3 * k];
-      r[1] = xyz[3 * k + 1];
-      r[2] = xyz[3 * k + 2];
-      r[3] = q[k];
-      r[4] = p[3 * k];
-      r[5] = p[3 * k + 1];
-      r[6] = p[3 * k + 2];
-      r[7] = Q9[9 * k];
-      r[8] = Q9[9 * k + 1];
-      r[9] = Q9[9 * k + 2];
-      r[10] = Q9[9 * k + 4];
-      r[11] = Q9[9 * k + 5];
-      r[12] = Q9[9 * k + 8];
+    for (int e = threadIdx.x; e < nk; e += 256) {
+      const int m = k0 + e;
+      for (int d = 0; d < 3; ++d) spos[4 * e + d] = xyz[3 * m + d];
+      T *r = sval + kRhsVal * e;
+      r[0] = (T)q[m];
+      for (int d = 0; d < 3; ++d) r[1 + d] = (T)p[3 * m + d];
+      const double *Q = Q9 + 9 * (size_t)m;
+      r[4] = (T)Q[0];
+      r[5] = (T)Q[1];
+      r[6] = (T)Q[2];
+      r[7] = (T)Q[4];
+      r[8] = (T)Q[5];
+      r[9] = (T)Q[8];
     }
     __syncthreads();
-    for (int e = 0; e < nk; ++e) {
-      const double *r = sh + kSiteRec * e;
-      if (FP64) {
-        const double X = cx - r[0], Y = cy - r[1], Z = cz - r[2];
-        const double rr = X * X + Y * Y + Z * Z;
-        const double ri = 1.0 / sqrt(rr);
-        const double ri2 = ri * ri;
-        const double pR = r[4] * X + r[5] * Y + r[6] * Z;
-        const double QRR = r[7] * X * X + r[10] * Y * Y + r[12] * Z * Z +
-                           2.0 * (r[8] * X * Y + r[9] * X * Z + r[11] * Y * Z);
-        acc += ri * (r[3] + ri2 * (pR + 0.5 * QRR * ri2));
-      } else {
-        const float X = (float)(cx - r[0]), Y = (float)(cy - r[1]),
-                    Z = (float)(cz - r[2]);
-        const float rr = fmaf(X, X, fmaf(Y, Y, Z * Z));
-        const float ri = __builtin_amdgcn_rsqf(rr);
-        const float ri2 = ri * ri;
-        const float pR = (float)r[4] * X + (float)r[5] * Y + (float)r[6] * Z;
-        const float QRR = (float)r[7] * X * X + (float)r[10] * Y * Y +
-                          (float)r[12] * Z * Z +
-                          2.0f * ((float)r[8] * X * Y + (float)r[9] * X * Z +
-                                  (float)r[11] * Y * Z);
-        acc += (double)(ri * ((float)r[3] + ri2 * (pR + 0.5f * QRR * ri2)));
+    for (int e = wave; e < nk; e += 4) {
+      const double *s = spos + 4 * e;
+      const T *r = sval + kRhsVal * e;
+#pragma unroll
+      for (int k = 0; k < TPT; ++k) {
+        const T X = (T)(c[k][0] - s[0]), Y = (T)(c[k][1] - s[1]), Z = (T)(c[k][2] - s[2]);
+        T rr, ri;
+        if constexpr (sizeof(T) == 4) {
+          rr = fmaf(X, X, fmaf(Y, Y, Z * Z));
+          ri = __builtin_amdgcn_rsqf(rr);
+        } else {
+          rr = X * X + Y * Y + Z * Z;
+          ri = rsqrt_fp64(rr);
+        }
+        const T ri2 = ri * ri;
+        const T pR = r[1] * X + r[2] * Y + r[3] * Z;
+        const T QRR = r[4] * X * X + r[7] * Y * Y + r[9] * Z * Z +
+                      T(2) * (r[5] * X * Y + r[6] * X * Z + r[8] * Y * Z);
+        acc[k] += (double)(ri * (r[0] + ri2 * (pR + T(0.5) * QRR * ri2)));
       }
     }
   }
-  if (i < N) f[i] = acc * scale;
+  if (wave > 0)
+    for (int k = 0; k < TPT; ++k) red[wave - 1][k][lane] = acc[k];
+  __syncthreads();
+  if (wave == 0)
+    for (int k = 0; k < TPT; ++k)
+      if (ti[k] < N)
+        f[ti[k]] = (acc[k] + red[0][k][lane] + red[1][k][lane] + red[2][k][lane]) * scale;
 }
 
 // ------------------------------------------------------------- readout
@@ -123,95 +136,130 @@ __device__ inline void node_kernels(T X, T Y, T Z, T nx, T ny, T nz, T nR,
   }
 }
 
-// Far-field readout: one site per lane (64 sites per block), the panels of
-// one source chunk staged through LDS in tiles of kRoTile records (coalesced
-// 16-byte loads of the contiguous records, all issued before the first
-// store), per-chunk partial sums part[chunk][site][k].  Per panel the sums
-// are formed as in the operator: node differences from FP64 positions, the
-// kernels in T, the panel's strengths applied before the FP64 accumulation.
+// Far-field readout.  A block takes 64 sites (or the next power of two of
+// fewer) and one source chunk, its panels staged through LDS in tiles of
+// kRoTile records (16-byte loads, all issued before the first store); its four
+// waves take every fourth panel, and with L < 64 site lanes the 64 / L groups
+// of a wave share those.  Per-chunk partial sums part[chunk][site][k].  (Blocks
+// of one wave with the same tiles were bound to 3.5 waves per SIMD by their
+// LDS: 3.65 ms against 3.15 ms on 144500 panels and 5000 sites.)
+//
+// Node differences and n.R are formed in FP64, the kernels in T, and each
+// panel's sums are added in FP64.  With s_V, s_K the strengths and R the
+// difference, one node adds to the potential and its derivatives
+//   value  s_V/r - s_K n.R/r^3,   gradient  a R + b n,
+//   second derivatives  c R R^T + d (n R^T + R n^T) + a I,
+//   a = 3 s_K n.R/r^5 - s_V/r^3,  b = -s_K/r^3,
+//   c = 3 s_V/r^5 - 15 s_K n.R/r^7,  d = 3 s_K/r^5,
+// so the nodes' sums of a R, a, b, c R R^T and d R suffice and the normal enters
+// once per panel: 33 FP32 operations per node where single and double layer
+// accumulated apart took about 90.  VALU issue bound; the FP64 differences,
+// conversions and per-panel additions are half of it.  All ten values on
+// 144500 panels and 5000 sites 7.90 -> 3.15 ms, the field alone on 28880 and
+// 1000 127 -> 67 us, on 1280 and 8 in FP64 39 -> 4.5 us.
 constexpr int kRoTile = 64;
+constexpr int kRoRec = 18;  // padded FP64 record: lane groups read different ones
 
-template <bool FP64, bool FULL>
-__global__ __launch_bounds__(64) void k_readout_far(
-    int N, int M, int nf, const double *__restrict__ src64,
-    const float *__restrict__ src32, const double *__restrict__ xyz, int chunk,
-    double *__restrict__ part) {
+template <class T, bool FULL, int NF>
+__global__ __launch_bounds__(256) void k_readout_far(
+    int N, int M, const double *__restrict__ src64, const double *__restrict__ xyz,
+    int chunk, int L, double *__restrict__ part) {
   constexpr int NO = FULL ? 10 : 4;
   typedef double d2 __attribute__((ext_vector_type(2)));
-  typedef float f4 __attribute__((ext_vector_type(4)));
-  __shared__ __align__(16) double s64[kRoTile * 16];
-  __shared__ __align__(16) float s32[FP64 ? 4 : kRoTile * 16];
-  const int lane = (int)threadIdx.x;
-  const int l = blockIdx.x * 64 + lane;
-  const int lc = min(l, M - 1);
+  __shared__ __align__(16) double s64[kRoTile * kRoRec];
+  __shared__ __align__(16) T sval[kRoTile * 8];  // n, s_V, s_K in T
+  __shared__ double red[3][64];
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+  const int G = 64 / L, gi = lane / L, li = lane - gi * L;
   const int j0 = blockIdx.y * chunk, j1 = min(N, j0 + chunk);
+  const int l = blockIdx.x * L + li, lc = min(l, M - 1);
   const double P[3] = {xyz[3 * lc], xyz[3 * lc + 1], xyz[3 * lc + 2]};
   double acc[NO];
-  for (int k = 0; k < NO; ++k) acc[k] = 0.0;
+  for (int c = 0; c < NO; ++c) acc[c] = 0.0;
   for (int jt = j0; jt < j1; jt += kRoTile) {
     const int nj = min(kRoTile, j1 - jt);
     __syncthreads();
     {
       const d2 *g = reinterpret_cast<const d2 *>(src64 + 16 * (size_t)jt);
-      d2 *d = reinterpret_cast<d2 *>(s64);
       const int n = nj * 8;
-      d2 v[8];
+      d2 v[2];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int e = lane + 64 * u;
+      for (int u = 0; u < 2; ++u) {
+        const int e = (int)threadIdx.x + 256 * u;
         if (e < n) v[u] = g[e];
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int e = lane + 64 * u;
-        if (e < n) d[e] = v[u];
-      }
-      if constexpr (!FP64) {
-        const f4 *g32 = reinterpret_cast<const f4 *>(src32 + 16 * (size_t)jt);
-        f4 *d32 = reinterpret_cast<f4 *>(s32);
-        const int n32 = nj * 4;
-        f4 w[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int e = lane + 64 * u;
-          if (e < n32) w[u] = g32[e];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int e = lane + 64 * u;
-          if (e < n32) d32[e] = w[u];
-        }
+      for (int u = 0; u < 2; ++u) {
+        const int e = (int)threadIdx.x + 256 * u;
+        if (e < n) *reinterpret_cast<d2 *>(s64 + kRoRec * (e >> 3) + 2 * (e & 7)) = v[u];
       }
     }
     __syncthreads();
-    for (int jj = 0; jj < nj; ++jj) {
-      const double *r64 = s64 + 16 * jj;
-      if constexpr (FP64) {
-        double g[NO], h[NO];
-        for (int k = 0; k < NO; ++k) g[k] = h[k] = 0.0;
-        const double nR = r64[9] * P[0] + r64[10] * P[1] + r64[11] * P[2] - r64[12];
-        for (int qn = 0; qn < nf; ++qn)
-          node_kernels<double, FULL>(P[0] - r64[3 * qn], P[1] - r64[3 * qn + 1],
-                                     P[2] - r64[3 * qn + 2], r64[9], r64[10], r64[11],
-                                     nR, g, h);
-        for (int k = 0; k < NO; ++k) acc[k] += r64[13] * g[k] - r64[14] * h[k];
-      } else {
-        const float *r = s32 + 16 * jj;
-        float g[NO], h[NO];
-        for (int k = 0; k < NO; ++k) g[k] = h[k] = 0.0f;
-        const float nR = (float)(r64[9] * P[0] + r64[10] * P[1] + r64[11] * P[2] - r64[12]);
-        for (int qn = 0; qn < nf; ++qn)
-          node_kernels<float, FULL>((float)(P[0] - r64[3 * qn]),
-                                    (float)(P[1] - r64[3 * qn + 1]),
-                                    (float)(P[2] - r64[3 * qn + 2]), r[9], r[10],
-                                    r[11], nR, g, h);
-        for (int k = 0; k < NO; ++k)
-          acc[k] += (double)(r[13] * g[k] - r[14] * h[k]);
+    if ((int)threadIdx.x < nj) {
+      const double *r = s64 + kRoRec * threadIdx.x;
+      T *t = sval + 8 * threadIdx.x;
+      for (int d = 0; d < 3; ++d) t[d] = (T)r[9 + d];
+      t[3] = (T)r[13];
+      t[4] = (T)r[14];
+    }
+    __syncthreads();
+    for (int jj = wave + 4 * gi; jj < nj; jj += 4 * G) {
+      const double *r = s64 + kRoRec * jj;
+      const T n[3] = {sval[8 * jj], sval[8 * jj + 1], sval[8 * jj + 2]};
+      const T sv = sval[8 * jj + 3], sk = sval[8 * jj + 4];
+      const T nR = (T)(r[9] * P[0] + r[10] * P[1] + r[11] * P[2] - r[12]);
+      const T skn = sk * nR;
+      T val = T(0), sa = T(0), sb = T(0), aR[3] = {T(0), T(0), T(0)};
+      T dR[3] = {T(0), T(0), T(0)}, rr6[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
+#pragma unroll
+      for (int q = 0; q < NF; ++q) {
+        const T R[3] = {(T)(P[0] - r[3 * q]), (T)(P[1] - r[3 * q + 1]), (T)(P[2] - r[3 * q + 2])};
+        const T rr = R[0] * R[0] + R[1] * R[1] + R[2] * R[2];
+        T i1;
+        if constexpr (sizeof(T) == 4) i1 = __builtin_amdgcn_rsqf(rr);
+        else i1 = rsqrt_fp64(rr);
+        const T i2 = i1 * i1, i3 = i1 * i2, i5 = i3 * i2;
+        const T a = T(3) * skn * i5 - sv * i3;
+        val += sv * i1 - skn * i3;
+        sb -= sk * i3;
+        for (int d = 0; d < 3; ++d) aR[d] += a * R[d];
+        if constexpr (FULL) {
+          const T i7 = i5 * i2;
+          const T c = T(3) * sv * i5 - T(15) * skn * i7;
+          const T d = T(3) * sk * i5;
+          sa += a;
+          for (int e = 0; e < 3; ++e) dR[e] += d * R[e];
+          const T cx = c * R[0], cy = c * R[1], cz = c * R[2];
+          rr6[0] += cx * R[0];
+          rr6[1] += cx * R[1];
+          rr6[2] += cx * R[2];
+          rr6[3] += cy * R[1];
+          rr6[4] += cy * R[2];
+          rr6[5] += cz * R[2];
+        }
+      }
+      acc[0] += (double)val;
+      for (int d = 0; d < 3; ++d) acc[1 + d] += (double)(aR[d] + sb * n[d]);
+      if constexpr (FULL) {
+        acc[4] += (double)(rr6[0] + (T(2) * n[0] * dR[0] + sa));
+        acc[5] += (double)(rr6[1] + (n[0] * dR[1] + n[1] * dR[0]));
+        acc[6] += (double)(rr6[2] + (n[0] * dR[2] + n[2] * dR[0]));
+        acc[7] += (double)(rr6[3] + (T(2) * n[1] * dR[1] + sa));
+        acc[8] += (double)(rr6[4] + (n[1] * dR[2] + n[2] * dR[1]));
+        acc[9] += (double)(rr6[5] + (T(2) * n[2] * dR[2] + sa));
       }
     }
   }
-  if (l < M)
-    for (int k = 0; k < NO; ++k) part[((size_t)blockIdx.y * M + l) * NO + k] = acc[k];
+  // groups, then waves, in a fixed order (L is a power of two)
+  for (int c = 0; c < NO; ++c) {
+    for (int o = L; o < 64; o <<= 1) acc[c] += __shfl_xor(acc[c], o, 64);
+    __syncthreads();
+    if (wave > 0) red[wave - 1][lane] = acc[c];
+    __syncthreads();
+    if (wave == 0 && gi == 0 && l < M)
+      part[((size_t)blockIdx.y * M + l) * NO + c] =
+          acc[c] + red[0][lane] + red[1][lane] + red[2][lane];
+  }
 }
 
 // Near-singular correction at the sites (19-node rule instead of the far
@@ -486,37 +534,50 @@ void launch_rhs(hipStream_t s, bool fp64, int N, int M, const double *geo,
                 const double *xyz, const double *q, const double *p,
                 const double *Q9, double eps_in, double *f) {
   const double scale = kInv4Pi / eps_in;
-  if (fp64)
-    hipLaunchKernelGGL(k_rhs<true>, dim3((N + 255) / 256), dim3(256), 0, s, N,
-                       M, geo, xyz, q, p, Q9, scale, f);
-  else
-    hipLaunchKernelGGL(k_rhs<false>, dim3((N + 255) / 256), dim3(256), 0, s, N,
-                       M, geo, xyz, q, p, Q9, scale, f);
+  // two panels per lane share the reads of a site where that still leaves
+  // four blocks per CU
+  const int tpt = N > 128 * 1024 ? 2 : 1;
+  const dim3 grid((N + 64 * tpt - 1) / (64 * tpt));
+#define PBMP_RHS(T, TPT)                                                                      \
+  hipLaunchKernelGGL((k_rhs<T, TPT>), grid, dim3(256), 0, s, N, M, geo, xyz, q, p, Q9, scale, f)
+  if (fp64 && tpt == 2) PBMP_RHS(double, 2);
+  else if (fp64) PBMP_RHS(double, 1);
+  else if (tpt == 2) PBMP_RHS(float, 2);
+  else PBMP_RHS(float, 1);
+#undef PBMP_RHS
   PBMP_HIP(hipGetLastError());
 }
 
 int readout_chunks(int N, int M) {
-  // about 4096 blocks, each chunk at least one tile of panels
+  // about 2048 blocks of four waves, each chunk at least one tile of panels
   const int tiles = (std::max(M, 1) + 63) / 64;
-  const int c = (4096 + tiles - 1) / tiles;
+  const int c = (2048 + tiles - 1) / tiles;
   return std::max(1, std::min(c, N / kRoTile));
 }
 
 void launch_readout(hipStream_t s, bool fp64, bool full, int N, int M,
-                    const double *src64, const float *src32, const double *geo,
+                    const double *src64, const double *geo,
                     const double *verts, const int *tri, const RuleArgs &ru,
                     const double *x, const double *xyz, const int *srow,
                     const int *scol, int nchunk, double *part, double *out) {
   if (M <= 0) return;
   const int chunk = (N + nchunk - 1) / nchunk;
-  dim3 grid((M + 63) / 64, nchunk);
-#define PBMP_RO(F64, FULL)                                                   \
-  hipLaunchKernelGGL((k_readout_far<F64, FULL>), grid, dim3(64), 0, s, N, M, \
-                     ru.nf, src64, src32, xyz, chunk, part)
-  if (fp64 && full) PBMP_RO(true, true);
-  else if (fp64) PBMP_RO(true, false);
-  else if (full) PBMP_RO(false, true);
-  else PBMP_RO(false, false);
+  int L = 64;
+  while (L / 2 >= M) L /= 2;
+  const dim3 grid((M + L - 1) / L, nchunk);
+#define PBMP_RO(T, FULL)                                                                       \
+  do {                                                                                         \
+    if (ru.nf == 3)                                                                            \
+      hipLaunchKernelGGL((k_readout_far<T, FULL, 3>), grid, dim3(256), 0, s, N, M, src64, xyz, \
+                         chunk, L, part);                                                      \
+    else                                                                                       \
+      hipLaunchKernelGGL((k_readout_far<T, FULL, 1>), grid, dim3(256), 0, s, N, M, src64, xyz, \
+                         chunk, L, part);                                                      \
+  } while (0)
+  if (fp64 && full) PBMP_RO(double, true);
+  else if (fp64) PBMP_RO(double, false);
+  else if (full) PBMP_RO(float, true);
+  else PBMP_RO(float, false);
 #undef PBMP_RO
   PBMP_HIP(hipGetLastError());
   if (full)

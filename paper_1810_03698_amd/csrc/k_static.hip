@@ -53,7 +53,7 @@ void Runtime::site_fields_noalloc(const double *x, double *out) {
   double *xi = scr, *part = scr + nx;
   launch_permute(s_, N_, 2, d_perm_.p, x, xi, true);
   launch_pack_strengths(s_, N_, ru_.nf, o.eps_in / o.eps_out, geo_.p, xi, src64_.p, src32_.p);
-  launch_readout(s_, fp64(), true, N_, M_, src64_.p, src32_.p, geo_.p, verts_.p, tri_.p, ru_,
+  launch_readout(s_, fp64(), true, N_, M_, src64_.p, geo_.p, verts_.p, tri_.p, ru_,
                  xi, sxyz_.p, srow_.p, scol_.p, nchunk, part, out);
   sync();
 }

@@ -78,7 +78,7 @@ void launch_rhs(hipStream_t s, bool fp64, int N, int M, const double *geo,
 // integral-equation normalisation.  Far rule over all panels, then the
 // near-singular correction over the site's near panels (srow/scol).
 void launch_readout(hipStream_t s, bool fp64, bool full, int N, int M,
-                    const double *src64, const float *src32, const double *geo,
+                    const double *src64, const double *geo,
                     const double *verts, const int *tri, const RuleArgs &ru,
                     const double *x, const double *xyz, const int *srow,
                     const int *scol, int nchunk, double *part, double *out);

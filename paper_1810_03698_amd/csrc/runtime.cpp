@@ -872,7 +872,7 @@ int Runtime::gmres_generic(int n, const KOp &op, const KPrec &prec, const double
 // ------------------------------------------------------------- readout
 void Runtime::readout(const double *x, bool full, double *out) {
   launch_pack_strengths(s_, N_, ru_.nf, o.eps_in / o.eps_out, geo_.p, x, src64_.p, src32_.p);
-  launch_readout(s_, fp64(), full, N_, M_, src64_.p, src32_.p, geo_.p, verts_.p,
+  launch_readout(s_, fp64(), full, N_, M_, src64_.p, geo_.p, verts_.p,
                  tri_.p, ru_, x, sxyz_.p, srow_.p, scol_.p, ro_chunks_, rpart_.p,
                  out);
 }

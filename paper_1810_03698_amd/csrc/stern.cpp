@@ -40,7 +40,7 @@ void Runtime::set_probe(int M, const std::vector<double> &pts) {
 
 void Runtime::probe(const double *x, bool f64, double *out4) {
   launch_pack_strengths(s_, N_, ru_.nf, o.eps_in / o.eps_out, geo_.p, x, src64_.p, src32_.p);
-  launch_readout(s_, fp64() || f64, false, N_, Mp_, src64_.p, src32_.p, geo_.p, verts_.p,
+  launch_readout(s_, fp64() || f64, false, N_, Mp_, src64_.p, geo_.p, verts_.p,
                  tri_.p, ru_, x, pxyz_.p, prow_.p, pcol_.p, p_chunks_, ppart_.p, out4);
 }
 
