@@ -92,235 +92,277 @@ __device__ inline int xcd_task(int ntasks) {
   return t < ntasks ? t : -1;
 }
 
+// ------------------------------------------------------------- harmonics
+// The harmonic words of a box (harmonic.hpp) from its Cartesian moments m
+// [NV | NK] in LDS, merged into the two rows of the product: Laplace mK - mV,
+// Yukawa eps mV - mK.  A lane per harmonic (at most 64), its terms (k, C for
+// Laplace, C for Yukawa) from a table.  Called by the first wave of whichever
+// block holds a box's final moments, so that the map costs no launch of its
+// own; to words64 or, rounded, to words32 (the other is null).
+struct HarmOut {
+  const int *off, *k, *pos;
+  const double *c;
+  double eps_ratio;
+  double *words64;
+  float *words32;
+};
+
+template <int P>
+__device__ __forceinline__ void harmonic_words(int box, const double *m, const HarmOut &h) {
+  constexpr int NC = Orders<P>::NV, NS = Orders<P>::NS, NH = Harm<P + 1>::NH;
+  static_assert(NH <= 64, "a lane per harmonic");
+  const int lane = (int)threadIdx.x;
+  if (lane >= NH) return;
+  double a = 0.0, b = 0.0;
+  for (int t = h.off[lane]; t < h.off[lane + 1]; ++t) {
+    const int k = h.k[t];
+    const double mv = k < NC ? m[k] : 0.0, mk = m[NC + k];
+    a += h.c[2 * t] * (mk - mv);
+    b += h.c[2 * t + 1] * (h.eps_ratio * mv - mk);
+  }
+  const size_t o = (size_t)box * NS + h.pos[lane];
+  if (h.words64) {
+    h.words64[o] = a;
+    h.words64[o + 1] = b;
+  } else {
+    h.words32[o] = (float)a;
+    h.words32[o + 1] = (float)b;
+  }
+}
+
 // ---------------------------------------------------------------- P2M
 // Moments of every leaf straight from its nodes (every box is a contiguous
-// panel range): one block (one wave by default) per task, a task being a
-// leaf's panels [s0, s1) or a slice of at most mom_chunk_panels(P) of them.
-// Every lane takes nodes, builds all monomials h^k incrementally (each from
-// its parent multi-index) and accumulates both moment sets in registers; a
-// wave reduction (shuffles), and an LDS reduction across waves when a block
-// has several, give the task's partial moments, and k_mom_reduce adds a
-// leaf's slices in a fixed order.  The accepted boxes above the leaves then
-// take their moments from the leaves' by exact shifts (k_shift_tasks): two
-// short launches instead of walking every box's nodes, whose long tasks and
-// few waves left the direct form latency-bound.
-#ifndef PBMP_P2M_THREADS
-#define PBMP_P2M_THREADS 64
-#endif
-constexpr int kP2MThreads = PBMP_P2M_THREADS;
-constexpr int kP2MTile = 64;  // panels per LDS tile (64 and 192 nodes: multiples of 64)
-static_assert(kP2MThreads % 64 == 0 && kP2MTile % kP2MThreads == 0, "P2M tiling");
+// panel range), one block per task, a task being a leaf's panels [s0, s1) or a
+// slice of at most kMomChunkPanels of them.  With h the node offsets,
+//   mV_k = sum s_V h^k,   mK_k = sum_d k_d sum s_K n_d h^(k - e_d),
+// so the four weighted sums of h^k with weights s_V, s_K n_x, s_K n_y, s_K n_z
+// over |k| <= P suffice: one per wave, lanes over the nodes, all monomials built
+// incrementally (each from its parent multi-index).  The panel records pass
+// through LDS in tiles, padded to 17 doubles against bank conflicts.
+// k_mom_reduce adds a leaf's slices in a fixed order.  Latency bound (a few
+// hundred to a thousand leaves); one wave per leaf with both moment sets of
+// 140 coefficients at P 5 left one wave per SIMD.
+constexpr int kP2MTile = 64;  // panels per LDS tile
 
 // direct: every leaf is one task, so the task's sums are the leaf's moments
-// and go straight to mom64 instead of part
+// and go straight to mom64 and the harmonic words instead of part
 template <int P>
-__global__ __launch_bounds__(kP2MThreads) void k_p2m_tasks(int nf, const int *__restrict__ tasks,
+__global__ __launch_bounds__(256) void k_p2m_tasks(int nf, const int *__restrict__ tasks,
                                                    const double *__restrict__ center,
                                                    const double *__restrict__ src,
+                                                   const int *__restrict__ monos,
                                                    double *__restrict__ part, int direct,
-                                                   double *__restrict__ mom64) {
+                                                   double *__restrict__ mom64, HarmOut ho) {
   constexpr Multi<P> mi{};
-  constexpr Multi<P + 1> miK{};
-  constexpr int NC = Orders<P>::NV, NK = Orders<P>::NK, NM = Orders<P>::NM;
-  constexpr int NW = kP2MThreads / 64;
-  __shared__ double red[NW][NM];
+  constexpr int NC = Orders<P>::NV, NM = Orders<P>::NM, NA = (NC + 3) / 4 * 4;
+  __shared__ double sh[kP2MTile * 17];
+  __shared__ double col[4][NC];
+  __shared__ double fin[NM];
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
   const int B = tasks[3 * blockIdx.x];
   const int s0 = tasks[3 * blockIdx.x + 1], s1 = tasks[3 * blockIdx.x + 2];
   const double c[3] = {center[3 * B], center[3 * B + 1], center[3 * B + 2]};
-  double m[NC], mk[NK];
+  double acc[NA];
 #pragma unroll
-  for (int k = 0; k < NC; ++k) m[k] = 0.0;
-#pragma unroll
-  for (int k = 0; k < NK; ++k) mk[k] = 0.0;
-  // the slice's panel records pass through LDS in tiles of kP2MTile
-  // (coalesced loads, all issued together); records padded to 17 doubles
-  // against bank conflicts.  A tile holds a multiple of 64 nodes, so every
-  // lane takes the same nodes in the same order as without staging.
-  __shared__ double sh[kP2MTile * 17];
+  for (int k = 0; k < NA; ++k) acc[k] = 0.0;
   for (int jt = s0; jt < s1; jt += kP2MTile) {
     const int nj = min(kP2MTile, s1 - jt);
     __syncthreads();
     {
-      // 16-byte loads, two in flight per round (a plain copy loop waits for
-      // each load before its store)
-      constexpr int U = kP2MTile * 8 / kP2MThreads, Bk = 2;
       typedef double d2 __attribute__((ext_vector_type(2)));
       const d2 *s2 = reinterpret_cast<const d2 *>(src + (size_t)jt * 16);
+      d2 buf[2];
 #pragma unroll
-      for (int u0 = 0; u0 < U; u0 += Bk) {
-        d2 buf[Bk];
+      for (int u = 0; u < 2; ++u) {
+        const int e = (int)threadIdx.x + 256 * u;
+        if (e < nj * 8) buf[u] = s2[e];
+      }
 #pragma unroll
-        for (int u = 0; u < Bk; ++u) {
-          const int e = threadIdx.x + (u0 + u) * kP2MThreads;
-          if (e < nj * 8) buf[u] = s2[e];
-        }
-#pragma unroll
-        for (int u = 0; u < Bk; ++u) {
-          const int e = threadIdx.x + (u0 + u) * kP2MThreads;
-          if (e < nj * 8) {
-            double *d = sh + 17 * (e >> 3) + 2 * (e & 7);
-            d[0] = buf[u].x;
-            d[1] = buf[u].y;
-          }
+      for (int u = 0; u < 2; ++u) {
+        const int e = (int)threadIdx.x + 256 * u;
+        if (e < nj * 8) {
+          double *d = sh + 17 * (e >> 3) + 2 * (e & 7);
+          d[0] = buf[u].x;
+          d[1] = buf[u].y;
         }
       }
     }
     __syncthreads();
-    for (int g = threadIdx.x; g < nj * nf; g += kP2MThreads) {
+    for (int g = lane; g < nj * nf; g += 64) {
       const int q = g % nf;
       const double *r = sh + 17 * (g / nf);
       const double h[3] = {r[3 * q] - c[0], r[3 * q + 1] - c[1], r[3 * q + 2] - c[2]};
-      const double n[3] = {r[9], r[10], r[11]};
-      const double sv = r[13], sk = r[14];
+      const double w = wave == 0 ? r[13] : r[14] * r[8 + wave];
       double mono[NC];
-      mono[0] = 1.0;
+      mono[0] = w;
+      acc[0] += w;
 #pragma unroll
       for (int k = 1; k < NC; ++k) {
         const int d = mi.e[k][0] ? 0 : (mi.e[k][1] ? 1 : 2);
         mono[k] = mono[mi.m1[k][d]] * h[d];
-      }
-#pragma unroll
-      for (int k = 0; k < NC; ++k) m[k] += sv * mono[k];
-      // double layer to degree P + 1 (its monomials h^(k - e_d) have
-      // degree <= P; a multi-index has the same position in both tables)
-#pragma unroll
-      for (int k = 0; k < NK; ++k) {
-        double dk = 0.0;
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-          if (miK.m1[k][d] >= 0) dk += miK.e[k][d] * n[d] * mono[miK.m1[k][d]];
-        mk[k] += sk * dk;
+        acc[k] += mono[k];
       }
     }
   }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < NM; ++k) {
-    double a = k < NC ? m[k] : mk[k - NC];
-    for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
-    if (lane == 0) red[wave][k] = a;
-  }
+  wave_sums(acc, [&](int k, double v) {
+    if (k < NC) col[wave][k] = v;
+  });
   __syncthreads();
-  for (int k = threadIdx.x; k < NM; k += kP2MThreads) {
-    double v = red[0][k];
-    for (int w = 1; w < NW; ++w) v += red[w][k];
-    if (direct) mom64[(size_t)B * NM + k] = v;
-    else part[(size_t)blockIdx.x * NM + k] = v;
+  for (int e = threadIdx.x; e < NM; e += 256) {
+    double v;
+    if (e < NC) {
+      v = col[0][e];
+    } else {
+      const int *x = monos + 3 * (e - NC);
+      v = 0.0;
+      if (x[0]) v += x[0] * col[1][Multi<P>::index(x[0] - 1, x[1], x[2])];
+      if (x[1]) v += x[1] * col[2][Multi<P>::index(x[0], x[1] - 1, x[2])];
+      if (x[2]) v += x[2] * col[3][Multi<P>::index(x[0], x[1], x[2] - 1)];
+    }
+    if (direct) {
+      fin[e] = v;
+      mom64[(size_t)B * NM + e] = v;
+    } else {
+      part[(size_t)blockIdx.x * NM + e] = v;
+    }
+  }
+  if (direct) {
+    __syncthreads();
+    harmonic_words<P>(B, fin, ho);
   }
 }
 
-// mom[B] = sum of the partial moments of B's slices, in slice order
-// (boxes with fewer than min_tasks tasks are skipped: not this pass's, or
-// written by their single task)
-__global__ void k_mom_reduce(int nbox, int ncoef2, const int *__restrict__ first,
-                             const int *__restrict__ count, const double *__restrict__ part,
-                             double *__restrict__ mom, int min_tasks) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= nbox * ncoef2) return;
-  const int B = e / ncoef2, k = e % ncoef2;
-  const int t0 = first[B], nt = count[B];
+// mom[B] = sum of the partial moments of B's slices, in slice order, and the
+// box's harmonic words (boxes with fewer than min_tasks tasks are skipped: not
+// this pass's, or written by their single task)
+template <int P>
+__global__ __launch_bounds__(128) void k_mom_reduce(const int *__restrict__ first,
+                                                    const int *__restrict__ count,
+                                                    const double *__restrict__ part,
+                                                    double *__restrict__ mom, int min_tasks,
+                                                    HarmOut ho) {
+  constexpr int NM = Orders<P>::NM;
+  __shared__ double fin[NM];
+  const int B = blockIdx.x, t0 = first[B], nt = count[B];
   if (nt == 0 || nt < min_tasks) return;
-  double v = 0.0;
-  for (int t = t0; t < t0 + nt; ++t) v += part[(size_t)t * ncoef2 + k];
-  mom[e] = v;
+  for (int k = threadIdx.x; k < NM; k += 128) {
+    double v = 0.0;
+    for (int t = t0; t < t0 + nt; ++t) v += part[(size_t)t * NM + k];
+    fin[k] = v;
+    mom[(size_t)B * NM + k] = v;
+  }
+  __syncthreads();
+  harmonic_words<P>(B, fin, ho);
 }
 
 // Moments of the accepted boxes with children from the leaf moments: with
 // d = c_L - c_B, (h + d)^k = sum_{j <= k} C(k, j) d^(k-j) h^j, and the
 // double-layer moments (n . grad_h) h^k shift with the same coefficients,
 // so m_k(B) = sum over the leaves L under B of sum_{j <= k} C(k, j)
-// d^(k-j) m_j(L), for both moment sets.  One wave per task (a run of at
-// most kShiftLeaves of a box's leaves): the moments of all the run's
-// leaves and the monomials of their d are staged in LDS with every load
-// issued together, then each lane owns coefficients k and walks its terms
-// (j, k - j, C(k, j)) from a table, leaf by leaf in order.
-constexpr int kShiftThreads = 64;
+// d^(k-j) m_j(L), for both moment sets.  One block of eight waves per task (a
+// run of at most kShiftLeaves of a box's leaves, sixteen to a round, two to a
+// wave): the moments of a round's leaves, the monomials of their d and the
+// term table (j, k - j, C(k, j) in one word) are staged in LDS, then each lane
+// owns coefficients k and walks its terms.  LDS bound (24 bytes per lane, term
+// and leaf, 2.6 us per round at P 5) and latency bound below some 500 boxes;
+// one wave with sixteen leaves and the table in global memory took 76 us on
+// 144500 panels at P 5 and 40 us on 28880 at P 4.
+constexpr int kShiftRound = 16, kShiftWaves = 8;
 
 template <int P>
-__global__ __launch_bounds__(kShiftThreads) void k_shift_tasks(
+__global__ __launch_bounds__(64 * kShiftWaves) void k_shift_tasks(
     const int *__restrict__ tasks, const int *__restrict__ leaves,
     const double *__restrict__ center, const int *__restrict__ monos,
-    const int *__restrict__ toff, const int *__restrict__ tjq,
-    const double *__restrict__ tc, double *__restrict__ mom,
-    const int *__restrict__ count, double *__restrict__ part) {
+    const int *__restrict__ toff, const unsigned *__restrict__ terms,
+    double *__restrict__ mom, const int *__restrict__ count, double *__restrict__ part,
+    HarmOut ho) {
   // single-layer moments k < NC, double-layer k < NK (the terms of a
   // coefficient reach only coefficients of lower or equal degree, so one
   // table of degree P + 1 serves both)
   constexpr int NC = Orders<P>::NV, NK = Orders<P>::NK, NM = Orders<P>::NM;
-  constexpr int R = (NK + kShiftThreads - 1) / kShiftThreads;
-  __shared__ double sm[kShiftLeaves * NM], sd[kShiftLeaves * NK];
-  __shared__ int sL[kShiftLeaves];
+  constexpr int R = (NK + 63) / 64, TH = 64 * kShiftWaves, LW = kShiftRound / kShiftWaves;
+  constexpr int NT = (P + 2) * (P + 3) * (P + 4) * (P + 5) * (P + 6) * (P + 7) / 720;
+  __shared__ __align__(16) double sm[kShiftRound][NK][2];  // (mV, mK); mV 0 beyond NC
+  __shared__ double sd[kShiftRound][NK];
+  __shared__ double pw[kShiftRound][3][P + 2];
+  __shared__ unsigned st[NT];
+  __shared__ int sL[kShiftRound];
+  static_assert(sizeof(sm) >= sizeof(double) * kShiftWaves * NM, "the reduction reuses sm");
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
   const int B = tasks[3 * blockIdx.x];
-  const int la = tasks[3 * blockIdx.x + 1];
-  const int nl = tasks[3 * blockIdx.x + 2] - la;
-  const double cB[3] = {center[3 * B], center[3 * B + 1], center[3 * B + 2]};
-  __shared__ double sdl[kShiftLeaves * 3];
-  if (threadIdx.x < nl) {
-    const int L = leaves[la + threadIdx.x];
-    sL[threadIdx.x] = L;
-    for (int c = 0; c < 3; ++c) sdl[3 * threadIdx.x + c] = center[3 * L + c] - cB[c];
-  }
-  __syncthreads();
-  // moments with eight loads in flight per lane
-  for (int e0 = threadIdx.x; e0 < nl * NM; e0 += 8 * kShiftThreads) {
-    double v[8];
+  const int l0 = tasks[3 * blockIdx.x + 1], l1 = tasks[3 * blockIdx.x + 2];
+  for (int e = threadIdx.x; e < NT; e += TH) st[e] = terms[e];
+  double aV[R], aK[R];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = e0 + u * kShiftThreads;
-      if (e < nl * NM) v[u] = mom[(size_t)sL[e / NM] * NM + e % NM];
+  for (int r = 0; r < R; ++r) aV[r] = aK[r] = 0.0;
+  for (int lr = l0; lr < l1; lr += kShiftRound) {
+    const int nl = min(kShiftRound, l1 - lr);
+    __syncthreads();
+    if ((int)threadIdx.x < nl) sL[threadIdx.x] = leaves[lr + threadIdx.x];
+    __syncthreads();
+    for (int e = threadIdx.x; e < nl * NK; e += TH) {
+      const int l = e / NK, k = e % NK;
+      const double *m = mom + (size_t)sL[l] * NM;
+      sm[l][k][0] = k < NC ? m[k] : 0.0;
+      sm[l][k][1] = m[NC + k];
     }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = e0 + u * kShiftThreads;
-      if (e < nl * NM) sm[e] = v[u];
+    if ((int)threadIdx.x < nl * 3) {
+      const int l = threadIdx.x / 3, d = threadIdx.x % 3;
+      const double x = center[3 * sL[l] + d] - center[3 * B + d];
+      double v = 1.0;
+      for (int u = 0; u < P + 2; ++u) {
+        pw[l][d][u] = v;
+        v *= x;
+      }
     }
-  }
-  for (int e = threadIdx.x; e < nl * NK; e += kShiftThreads) {
-    const int l = e / NK, k = e % NK;
-    double v = 1.0;
-    for (int c = 0; c < 3; ++c)
-      for (int u = 0; u < monos[3 * k + c]; ++u) v *= sdl[3 * l + c];
-    sd[e] = v;
-  }
-  __syncthreads();
+    __syncthreads();
+    for (int e = threadIdx.x; e < nl * NK; e += TH) {
+      const int l = e / NK, k = e % NK;
+      sd[l][k] = pw[l][0][monos[3 * k]] * pw[l][1][monos[3 * k + 1]] * pw[l][2][monos[3 * k + 2]];
+    }
+    __syncthreads();
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int k = threadIdx.x + r * kShiftThreads;
-    if (k >= NK) continue;
-    const bool hasV = k < NC;
-    const int t0 = toff[k], t1 = toff[k + 1];
-    // terms outer (one table read each), leaves inner; per-leaf sums in
-    // registers are added in leaf order at the end
-    double v[kShiftLeaves], w[kShiftLeaves];
+    for (int r = 0; r < R; ++r) {
+      const int k = lane + 64 * r;
+      if (k >= NK) continue;
+      const int t0 = toff[k], t1 = toff[k + 1];
+      for (int t = t0; t < t1; ++t) {
+        const unsigned w = st[t];
+        const int j = w & 255, q = (w >> 8) & 255;
+        const double ct = (double)(w >> 16);
 #pragma unroll
-    for (int l = 0; l < kShiftLeaves; ++l) v[l] = w[l] = 0.0;
-    for (int t = t0; t < t1; ++t) {
-      const int j = tjq[2 * t], q = tjq[2 * t + 1];
-      const double ct = tc[t];
-#pragma unroll
-      for (int l = 0; l < kShiftLeaves; ++l) {
-        if (l < nl) {
-          const double c = ct * sd[l * NK + q];
-          if (hasV) v[l] += c * sm[l * NM + j];
-          w[l] += c * sm[l * NM + NC + j];
+        for (int u = 0; u < LW; ++u) {
+          const int l = LW * wave + u;
+          if (l < nl) {
+            const double c = ct * sd[l][q];
+            aV[r] += c * sm[l][j][0];
+            aK[r] += c * sm[l][j][1];
+          }
         }
       }
     }
-    double aV = 0.0, aK = 0.0;
+  }
+  __syncthreads();
+  double *red = &sm[0][0][0];
 #pragma unroll
-    for (int l = 0; l < kShiftLeaves; ++l) {
-      if (l < nl) {
-        aV += v[l];
-        aK += w[l];
-      }
-    }
-    if (count[B] == 1) {  // the box's only task: its moments
-      if (hasV) mom[(size_t)B * NM + k] = aV;
-      mom[(size_t)B * NM + NC + k] = aK;
-    } else {
-      if (hasV) part[(size_t)blockIdx.x * NM + k] = aV;
-      part[(size_t)blockIdx.x * NM + NC + k] = aK;
-    }
+  for (int r = 0; r < R; ++r) {
+    const int k = lane + 64 * r;
+    if (k >= NK) continue;
+    if (k < NC) red[wave * NM + k] = aV[r];
+    red[wave * NM + NC + k] = aK[r];
+  }
+  __syncthreads();
+  const bool last = count[B] == 1;  // the box's only task: its moments
+  for (int k = threadIdx.x; k < NM; k += TH) {
+    double v = red[k];
+    for (int w = 1; w < kShiftWaves; ++w) v += red[w * NM + k];
+    red[k] = v;
+    if (last) mom[(size_t)B * NM + k] = v;
+    else part[(size_t)blockIdx.x * NM + k] = v;
+  }
+  if (last) {
+    __syncthreads();
+    harmonic_words<P>(B, red, ho);
   }
 }
 
@@ -475,39 +517,6 @@ template <> __device__ inline float expneg_t<float>(float nk, float, float r) {
 }
 template <> __device__ inline double expneg_t<double>(double, double kappa, double r) {
   return exp_fp64(-kappa * r);
-}
-
-// Harmonic words of every box from its Cartesian moments, merged into the two
-// rows of the product: Laplace mK - mV, Yukawa eps mV - mK.  One wave per box,
-// a lane per harmonic (at most 64), its terms (k, C for Laplace, C for Yukawa)
-// from a table; of the order of ten terms each, so latency bound.
-template <class T, int P>
-__global__ __launch_bounds__(64) void k_harmonics(const double *__restrict__ mom,
-                                                  const int *__restrict__ hoff,
-                                                  const int *__restrict__ hk,
-                                                  const double *__restrict__ hc,
-                                                  const int *__restrict__ hpos,
-                                                  double eps_ratio, T *__restrict__ out) {
-  constexpr int NC = Orders<P>::NV, NM = Orders<P>::NM, NS = Orders<P>::NS;
-  constexpr int NH = Harm<P + 1>::NH;
-  static_assert(NH <= 64, "a lane per harmonic");
-  __shared__ double sm[NM];
-  const double *m = mom + (size_t)blockIdx.x * NM;
-  for (int e = threadIdx.x; e < NM; e += 64) sm[e] = m[e];
-  __syncthreads();
-  T *o = out + (size_t)blockIdx.x * NS;
-  if (threadIdx.x < NH) {
-    double a = 0.0, b = 0.0;
-    for (int t = hoff[threadIdx.x]; t < hoff[threadIdx.x + 1]; ++t) {
-      const int k = hk[t];
-      const double mv = k < NC ? sm[k] : 0.0, mk = sm[NC + k];
-      a += hc[2 * t] * (mk - mv);
-      b += hc[2 * t + 1] * (eps_ratio * mv - mk);
-    }
-    const int pos = hpos[threadIdx.x];
-    o[pos] = (T)a;
-    o[pos + 1] = (T)b;
-  }
 }
 
 // M2P.  A task is a target leaf against a run of its accepted boxes, one wave,
@@ -666,10 +675,8 @@ __global__ __launch_bounds__(kFinBlock) void k_finish_slots(
 }
 
 template <class T, int P>
-void launch_m2p_p(Tree &t, hipStream_t s, T *words, const T *tgt, int N, T kappa, T nk,
-                  double eps_ratio, double *part) {
-  hipLaunchKernelGGL((k_harmonics<T, P>), dim3(t.nbox), dim3(64), 0, s, t.d_mom64.p,
-                     t.d_hoff.p, t.d_hk.p, t.d_hc.p, t.d_hpos.p, eps_ratio, words);
+void launch_m2p_p(Tree &t, hipStream_t s, const T *words, const T *tgt, int N, T kappa, T nk,
+                  double *part) {
   const int nb = ((t.n_m2p_tasks + 7) / 8) * 8;
   hipLaunchKernelGGL((k_m2p_tasks<T, P>), dim3(nb), dim3(64), 0, s, t.n_m2p_tasks,
                      t.d_m2p_task.p, t.d_m2p_slot.p, t.d_m2p_box.p, t.d_center.p, words,
@@ -677,25 +684,26 @@ void launch_m2p_p(Tree &t, hipStream_t s, T *words, const T *tgt, int N, T kappa
 }
 
 template <int P>
-void launch_moments_p(Tree &t, hipStream_t s, int nf, const double *src64) {
-  constexpr int NM = Orders<P>::NM;
+void launch_moments_p(Tree &t, hipStream_t s, int nf, const double *src64, bool fp64,
+                      double eps_ratio) {
   if (t.n_mom_tasks == 0) return;
+  const HarmOut ho{t.d_hoff.p, t.d_hk.p, t.d_hpos.p, t.d_hc.p, eps_ratio,
+                   fp64 ? t.d_harm64.p : nullptr, fp64 ? nullptr : t.d_harm32.p};
   const int direct = t.n_mom_tasks == t.nleaf;  // no leaf split into slices
-  hipLaunchKernelGGL(k_p2m_tasks<P>, dim3(t.n_mom_tasks), dim3(kP2MThreads), 0, s, nf,
-                     t.d_mom_task.p, t.d_center.p, src64, t.d_mom_part.p, direct, t.d_mom64.p);
-  const int n = t.nbox * NM;
+  hipLaunchKernelGGL(k_p2m_tasks<P>, dim3(t.n_mom_tasks), dim3(256), 0, s, nf,
+                     t.d_mom_task.p, t.d_center.p, src64, t.d_monos.p, t.d_mom_part.p, direct,
+                     t.d_mom64.p, ho);
   if (!direct)
-    hipLaunchKernelGGL(k_mom_reduce, dim3((n + 255) / 256), dim3(256), 0, s, t.nbox, NM,
-                       t.d_mom_first.p, t.d_mom_count.p, t.d_mom_part.p, t.d_mom64.p, 1);
+    hipLaunchKernelGGL(k_mom_reduce<P>, dim3(t.nbox), dim3(128), 0, s, t.d_mom_first.p,
+                       t.d_mom_count.p, t.d_mom_part.p, t.d_mom64.p, 1, ho);
   if (t.n_shift_tasks > 0) {
-    hipLaunchKernelGGL(k_shift_tasks<P>, dim3(t.n_shift_tasks), dim3(kShiftThreads), 0, s,
+    hipLaunchKernelGGL(k_shift_tasks<P>, dim3(t.n_shift_tasks), dim3(64 * kShiftWaves), 0, s,
                        t.d_shift_task.p, t.d_leaves.p, t.d_center.p, t.d_monos.p,
-                       t.d_shift_toff.p, t.d_shift_tjq.p, t.d_shift_tc.p, t.d_mom64.p,
-                       t.d_shift_count.p, t.d_shift_part.p);
+                       t.d_shift_toff.p, t.d_shift_term.p, t.d_mom64.p, t.d_shift_count.p,
+                       t.d_shift_part.p, ho);
     if (t.shift_multi)
-      hipLaunchKernelGGL(k_mom_reduce, dim3((n + 255) / 256), dim3(256), 0, s, t.nbox, NM,
-                         t.d_shift_first.p, t.d_shift_count.p, t.d_shift_part.p, t.d_mom64.p,
-                         2);
+      hipLaunchKernelGGL(k_mom_reduce<P>, dim3(t.nbox), dim3(128), 0, s, t.d_shift_first.p,
+                         t.d_shift_count.p, t.d_shift_part.p, t.d_mom64.p, 2, ho);
   }
 }
 
@@ -711,16 +719,18 @@ void launch_moments_p(Tree &t, hipStream_t s, int nf, const double *src64) {
   }
 
 template <class T>
-void launch_m2p(Tree &t, hipStream_t s, T *words, const T *tgt, int N, T kappa, T nk,
-                double eps_ratio, double *part) {
-#define PBMP_CALL(P) launch_m2p_p<T, P>(t, s, words, tgt, N, kappa, nk, eps_ratio, part)
+void launch_m2p(Tree &t, hipStream_t s, const T *words, const T *tgt, int N, T kappa, T nk,
+                double *part) {
+#define PBMP_CALL(P) launch_m2p_p<T, P>(t, s, words, tgt, N, kappa, nk, part)
   PBMP_BY_ORDER(PBMP_CALL)
 #undef PBMP_CALL
 }
 
-// Cartesian moments of every leaf and accepted box, FP64
-void launch_moments(Tree &t, hipStream_t s, int nf, const double *src64) {
-#define PBMP_CALL(P) launch_moments_p<P>(t, s, nf, src64)
+// Cartesian moments of every leaf and accepted box, FP64, and their harmonic
+// words in the product's precision
+void launch_moments(Tree &t, hipStream_t s, int nf, const double *src64, bool fp64,
+                    double eps_ratio) {
+#define PBMP_CALL(P) launch_moments_p<P>(t, s, nf, src64, fp64, eps_ratio)
   PBMP_BY_ORDER(PBMP_CALL)
 #undef PBMP_CALL
 }
@@ -1498,22 +1508,23 @@ void tree_upload_exponents(Tree &t, hipStream_t s) {
     return c;
   };
   const int nc = (int)ex.size() / 3;
-  std::vector<int> off(nc + 1, 0), jq;
-  std::vector<double> c;
+  std::vector<int> off(nc + 1, 0);
+  std::vector<unsigned> term;  // j | (k - j) << 8 | C(k, j) << 16 (at most 119, 119, 35)
   for (int k = 0; k < nc; ++k) {
     const int kx = ex[3 * k], ky = ex[3 * k + 1], kz = ex[3 * k + 2];
     for (int jx = 0; jx <= kx; ++jx)
       for (int jy = 0; jy <= ky; ++jy)
         for (int jz = 0; jz <= kz; ++jz) {
-          jq.push_back(index(jx, jy, jz));
-          jq.push_back(index(kx - jx, ky - jy, kz - jz));
-          c.push_back(binom(kx, jx) * binom(ky, jy) * binom(kz, jz));
+          const double c = binom(kx, jx) * binom(ky, jy) * binom(kz, jz);
+          term.push_back((unsigned)index(jx, jy, jz) |
+                         (unsigned)index(kx - jx, ky - jy, kz - jz) << 8 |
+                         (unsigned)std::lround(c) << 16);
         }
-    off[k + 1] = (int)c.size();
+    off[k + 1] = (int)term.size();
   }
   t.d_shift_toff.upload(off.data(), off.size(), s);
-  t.d_shift_tjq.upload(jq.data(), jq.size(), s);
-  t.d_shift_tc.upload(c.data(), c.size(), s);
+  t.d_shift_term.upload(term.data(), term.size(), s);
+  PBMP_HIP(hipStreamSynchronize(s));
 }
 
 // Tables of the harmonic form of order P (harmonic.hpp) for degrees up to
@@ -1690,7 +1701,7 @@ void tree_apply(Tree &t, hipStream_t s, bool fp64, int nf, int N, const double *
                 const double *src64, const float *src32, const float *tgt32,
                 double kappa, double eps_ratio, double *part, KernelClock &clk, bool floor_r2) {
   hipEvent_t e0 = clk.on ? clk.begin(s) : nullptr;
-  launch_moments(t, s, nf, src64);
+  launch_moments(t, s, nf, src64, fp64, eps_ratio);
   PBMP_HIP(hipGetLastError());
   if (clk.on) clk.end(s, e0, KernelClock::P2M, 0.0);
 
@@ -1719,9 +1730,9 @@ void tree_apply(Tree &t, hipStream_t s, bool fp64, int nf, int N, const double *
   if (t.n_m2p_tasks > 0 && t.n_m2p_entries > 0) {
     e0 = clk.on ? clk.begin(s) : nullptr;
     if (fp64)
-      launch_m2p<double>(t, s, t.d_harm64.p, geo, N, kappa, 0.0, eps_ratio, part);
+      launch_m2p<double>(t, s, t.d_harm64.p, geo, N, kappa, 0.0, part);
     else
-      launch_m2p<float>(t, s, t.d_harm32.p, tgt32, N, (float)kappa, nk32, eps_ratio, part);
+      launch_m2p<float>(t, s, t.d_harm32.p, tgt32, N, (float)kappa, nk32, part);
     PBMP_HIP(hipGetLastError());
     if (clk.on) clk.end(s, e0, KernelClock::M2P, t.m2p_pairs);
   }

@@ -757,11 +757,11 @@ void Tree::build_device(int N, int nf, const uint64_t *key, const double *geo,
     d_mom_count.alloc(nbox);
     d_mom_first.alloc(nbox);
     hipLaunchKernelGGL(k_mom_counts, grid_for(nbox), dim3(256), 0, s, nbox, view(),
-                       mom_chunk_panels(prm.order), d_mom_count.p);
+                       kMomChunkPanels, d_mom_count.p);
     n_mom_tasks = exclusive_scan_total(s, d_mom_count.p, d_mom_first.p, nbox, tmp);
     d_mom_task.alloc(3 * (size_t)std::max(1, n_mom_tasks));
     hipLaunchKernelGGL(k_mom_fill, grid_for(nbox), dim3(256), 0, s, nbox, d_mom_first.p,
-                       d_mom_count.p, view(), mom_chunk_panels(prm.order), d_mom_task.p);
+                       d_mom_count.p, view(), kMomChunkPanels, d_mom_task.p);
     d_mom_part.alloc((size_t)std::max(1, n_mom_tasks) * nmom);
     // shifts of the leaf moments to the accepted boxes above them
     Dbuf<int> ls, range;

@@ -63,17 +63,13 @@ constexpr int kP2PTaskWork = PBMP_P2P_WORK;
 // cost more than the shorter tasks gain (28880 panels: 59, 56 and 69 us for
 // both kernels at 512, 1024 and 256)
 inline int m2p_task_work(int N) { return N / 48 < 1024 ? 1024 : N / 48 > 4096 ? 4096 : N / 48; }
-// panels per moment task
-// Panels per moment task: one wave per task, so a slice bounds the nodes a
-// lane walks; higher orders carry a longer wave reduction per task and
-// take longer slices (measured fastest: 512 up to P = 4, 1024 above).
-#ifdef PBMP_MOM_CHUNK
-inline int mom_chunk_panels(int) { return PBMP_MOM_CHUNK; }
-#else
-inline int mom_chunk_panels(int order) { return order <= 4 ? 512 : 1024; }
-#endif
-// leaves per shift task (moments of the boxes above the leaves)
-constexpr int kShiftLeaves = 16;
+// Panels per moment task: longer leaves are cut into slices, which cost a
+// reduction launch.
+constexpr int kMomChunkPanels = 1024;
+// leaves per shift task (moments of the boxes above the leaves): the boxes that
+// surfaces of leaf_panels ~ 300 accept hold up to 64, so their moments come
+// from one task without a second pass
+constexpr int kShiftLeaves = 64;
 // target panels per M2P^T task (adjoint product)
 constexpr int kM2PTChunkTargets = 512;
 
@@ -133,8 +129,8 @@ class Tree {
   bool shift_multi = false;  // some box has several shift tasks
   Dbuf<int> d_shift_task, d_shift_first, d_shift_count;
   Dbuf<double> d_shift_part;  // [n_shift_tasks][nmom]
-  Dbuf<int> d_shift_toff, d_shift_tjq;  // per coefficient k: terms [toff[k], toff[k+1]), (j, k-j)
-  Dbuf<double> d_shift_tc;              // C(k, j) of each term
+  Dbuf<int> d_shift_toff;       // per coefficient k: terms [toff[k], toff[k+1])
+  Dbuf<unsigned> d_shift_term;  // j | (k - j) << 8 | C(k, j) << 16 of each term
   Dbuf<double> d_mom64;   // [nbox][nmom]
   // harmonic form (harmonic.hpp): words per box, and the tables of the maps
   // from the Cartesian moments and (transposed) to the Cartesian locals
