@@ -46,8 +46,6 @@ void launch_readout_grad(hipStream_t s, int N, int M, const double *src64, const
 void launch_rhs_grad(hipStream_t s, int N, int M, const double *geo, const double *sigma,
                      const double *xyz, const double *q, const double *p, const double *Q,
                      double *g_r, double *g_q, double *g_d, double *g_Q);
-void launch_precond_T(hipStream_t s, int N, const double *diag, double eps_ratio,
-                      const double *u, double *z);
 void launch_scale_sites(hipStream_t s, int M, const double *alpha, const double *lam,
                         double *w);
 void launch_adj_update(hipStream_t s, int M, double omega, const double *E, const double *F,
@@ -88,7 +86,7 @@ int Runtime::backward(double dGbar, double *g_xyz, double *g_q, double *g_d, dou
   const int M = M_, N = N_;
   const double c = dGbar * coulomb_kcal() * 0.5;
   const double ta = o.thole_a, eps = o.eps_in;
-  Dbuf<double> Wc, Wp, Jmu, wv, wd, E, F, sig, rhs, red;
+  Dbuf<double> Wc, Wp, Jmu, wv, wd, E, F, sig, rhs;
   // multipliers, kept on the context: with warm_start a backward starts
   // from the previous backward's (same mesh and site count), rescaled to
   // this dG_bar
@@ -108,7 +106,6 @@ int Runtime::backward(double dGbar, double *g_xyz, double *g_q, double *g_d, dou
   sig.alloc(N);
   lx.alloc(2 * (size_t)N);
   rhs.alloc(2 * (size_t)N);
-  red.alloc(2);
   if (warm && dGbar != adj_bar_) {
     const double f = dGbar / adj_bar_;
     launch_scale(s_, 3 * M, f, lv.p, lv.p);
@@ -142,10 +139,9 @@ int Runtime::backward(double dGbar, double *g_xyz, double *g_q, double *g_d, dou
       }
       launch_induced(s_, false, M, sxyz_.p, w.p, salpha_.p, ta, eps, E.p);
       launch_adj_update(s_, M, o.scf_omega, E.p, dissolved ? F.p : nullptr, Jmu.p,
-                        dissolved ? -1.0 : 1.0, lam.p, red.p);
-      double h[2];
-      PBMP_HIP(hipMemcpyAsync(h, red.p, sizeof(h), hipMemcpyDeviceToHost, s_));
+                        dissolved ? -1.0 : 1.0, lam.p, hloop_);
       sync();
+      const double h[2] = {hloop_[0], hloop_[1]};
       if (o.verbose)
         std::fprintf(stderr, "pbmp backward: %s iteration %d gmres %d change %.3e %.1f s\n",
                      dissolved ? "dissolved" : "vacuum", it, gi,

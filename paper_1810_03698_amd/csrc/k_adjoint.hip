@@ -420,17 +420,6 @@ __global__ __launch_bounds__(256) void k_rhs_grad(int N, const double *__restric
   }
 }
 
-// z = M^{-T} u for the transposed 2x2 panel blocks [[1/2, 1/2],[-a, e b]]
-__global__ void k_precond_T(int N, const double *__restrict__ diag, double e,
-                            const double *__restrict__ u, double *__restrict__ z) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N) return;
-  const double a = diag[i], b = diag[N + i];
-  const double det = 0.5 * (e * b + a);
-  z[i] = (e * b * u[i] - 0.5 * u[N + i]) / det;
-  z[N + i] = (a * u[i] + 0.5 * u[N + i]) / det;
-}
-
 __global__ void k_scale_sites(int M, const double *__restrict__ alpha,
                               const double *__restrict__ lam, double *__restrict__ w) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -556,13 +545,6 @@ void launch_rhs_grad(hipStream_t s, int N, int M, const double *geo, const doubl
                      double *g_r, double *g_q, double *g_d, double *g_Q) {
   hipLaunchKernelGGL(k_rhs_grad, dim3(M), dim3(256), 0, s, N, geo, sigma, xyz, q, p, Q, g_r,
                      g_q, g_d, g_Q);
-  PBMP_HIP(hipGetLastError());
-}
-
-void launch_precond_T(hipStream_t s, int N, const double *diag, double eps_ratio,
-                      const double *u, double *z) {
-  hipLaunchKernelGGL(k_precond_T, dim3((N + 255) / 256), dim3(256), 0, s, N, diag, eps_ratio, u,
-                     z);
   PBMP_HIP(hipGetLastError());
 }
 

@@ -260,14 +260,14 @@ __global__ __launch_bounds__(128) void k_mom_reduce(const int *__restrict__ firs
 // double-layer moments (n . grad_h) h^k shift with the same coefficients,
 // so m_k(B) = sum over the leaves L under B of sum_{j <= k} C(k, j)
 // d^(k-j) m_j(L), for both moment sets.  One block of eight waves per task (a
-// run of at most kShiftLeaves of a box's leaves, sixteen to a round, two to a
-// wave): the moments of a round's leaves, the monomials of their d and the
+// run of at most kShiftLeaves of a box's leaves, two to a wave): the moments of
+// the leaves, the monomials of their d and the
 // term table (j, k - j, C(k, j) in one word) are staged in LDS, then each lane
 // owns coefficients k and walks its terms.  LDS bound (24 bytes per lane, term
-// and leaf, 2.6 us per round at P 5) and latency bound below some 500 boxes;
+// and leaf, 2.6 us per block at P 5) and latency bound below some 500 tasks;
 // one wave with sixteen leaves and the table in global memory took 76 us on
-// 144500 panels at P 5 and 40 us on 28880 at P 4.
-constexpr int kShiftRound = 16, kShiftWaves = 8;
+// 144500 panels at P 5 and 40 us on 28880 at P 4, this 18 and 9.
+constexpr int kShiftWaves = 8;
 
 template <int P>
 __global__ __launch_bounds__(64 * kShiftWaves) void k_shift_tasks(
@@ -280,13 +280,13 @@ __global__ __launch_bounds__(64 * kShiftWaves) void k_shift_tasks(
   // coefficient reach only coefficients of lower or equal degree, so one
   // table of degree P + 1 serves both)
   constexpr int NC = Orders<P>::NV, NK = Orders<P>::NK, NM = Orders<P>::NM;
-  constexpr int R = (NK + 63) / 64, TH = 64 * kShiftWaves, LW = kShiftRound / kShiftWaves;
+  constexpr int R = (NK + 63) / 64, TH = 64 * kShiftWaves, LW = kShiftLeaves / kShiftWaves;
   constexpr int NT = (P + 2) * (P + 3) * (P + 4) * (P + 5) * (P + 6) * (P + 7) / 720;
-  __shared__ __align__(16) double sm[kShiftRound][NK][2];  // (mV, mK); mV 0 beyond NC
-  __shared__ double sd[kShiftRound][NK];
-  __shared__ double pw[kShiftRound][3][P + 2];
+  __shared__ __align__(16) double sm[kShiftLeaves][NK][2];  // (mV, mK); mV 0 beyond NC
+  __shared__ double sd[kShiftLeaves][NK];
+  __shared__ double pw[kShiftLeaves][3][P + 2];
   __shared__ unsigned st[NT];
-  __shared__ int sL[kShiftRound];
+  __shared__ int sL[kShiftLeaves];
   static_assert(sizeof(sm) >= sizeof(double) * kShiftWaves * NM, "the reduction reuses sm");
   const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
   const int B = tasks[3 * blockIdx.x];
@@ -295,49 +295,46 @@ __global__ __launch_bounds__(64 * kShiftWaves) void k_shift_tasks(
   double aV[R], aK[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) aV[r] = aK[r] = 0.0;
-  for (int lr = l0; lr < l1; lr += kShiftRound) {
-    const int nl = min(kShiftRound, l1 - lr);
-    __syncthreads();
-    if ((int)threadIdx.x < nl) sL[threadIdx.x] = leaves[lr + threadIdx.x];
-    __syncthreads();
-    for (int e = threadIdx.x; e < nl * NK; e += TH) {
-      const int l = e / NK, k = e % NK;
-      const double *m = mom + (size_t)sL[l] * NM;
-      sm[l][k][0] = k < NC ? m[k] : 0.0;
-      sm[l][k][1] = m[NC + k];
+  const int nl = l1 - l0;
+  if ((int)threadIdx.x < nl) sL[threadIdx.x] = leaves[l0 + threadIdx.x];
+  __syncthreads();
+  for (int e = threadIdx.x; e < nl * NK; e += TH) {
+    const int l = e / NK, k = e % NK;
+    const double *m = mom + (size_t)sL[l] * NM;
+    sm[l][k][0] = k < NC ? m[k] : 0.0;
+    sm[l][k][1] = m[NC + k];
+  }
+  if ((int)threadIdx.x < nl * 3) {
+    const int l = threadIdx.x / 3, d = threadIdx.x % 3;
+    const double x = center[3 * sL[l] + d] - center[3 * B + d];
+    double v = 1.0;
+    for (int u = 0; u < P + 2; ++u) {
+      pw[l][d][u] = v;
+      v *= x;
     }
-    if ((int)threadIdx.x < nl * 3) {
-      const int l = threadIdx.x / 3, d = threadIdx.x % 3;
-      const double x = center[3 * sL[l] + d] - center[3 * B + d];
-      double v = 1.0;
-      for (int u = 0; u < P + 2; ++u) {
-        pw[l][d][u] = v;
-        v *= x;
-      }
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < nl * NK; e += TH) {
-      const int l = e / NK, k = e % NK;
-      sd[l][k] = pw[l][0][monos[3 * k]] * pw[l][1][monos[3 * k + 1]] * pw[l][2][monos[3 * k + 2]];
-    }
-    __syncthreads();
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < nl * NK; e += TH) {
+    const int l = e / NK, k = e % NK;
+    sd[l][k] = pw[l][0][monos[3 * k]] * pw[l][1][monos[3 * k + 1]] * pw[l][2][monos[3 * k + 2]];
+  }
+  __syncthreads();
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int k = lane + 64 * r;
-      if (k >= NK) continue;
-      const int t0 = toff[k], t1 = toff[k + 1];
-      for (int t = t0; t < t1; ++t) {
-        const unsigned w = st[t];
-        const int j = w & 255, q = (w >> 8) & 255;
-        const double ct = (double)(w >> 16);
+  for (int r = 0; r < R; ++r) {
+    const int k = lane + 64 * r;
+    if (k >= NK) continue;
+    const int t0 = toff[k], t1 = toff[k + 1];
+    for (int t = t0; t < t1; ++t) {
+      const unsigned w = st[t];
+      const int j = w & 255, q = (w >> 8) & 255;
+      const double ct = (double)(w >> 16);
 #pragma unroll
-        for (int u = 0; u < LW; ++u) {
-          const int l = LW * wave + u;
-          if (l < nl) {
-            const double c = ct * sd[l][q];
-            aV[r] += c * sm[l][j][0];
-            aK[r] += c * sm[l][j][1];
-          }
+      for (int u = 0; u < LW; ++u) {
+        const int l = LW * wave + u;
+        if (l < nl) {
+          const double c = ct * sd[l][q];
+          aV[r] += c * sm[l][j][0];
+          aK[r] += c * sm[l][j][1];
         }
       }
     }

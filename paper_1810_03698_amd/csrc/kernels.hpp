@@ -132,19 +132,25 @@ void launch_mdot(hipStream_t s, int n, int nv, const double *V, size_t ld,
 void launch_gemv_sub(hipStream_t s, int n, int nv, const double *V, size_t ld,
                      const double *h, double *w);
 // Arnoldi-step forms without the final reduction launch: the block sums of
-// launch_mdot_partial (returns their count per vector) are added by every
-// block of the consumer in a fixed order; block 0 stores the totals to hout.
-// gemv_sub_p: w -= V h (nv <= 256); scale_inv_sqrt_p: v = w / |w| (zero
-// stays zero).
+// launch_mdot_partial (returns their count per vector; krylov_partials(n, m)
+// doubles hold those of m + 1 vectors) are added by every block of the consumer
+// in a fixed order; block 0 stores the totals to hout, which may be pinned host
+// memory.  gemv_sub_p: w -= V h (nv <= 256) and, where norm is not null, the
+// blocks' shares of |w|^2 (returns their count, n / 256 rounded up).
+// next_vector: v = w / |w| (zero stays zero) from those shares and, mode 1,
+// z = M^{-1} v with the far-field strengths of z packed into src64/src32, mode
+// 2, z = M^{-T} v, mode 0 nothing more.
+size_t krylov_partials(int n, int m);
 int launch_mdot_partial(hipStream_t s, int n, int nv, const double *V, size_t ld,
                         const double *w, double *partial);
-void launch_gemv_sub_p(hipStream_t s, int n, int nv, const double *V, size_t ld, int nblk,
-                       const double *partial, double *hout, double *w);
-void launch_scale_inv_sqrt_p(hipStream_t s, int n, int nblk, const double *partial,
-                             double *hout, const double *w, double *v);
-// v = w * (1/ *nrm) with nrm = sqrt(*nrm2); zero when *nrm2 is zero
-void launch_scale_inv_sqrt(hipStream_t s, int n, const double *w,
-                           const double *nrm2, double *v);
+int launch_gemv_sub_p(hipStream_t s, int n, int nv, const double *V, size_t ld, int nblk,
+                      const double *partial, double *hout, double *w, double *norm);
+void launch_next_vector(hipStream_t s, int mode, int n, int nb, const double *norm, double *hout,
+                        const double *w, double *v, int nf, const double *diag, double eps_ratio,
+                        const double *geo, double *z, double *src64, float *src32);
+// z = M^{-T} u
+void launch_precond_T(hipStream_t s, int N, const double *diag, double eps_ratio,
+                      const double *u, double *z);
 void launch_axpy(hipStream_t s, int n, double a, const double *x, double *y);
 void launch_xmy(hipStream_t s, int n, const double *b, const double *ax,
                 double *r);  // r = b - ax

@@ -252,8 +252,6 @@ void Runtime::set_options(const pbmp_options &n) {
     alloc_work();
   } else if (restart_changed && N_ > 0) {
     alloc_work();
-    if (outer_)
-      partial_.reserve((size_t)(o.gmres_restart + 2) * ((sX_.n + 4095) / 4096 + 1));
   }
 }
 
@@ -265,6 +263,7 @@ Runtime::~Runtime() {
   if (s_) (void)hipStreamSynchronize(s_);
   for (hipEvent_t e : kev_) (void)hipEventDestroy(e);
   if (hpin_) (void)hipHostFree(hpin_);
+  if (hloop_) (void)hipHostFree(hloop_);
   if (own_stream_ && s_) (void)hipStreamDestroy(s_);
 }
 
@@ -474,8 +473,8 @@ void Runtime::alloc_work() {
   b_.alloc(n);
   x_.alloc(n);
   ybuf_.alloc(m + 2);
-  hbuf_.alloc(3 * (m + 2));
-  partial_.alloc((size_t)(m + 2) * ((n + 4095) / 4096 + 1));
+  partial_.alloc(krylov_partials(n, m));
+  norm_.alloc((size_t)n / 256 + 1);
   tmp_.alloc(n);
   io_a_.alloc(n > 0 ? n : 1);
   io_b_.alloc(n > 0 ? n : 1);
@@ -551,7 +550,8 @@ void Runtime::set_sites(int64_t m, const double *xyz, const double *q,
   vac_ind_.alloc(10 * (size_t)M);
   p_.alloc(3 * (size_t)M);
   f_.alloc(N_);
-  dmu2_.alloc(1);
+  if (!hloop_)
+    PBMP_HIP(hipHostMalloc((void **)&hloop_, 2 * sizeof(double), hipHostMallocDefault));
   e_.alloc(10);
   ro_chunks_ = readout_chunks(N_, M);
   rpart_.alloc((size_t)ro_chunks_ * M * 10);
@@ -645,10 +645,11 @@ void Runtime::apply(const double *x, double *y, bool f64, bool packed) {
 // columns.
 void Runtime::krylov_reserve(int n) {
   const int m = o.gmres_restart;
-  partial_.reserve((size_t)(m + 2) * ((n + 4095) / 4096 + 1));
-  hbuf_.reserve(3 * (size_t)(m + 2));
+  partial_.reserve(krylov_partials(n, m));
+  norm_.reserve((size_t)n / 256 + 1);
   ybuf_.reserve((size_t)(m + 2));
-  const size_t need = (size_t)m * 3 * (m + 2);
+  // a column per step, and two scalars of the solve
+  const size_t need = (size_t)m * 3 * (m + 2) + 2;
   if (hpin_n_ < need) {
     if (hpin_) PBMP_HIP(hipHostFree(hpin_));
     hpin_ = nullptr;
@@ -665,7 +666,8 @@ void Runtime::krylov_reserve(int n) {
 
 int Runtime::gmres_core(int n, const KOp &op, const KPrec &prec, const KUpdate &update,
                         const double *b, double *x, double *V, double *w, double *z,
-                        double *ax, int *iters, bool *ax_valid, const KPrecOp &precop) {
+                        double *ax, int *iters, bool *ax_valid, const KPrecOp &precop,
+                        int next_mode) {
   // ax_valid (may be null): in, ax already holds op(x) for this x (the last
   // residual product of the previous solve, x unchanged since), so the first
   // residual needs no product; out, whether ax holds op(x) on return
@@ -675,14 +677,24 @@ int Runtime::gmres_core(int n, const KOp &op, const KPrec &prec, const KUpdate &
   const size_t ld = n;
   const size_t stride = 3 * (size_t)(m + 2);
   krylov_reserve(n);
-  auto dot_host = [&](const double *a, const double *bb) {
-    launch_mdot(s_, n, 1, a, ld, bb, partial_.p, hbuf_.p);
-    double h;
-    PBMP_HIP(hipMemcpyAsync(&h, hbuf_.p, sizeof(double), hipMemcpyDeviceToHost, s_));
-    sync();
-    return h;
+  // squared norms, written by their kernel straight to pinned host memory
+  double *const scalars = hpin_ + (size_t)m * stride;
+  auto norm2_host = [&](const double *a, int slot) {
+    launch_mdot(s_, n, 1, a, ld, a, partial_.p, scalars + slot);
   };
-  const double bnorm = std::sqrt(dot_host(b, b));
+  auto dot_host = [&](const double *a) {
+    norm2_host(a, 0);
+    sync();
+    return scalars[0];
+  };
+  // with op(x) at hand the first residual joins the right-hand side's wait
+  double beta2_first = -1.0;
+  if (have_ax) {
+    launch_xmy(s_, n, b, ax, w);
+    norm2_host(w, 1);
+  }
+  const double bnorm = std::sqrt(dot_host(b));
+  if (have_ax) beta2_first = scalars[1];
   *iters = 0;
   if (bnorm == 0.0) {
     launch_scale(s_, n, 0.0, x, x);
@@ -703,16 +715,19 @@ int Runtime::gmres_core(int n, const KOp &op, const KPrec &prec, const KUpdate &
   double ratio[3] = {0.1, 0.1, 0.1};
   int it = 0;
   while (true) {
-    if (!have_ax) op(x, ax, refine);
+    if (!have_ax) {
+      op(x, ax, refine);
+      launch_xmy(s_, n, b, ax, w);
+      beta2_first = dot_host(w);
+    }
     have_ax = false;
-    launch_xmy(s_, n, b, ax, w);
-    double beta = std::sqrt(dot_host(w, w));
+    double beta = std::sqrt(beta2_first);
     if (!refine && !fp64() && beta / bnorm > o.gmres_tol &&
         ((it > 0 && beta / bnorm > 0.5 * prev) || beta / bnorm <= kFloor32)) {
       refine = true;
       op(x, ax, true);
       launch_xmy(s_, n, b, ax, w);
-      beta = std::sqrt(dot_host(w, w));
+      beta = std::sqrt(dot_host(w));
     }
     last_relres_ = beta / bnorm;
     prev = last_relres_;
@@ -731,23 +746,23 @@ int Runtime::gmres_core(int n, const KOp &op, const KPrec &prec, const KUpdate &
                  : 0.5 * bnorm * std::max(o.gmres_tol, kFloor32);
     const int kmax = std::min(m, o.gmres_maxit - it);
     auto enqueue = [&](int k) {
+      // z = M^{-1} v_k (and its strengths) is ready when next_mode put it there
       if (precop) {
-        precop(V + (size_t)k * ld, z, w);
+        precop(V + (size_t)k * ld, z, w, k > 0);
       } else {
-        prec(V + (size_t)k * ld, z);
+        if (k == 0 || next_mode == 0) prec(V + (size_t)k * ld, z);
         op(z, w, false);
       }
-      // CGS2: h1 = V^T w, w -= V h1, h2 = V^T w, w -= V h2, |w|^2; the
-      // totals land in hbuf (h1, h2, |w|^2) for the host
+      // CGS2: h1 = V^T w, w -= V h1, h2 = V^T w, w -= V h2, |w|^2; the totals
+      // (h1, h2, |w|^2) go straight to the step's pinned host column
+      double *col = hpin_ + k * stride;
       int nb = launch_mdot_partial(s_, n, k + 1, V, ld, w, partial_.p);
-      launch_gemv_sub_p(s_, n, k + 1, V, ld, nb, partial_.p, hbuf_.p, w);
+      launch_gemv_sub_p(s_, n, k + 1, V, ld, nb, partial_.p, col, w, nullptr);
       nb = launch_mdot_partial(s_, n, k + 1, V, ld, w, partial_.p);
-      launch_gemv_sub_p(s_, n, k + 1, V, ld, nb, partial_.p, hbuf_.p + (m + 2), w);
-      nb = launch_mdot_partial(s_, n, 1, w, ld, w, partial_.p);
-      launch_scale_inv_sqrt_p(s_, n, nb, partial_.p, hbuf_.p + 2 * (m + 2), w,
-                              V + (size_t)(k + 1) * ld);
-      PBMP_HIP(hipMemcpyAsync(hpin_ + k * stride, hbuf_.p, sizeof(double) * stride,
-                              hipMemcpyDeviceToHost, s_));
+      nb = launch_gemv_sub_p(s_, n, k + 1, V, ld, nb, partial_.p, col + (m + 2), w, norm_.p);
+      launch_next_vector(s_, next_mode, n, nb, norm_.p, col + 2 * (m + 2), w,
+                         V + (size_t)(k + 1) * ld, ru_.nf, diag_.p, o.eps_in / o.eps_out, geo_.p,
+                         z, src64_.p, src32_.p);
       PBMP_HIP(hipEventRecord(kev_[k], s_));
       ++gmres_iters_;
     };
@@ -832,15 +847,18 @@ int Runtime::gmres(const double *b, double *x, bool transpose, int *iters) {
   // the forward solve of the SCF loop reuses A x_ from the previous solve
   bool *valid = (!transpose && x == x_.p) ? &ax_holds_x_ : nullptr;
   if (!valid) ax_holds_x_ = false;  // ax_ is overwritten
-  // forward Arnoldi steps: preconditioner and strength packing in one launch
+  // forward Arnoldi steps: preconditioner and strength packing in one launch,
+  // from the second step on in the previous one's last
   KPrecOp precop;
   if (!transpose)
-    precop = [&](const double *v, double *zz, double *ww) {
-      launch_precond_pack(s_, N, ru_.nf, diag_.p, o.eps_in / o.eps_out, geo_.p, v, zz,
-                          src64_.p, src32_.p);
+    precop = [&](const double *v, double *zz, double *ww, bool packed) {
+      if (!packed)
+        launch_precond_pack(s_, N, ru_.nf, diag_.p, o.eps_in / o.eps_out, geo_.p, v, zz,
+                            src64_.p, src32_.p);
       apply(zz, ww, false, true);
     };
-  return gmres_core(n, op, prec, update, b, x, V_.p, w_.p, z_.p, ax_.p, iters, valid, precop);
+  return gmres_core(n, op, prec, update, b, x, V_.p, w_.p, z_.p, ax_.p, iters, valid, precop,
+                    transpose ? 2 : 1);
 }
 
 // GMRES for a general operator of size n (right preconditioning, CGS2,
@@ -866,7 +884,7 @@ int Runtime::gmres_generic(int n, const KOp &op, const KPrec &prec, const double
     sync();
   };
   return gmres_core(n, op, prec, update, b, x, gV_.p, gw_.p, gz_.p, gax_.p, iters, ax_valid,
-                    KPrecOp());
+                    KPrecOp(), 0);
 }
 
 // ------------------------------------------------------------- readout
@@ -908,11 +926,9 @@ int Runtime::scf(bool solvent, double *mu, int *gm_warn) {
     }
     launch_induced(s_, false, M, sxyz_.p, mu, salpha_.p, o.thole_a, o.eps_in, Eind_.p);
     launch_scf_update(s_, M, salpha_.p, Eperm_.p, Eind_.p, solvent ? reac_.p : nullptr,
-                      4, o.scf_omega, mu, dmu2_.p);
-    double d2;
-    PBMP_HIP(hipMemcpyAsync(&d2, dmu2_.p, sizeof(double), hipMemcpyDeviceToHost, s_));
+                      4, o.scf_omega, mu, hloop_);
     sync();
-    const double rms = std::sqrt(d2 / M) * dbye;
+    const double rms = std::sqrt(hloop_[0] / M) * dbye;
     if (o.verbose)
       std::fprintf(stderr, "pbmp solve: %s iteration %d gmres %d rms change %.3e D %.1f s\n",
                    solvent ? "dissolved" : "vacuum", it, gi, rms, 1e-3 * ms_since(t_start));

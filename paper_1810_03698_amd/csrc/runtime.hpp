@@ -115,8 +115,8 @@ class Runtime {
   // ---- work ----
   Dbuf<double> part_, rpart_;
   int p2p_chunks_ = 1, ro_chunks_ = 1;
-  Dbuf<double> V_, w_, z_, ax_, b_, x_, hbuf_, partial_, ybuf_, tmp_;
-  Dbuf<double> mu_d_, mu_v_, Eperm_, Eind_, reac_, ind_, p_, f_, dmu2_, e_;
+  Dbuf<double> V_, w_, z_, ax_, b_, x_, partial_, norm_, ybuf_, tmp_;
+  Dbuf<double> mu_d_, mu_v_, Eperm_, Eind_, reac_, ind_, p_, f_, e_;
   Dbuf<double> io_a_, io_b_;  // permutation staging
   Dbuf<double> vac_perm_, vac_ind_;  // vacuum-state potential data [10M]
   bool solved_ = false;
@@ -167,12 +167,13 @@ class Runtime {
   using KOp = std::function<void(const double *, double *, bool)>;  // y = A x (f64 flag)
   using KPrec = std::function<void(const double *, double *)>;      // z = M^{-1} v
   using KUpdate = std::function<void(int, const double *)>;         // x += M^{-1} V y
-  using KPrecOp = std::function<void(const double *, double *, double *)>;  // z = M^{-1} v, w = A z
+  // z = M^{-1} v (unless already there, with its strengths), w = A z
+  using KPrecOp = std::function<void(const double *, double *, double *, bool)>;
   int gmres_generic(int n, const KOp &op, const KPrec &prec, const double *b, double *x,
                     int *iters, bool *ax_valid = nullptr);
   int gmres_core(int n, const KOp &op, const KPrec &prec, const KUpdate &update,
                  const double *b, double *x, double *V, double *w, double *z, double *ax,
-                 int *iters, bool *ax_valid, const KPrecOp &precop);
+                 int *iters, bool *ax_valid, const KPrecOp &precop, int next_mode);
   // ax_ = A x_ (gax_ = A sX_ for the layer system): the residual product of
   // the last solve, valid while neither x nor the operator changed
   bool ax_holds_x_ = false, gax_holds_x_ = false;
@@ -183,7 +184,8 @@ class Runtime {
   double adj_bar_ = 0.0;
   int adj_M_ = 0;
   void krylov_reserve(int n);
-  double *hpin_ = nullptr;           // pinned Hessenberg columns [m][3(m+2)]
+  double *hpin_ = nullptr;           // pinned Hessenberg columns [m][3(m+2)], two scalars
+  double *hloop_ = nullptr;          // pinned: the dipole loops' changes, written by their kernels
   size_t hpin_n_ = 0;
   std::vector<hipEvent_t> kev_;      // one per Arnoldi step of a cycle
   friend struct Backward;

@@ -107,7 +107,6 @@ void Runtime::set_stern(int64_t nv, const double *verts, int64_t nt, const int32
   sY_.alloc(n);
   sT_.alloc(2 * (size_t)N1);
   warm_ok_ = false;
-  partial_.reserve((size_t)(o.gmres_restart + 2) * ((n + 4095) / 4096 + 1));
   solved_ = false;
 }
 

@@ -66,10 +66,12 @@ inline int m2p_task_work(int N) { return N / 48 < 1024 ? 1024 : N / 48 > 4096 ? 
 // Panels per moment task: longer leaves are cut into slices, which cost a
 // reduction launch.
 constexpr int kMomChunkPanels = 1024;
-// leaves per shift task (moments of the boxes above the leaves): the boxes that
-// surfaces of leaf_panels ~ 300 accept hold up to 64, so their moments come
-// from one task without a second pass
-constexpr int kShiftLeaves = 64;
+// leaves per shift task (moments of the boxes above the leaves), one round of
+// a task: the boxes with more leaves (up to some 64 on surfaces cut into leaves
+// of 300) take a reduction launch, which costs less than their rounds in turn
+// (16, 32, 64 leaves: 13, 16, 18 us with it on 28880 panels, 27, 34, 54 us on
+// 144500)
+constexpr int kShiftLeaves = 16;
 // target panels per M2P^T task (adjoint product)
 constexpr int kM2PTChunkTargets = 512;
 
