@@ -12,6 +12,7 @@
 
 #include "dual.hpp"
 #include "kernels.hpp"
+#include "pair.hpp"
 
 namespace pbmp {
 
@@ -129,19 +130,51 @@ __global__ void k_make_weights(int M, double c, const double *__restrict__ q,
   w[9] = c * Ql[8] / 6.0;
 }
 
+// w times the single-layer (G = 1/r) and double-layer (H = n.R/r^3) data of
+// one node contracted with the weights W of (value, gradient, second
+// derivatives): sg += w W.G, sh += w W.H.
+__device__ __forceinline__ void node_weights(const double R[3], const double n[3],
+                                             const double *W, double w, double &sg, double &sh) {
+  const double rr = R[0] * R[0] + R[1] * R[1] + R[2] * R[2];
+  const double i1 = rsqrt_fp64(rr);
+  const double i2 = i1 * i1, i3 = i1 * i2, i5 = i3 * i2;
+  const double nR = n[0] * R[0] + n[1] * R[1] + n[2] * R[2];
+  const double WR = W[1] * R[0] + W[2] * R[1] + W[3] * R[2];
+  const double Wn = W[1] * n[0] + W[2] * n[1] + W[3] * n[2];
+  const double tr = W[4] + W[7] + W[9];
+  // symmetric matrix of the upper-triangle weights (off-diagonal ones halved
+  // into both places), doubled: M R
+  const double M0 = 2.0 * W[4] * R[0] + W[5] * R[1] + W[6] * R[2];
+  const double M1 = W[5] * R[0] + 2.0 * W[7] * R[1] + W[8] * R[2];
+  const double M2 = W[6] * R[0] + W[8] * R[1] + 2.0 * W[9] * R[2];
+  const double RMR = 0.5 * (M0 * R[0] + M1 * R[1] + M2 * R[2]);
+  const double nMR = M0 * n[0] + M1 * n[1] + M2 * n[2];
+  sg += w * (W[0] * i1 - i3 * (WR + tr) + 3.0 * i5 * RMR);
+  sh += w * (i3 * (W[0] * nR + Wn) - 3.0 * i5 * (nR * (WR + tr) + nMR) +
+             15.0 * nR * RMR * i5 * i2);
+}
+
 // out[j] = -d/dphi_j, out[N+j] = -d/ddphi_j of sum_l W_l . reac_l(x), i.e.
 // minus the transposed readout (far rule everywhere, near rule on the
-// panel's near sites via the transposed site list).
-__global__ __launch_bounds__(256) void k_readout_T(
+// panel's near sites via the transposed site list).  Blocks of 64 panels whose
+// eight waves take every eighth site (a panel per thread walked all sites with
+// 32 blocks on 8000 panels: 126 us at 100 sites).
+constexpr int kRoTWaves = 8;
+
+__global__ __launch_bounds__(64 * kRoTWaves) void k_readout_T(
     int N, int M, int nf, const double *__restrict__ src64, const double *__restrict__ geo,
     const double *__restrict__ verts, const int *__restrict__ tri, RuleArgs ru,
     const double *__restrict__ xyz, const double *__restrict__ W,
     const int *__restrict__ tsrow, const int *__restrict__ tscol, double *__restrict__ out) {
   constexpr int kT = 64;
   __shared__ double sh[kT * 13];
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  __shared__ double red[kRoTWaves - 1][2][64];
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+  const int j = blockIdx.x * 64 + lane;
   const int jl = min(j, N - 1);
-  const double *rec = src64 + 16 * (size_t)jl;
+  double rec[12];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) rec[k] = src64[16 * (size_t)jl + k];
   const double n[3] = {rec[9], rec[10], rec[11]};
   const double A = geo[6 * N + jl];
   double sg = 0.0, sh_ = 0.0;
@@ -153,18 +186,27 @@ __global__ __launch_bounds__(256) void k_readout_T(
       sh[e] = k < 3 ? xyz[3 * l + k] : W[10 * l + k - 3];
     }
     __syncthreads();
-    for (int e = 0; e < nl; ++e) {
+    for (int e = wave; e < nl; e += kRoTWaves) {
       const double *s = sh + 13 * e;
       for (int q = 0; q < nf; ++q) {
-        const double R[3] = {s[0] - rec[3 * q], s[1] - rec[3 * q + 1], s[2] - rec[3 * q + 2]};
-        double g[10], h[10];
-        node_data<double>(R, n, g, h);
-        sg += ru.fw[q] * dot10<double>(s + 3, g);
-        sh_ += ru.fw[q] * dot10<double>(s + 3, h);
+        const double y[3] = {q == 0 ? rec[0] : q == 1 ? rec[3] : rec[6],
+                             q == 0 ? rec[1] : q == 1 ? rec[4] : rec[7],
+                             q == 0 ? rec[2] : q == 1 ? rec[5] : rec[8]};
+        const double R[3] = {s[0] - y[0], s[1] - y[1], s[2] - y[2]};
+        node_weights(R, n, s + 3, ru.fw[q], sg, sh_);
       }
     }
   }
-  if (j >= N) return;
+  if (wave > 0) {
+    red[wave - 1][0][lane] = sg;
+    red[wave - 1][1][lane] = sh_;
+  }
+  __syncthreads();
+  if (wave > 0 || j >= N) return;
+  for (int w = 0; w < kRoTWaves - 1; ++w) {
+    sg += red[w][0][lane];
+    sh_ += red[w][1][lane];
+  }
   // near sites: far rule -> 19-node rule
   double v[3][3];
   load_panel(verts, tri, j, v);
@@ -172,20 +214,15 @@ __global__ __launch_bounds__(256) void k_readout_T(
     const int l = tscol[t];
     const double P[3] = {xyz[3 * l], xyz[3 * l + 1], xyz[3 * l + 2]};
     for (int q = 0; q < nf; ++q) {
-      const double R[3] = {P[0] - rec[3 * q], P[1] - rec[3 * q + 1], P[2] - rec[3 * q + 2]};
-      double g[10], h[10];
-      node_data<double>(R, n, g, h);
-      sg -= ru.fw[q] * dot10<double>(W + 10 * l, g);
-      sh_ -= ru.fw[q] * dot10<double>(W + 10 * l, h);
+      const double R[3] = {P[0] - src64[16 * (size_t)j + 3 * q], P[1] - src64[16 * (size_t)j + 3 * q + 1],
+                           P[2] - src64[16 * (size_t)j + 3 * q + 2]};
+      node_weights(R, n, W + 10 * l, -ru.fw[q], sg, sh_);
     }
     for (int q = 0; q < ru.nn; ++q) {
       double R[3];
       for (int d = 0; d < 3; ++d)
         R[d] = P[d] - (ru.nb[q][0] * v[0][d] + ru.nb[q][1] * v[1][d] + ru.nb[q][2] * v[2][d]);
-      double g[10], h[10];
-      node_data<double>(R, n, g, h);
-      sg += ru.nw[q] * dot10<double>(W + 10 * l, g);
-      sh_ += ru.nw[q] * dot10<double>(W + 10 * l, h);
+      node_weights(R, n, W + 10 * l, ru.nw[q], sg, sh_);
     }
   }
   out[j] = A * sh_;       // -(-A sum h)
@@ -502,7 +539,7 @@ void launch_readout_T(hipStream_t s, int N, int M, const double *src64, const do
                       const double *verts, const int *tri, const RuleArgs &ru,
                       const double *xyz, const double *W, const int *tsrow, const int *tscol,
                       double *out) {
-  hipLaunchKernelGGL(k_readout_T, dim3((N + 255) / 256), dim3(256), 0, s, N, M, ru.nf, src64,
+  hipLaunchKernelGGL(k_readout_T, dim3((N + 63) / 64), dim3(64 * kRoTWaves), 0, s, N, M, ru.nf, src64,
                      geo, verts, tri, ru, xyz, W, tsrow, tscol, out);
   PBMP_HIP(hipGetLastError());
 }

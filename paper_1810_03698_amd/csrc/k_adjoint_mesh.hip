@@ -23,107 +23,154 @@ constexpr double kInv4Pi = 0.07957747154594767;
 constexpr int kB = 256;
 constexpr int kT = 64;
 
+// Far-rule operator pairs, direct mode.  A block of eight waves takes 32 panels
+// (lane l and l + 32 the same one); its 16 half waves take every sixteenth
+// panel of the other side from tiles staged through LDS, and their sums are
+// added by a lane exchange and through LDS in a fixed order.  FP64 VALU issue
+// bound from some 8000 panels on; a panel per thread left 125 waves walking all
+// 8000 panels: 7.8 ms for the targets and 12.4 ms for the sources there, 2.4
+// and 3.8 ms at 2420.
+constexpr int kGradLanes = 32, kGradBlock = 512, kGradSets = kGradBlock / kGradLanes;
+
+// sum of v over the block's sets for the first 32 threads
+__device__ __forceinline__ double grad_sum(double v, double (*red)[kGradLanes]) {
+  const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+  v += __shfl_xor(v, 32, 64);
+  __syncthreads();
+  if (lane < kGradLanes) red[wave][lane] = v;
+  __syncthreads();
+  double t = 0.0;
+  if (threadIdx.x < kGradLanes)
+    for (int w = 0; w < kGradBlock / 64; ++w) t += red[w][lane];
+  return t;
+}
+
 // per target panel i: d/dc_i of sum_j lambda_x . A x (far rule everywhere)
-__global__ __launch_bounds__(kB) void k_op_grad_target(int N, int nf,
-                                                       const double *__restrict__ src64,
-                                                       const double *__restrict__ geo,
-                                                       const double *__restrict__ x,
-                                                       const double *__restrict__ lam,
-                                                       double kappa, double eps_ratio,
-                                                       RuleArgs ru, double *__restrict__ gc) {
+template <int NF>
+__global__ __launch_bounds__(kGradBlock) void k_op_grad_target(
+    int N, const double *__restrict__ src64, const double *__restrict__ geo,
+    const double *__restrict__ x, const double *__restrict__ lam, double kappa,
+    double eps_ratio, double *__restrict__ gc) {
   __shared__ double sh[kT * 15];
-  const int i = blockIdx.x * kB + threadIdx.x;
-  const int il = min(i, N - 1);
+  __shared__ double etab[64];
+  __shared__ double red[kGradBlock / 64][kGradLanes];
+  const Screen<double> sc = make_screen(kappa, etab);
+  const int li = (int)threadIdx.x % kGradLanes, set = (int)threadIdx.x / kGradLanes;
+  const int i = blockIdx.x * kGradLanes + li, il = min(i, N - 1);
   const double c[3] = {geo[il], geo[N + il], geo[2 * N + il]};
   const double l1 = lam[il], l2 = lam[N + il];
   double g[3] = {0.0, 0.0, 0.0};
   for (int j0 = 0; j0 < N; j0 += kT) {
     const int nj = min(kT, N - j0);
     __syncthreads();
-    for (int e = threadIdx.x; e < nj * 15; e += kB) {
+    for (int e = threadIdx.x; e < nj * 15; e += kGradBlock) {
       const int j = j0 + e / 15, k = e % 15;
       const double *rec = src64 + 16 * (size_t)j;
       sh[e] = k < 12 ? rec[k] : (k == 12 ? geo[6 * N + j] : (k == 13 ? x[j] : x[N + j]));
     }
     __syncthreads();
-    for (int e = 0; e < nj; ++e) {
+    for (int e = set; e < nj; e += kGradSets) {
       const double *s = sh + 15 * e;
-      const double alpha = s[12] * kInv4Pi;
-      const double a1 = l1 * s[13], a2 = l1 * s[14], a3 = l2 * s[13], a4 = eps_ratio * l2 * s[14];
-      for (int q = 0; q < nf; ++q) {
+      const double w = s[12] * (kInv4Pi / NF);  // equal-weight rules
+      const double a1 = w * l1 * s[13], a2 = w * l1 * s[14], a3 = w * l2 * s[13],
+                   a4 = w * eps_ratio * l2 * s[14];
+#pragma unroll
+      for (int q = 0; q < NF; ++q) {
         const double R[3] = {c[0] - s[3 * q], c[1] - s[3 * q + 1], c[2] - s[3 * q + 2]};
         double gR[3], gn[3];
-        op_pair(R, s + 9, kappa, a1, a2, a3, a4, gR, gn);
-        for (int d = 0; d < 3; ++d) g[d] += alpha * ru.fw[q] * gR[d];
+        op_pair(R, s + 9, sc, a1, a2, a3, a4, gR, gn);
+        for (int d = 0; d < 3; ++d) g[d] += gR[d];
       }
     }
   }
-  if (i < N)
-    for (int d = 0; d < 3; ++d) gc[3 * i + d] = g[d];
+  for (int d = 0; d < 3; ++d) {
+    const double t = grad_sum(g[d], red);
+    if (threadIdx.x < kGradLanes && i < N) gc[3 * i + d] = t;
+  }
 }
 
 // per source panel j: d/dy_jq, d/dn_j, d/dA_j of sum_i lambda_x . A x
-__global__ __launch_bounds__(kB) void k_op_grad_source(int N, int nf,
-                                                       const double *__restrict__ src64,
-                                                       const double *__restrict__ geo,
-                                                       const double *__restrict__ x,
-                                                       const double *__restrict__ lam,
-                                                       double kappa, double eps_ratio,
-                                                       RuleArgs ru, double *__restrict__ gy,
-                                                       double *__restrict__ gn,
-                                                       double *__restrict__ gA) {
+template <int NF>
+__global__ __launch_bounds__(kGradBlock) void k_op_grad_source(
+    int N, const double *__restrict__ src64, const double *__restrict__ geo,
+    const double *__restrict__ x, const double *__restrict__ lam, double kappa,
+    double eps_ratio, double *__restrict__ gy, double *__restrict__ gn,
+    double *__restrict__ gA) {
   __shared__ double sh[kT * 5];
-  const int j = blockIdx.x * kB + threadIdx.x;
-  const int jl = min(j, N - 1);
-  const double *rec = src64 + 16 * (size_t)jl;
-  const double n[3] = {rec[9], rec[10], rec[11]};
-  const double A = geo[6 * N + jl];
+  __shared__ double etab[64];
+  __shared__ double red[kGradBlock / 64][kGradLanes];
+  const Screen<double> sc = make_screen(kappa, etab);
+  const int li = (int)threadIdx.x % kGradLanes, set = (int)threadIdx.x / kGradLanes;
+  const int j = blockIdx.x * kGradLanes + li, jl = min(j, N - 1);
+  double rec[12];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) rec[k] = src64[16 * (size_t)jl + k];
   const double ph = x[jl], dp = x[N + jl];
-  double ay[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, an[3] = {0, 0, 0}, aA = 0.0;
+  double ay[3 * NF], an[3] = {0, 0, 0}, aA = 0.0;
+#pragma unroll
+  for (int k = 0; k < 3 * NF; ++k) ay[k] = 0.0;
   for (int i0 = 0; i0 < N; i0 += kT) {
     const int ni = min(kT, N - i0);
     __syncthreads();
-    for (int e = threadIdx.x; e < ni * 5; e += kB) {
+    for (int e = threadIdx.x; e < ni * 5; e += kGradBlock) {
       const int i = i0 + e / 5, k = e % 5;
       sh[e] = k < 3 ? geo[k * N + i] : lam[(k - 3) * N + i];
     }
     __syncthreads();
-    for (int e = 0; e < ni; ++e) {
+    for (int e = set; e < ni; e += kGradSets) {
       const double *s = sh + 5 * e;
       const double a1 = s[3] * ph, a2 = s[3] * dp, a3 = s[4] * ph, a4 = eps_ratio * s[4] * dp;
-      for (int q = 0; q < nf; ++q) {
+#pragma unroll
+      for (int q = 0; q < NF; ++q) {
         const double R[3] = {s[0] - rec[3 * q], s[1] - rec[3 * q + 1], s[2] - rec[3 * q + 2]};
         double gR[3], gnn[3];
-        const double f = op_pair(R, n, kappa, a1, a2, a3, a4, gR, gnn);
-        const double w = ru.fw[q] * kInv4Pi;
+        aA += op_pair(R, rec + 9, sc, a1, a2, a3, a4, gR, gnn);
         for (int d = 0; d < 3; ++d) {
-          ay[3 * q + d] -= w * A * gR[d];
-          an[d] += w * A * gnn[d];
+          ay[3 * q + d] -= gR[d];
+          an[d] += gnn[d];
         }
-        aA += w * f;
       }
     }
   }
-  if (j < N) {
-    for (int k = 0; k < 9; ++k) gy[9 * j + k] = ay[k];
-    for (int d = 0; d < 3; ++d) gn[3 * j + d] = an[d];
-    gA[j] = aA;
+  const double w = kInv4Pi / NF, A = geo[6 * (size_t)N + jl];
+  const bool out = threadIdx.x < kGradLanes && j < N;
+#pragma unroll
+  for (int k = 0; k < 3 * NF; ++k) {
+    const double t = grad_sum(ay[k], red);
+    if (out) gy[9 * j + k] = w * A * t;
   }
+  for (int d = 0; d < 3; ++d) {
+    const double t = grad_sum(an[d], red);
+    if (out) gn[3 * j + d] = w * A * t;
+  }
+  const double t = grad_sum(aA, red);
+  if (out) gA[j] = w * t;
 }
 
 // Near/self correction entries (fine - far rule) differentiated in the
 // target point and the source panel's vertices: ge[e][0..2] = d/dc_i,
 // ge[e][3..11] = d/dv_j (for the self entry, c_i is the panel's own centroid
 // and everything is carried by the vertices).
-__global__ void k_near_grad(int N, const int *__restrict__ rowptr, const int *__restrict__ col,
-                            const double *__restrict__ verts, const int *__restrict__ tri,
-                            const double *__restrict__ geo, const double *__restrict__ x,
-                            const double *__restrict__ lam, double kappa, double eps_ratio,
-                            RuleArgs ru, double *__restrict__ ge) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+//
+// SELF: the rows' first entries, one thread each; else the others, sixteen lanes
+// per row (a thread per row walked some 16 entries of 22 nodes in dual numbers:
+// 3.8 ms on 2420 panels).
+constexpr int kNearLanes = 16;
+
+template <bool SELF>
+__global__ __launch_bounds__(64) void k_near_grad(
+    int N, const int *__restrict__ rowptr, const int *__restrict__ col,
+    const double *__restrict__ verts, const int *__restrict__ tri,
+    const double *__restrict__ geo, const double *__restrict__ x,
+    const double *__restrict__ lam, double kappa, double eps_ratio, RuleArgs ru,
+    double *__restrict__ ge) {
+  const int t = blockIdx.x * 64 + (int)threadIdx.x;
+  const int i = SELF ? t : t / kNearLanes;
   if (i >= N) return;
   const double l1 = lam[i], l2 = lam[N + i];
-  for (int e = rowptr[i]; e < rowptr[i + 1]; ++e) {
+  const int e0 = rowptr[i] + (SELF ? 0 : 1 + t % kNearLanes);
+  const int e1 = SELF ? rowptr[i] + 1 : rowptr[i + 1];
+  for (int e = e0; e < e1; e += kNearLanes) {
     const int j = col[e];
     const double a1 = l1 * x[j], a2 = l1 * x[N + j], a3 = l2 * x[j], a4 = eps_ratio * l2 * x[N + j];
     using D = Dual<12>;
@@ -131,13 +178,9 @@ __global__ void k_near_grad(int N, const int *__restrict__ rowptr, const int *__
     for (int a = 0; a < 3; ++a)
       for (int d = 0; d < 3; ++d) v[a][d] = D::var(verts[3 * tri[3 * j + a] + d], 3 + 3 * a + d);
     panel_frame_t<D>(v, cj, n, A);
-    if (j == i) {
-      for (int d = 0; d < 3; ++d) c[d] = cj[d];
-    } else {
-      for (int d = 0; d < 3; ++d) c[d] = D::var(geo[d * N + i], d);
-    }
+    for (int d = 0; d < 3; ++d) c[d] = SELF ? cj[d] : D::var(geo[d * N + i], d);
     D fine[4], coarse[4];
-    if (j == i) {
+    if (SELF) {
       singular_panel_t<D>(v, c, kappa, ru, fine[0], fine[2]);
       fine[1] = D(0.0);
       fine[3] = D(0.0);
@@ -356,13 +399,24 @@ void launch_mesh_adjoint(hipStream_t s, int N, int M, int nf, const double *src6
     tree_mesh_adjoint_far(*tree, s, nf, N, geo, src64, lam, kappa, eps_ratio, part, partT, gc,
                           gy, gn, gA);
   } else {
-    hipLaunchKernelGGL(k_op_grad_target, g1, dim3(kB), 0, s, N, nf, src64, geo, x, lam, kappa,
-                       eps_ratio, ru, gc);
-    hipLaunchKernelGGL(k_op_grad_source, g1, dim3(kB), 0, s, N, nf, src64, geo, x, lam, kappa,
-                       eps_ratio, ru, gy, gn, gA);
+    const dim3 gg((N + kGradLanes - 1) / kGradLanes);
+#define PBMP_OG(NF)                                                                         \
+  hipLaunchKernelGGL(k_op_grad_target<NF>, gg, dim3(kGradBlock), 0, s, N, src64, geo, x, lam, \
+                     kappa, eps_ratio, gc);                                                 \
+  hipLaunchKernelGGL(k_op_grad_source<NF>, gg, dim3(kGradBlock), 0, s, N, src64, geo, x, lam, \
+                     kappa, eps_ratio, gy, gn, gA)
+    if (nf == 3) {
+      PBMP_OG(3);
+    } else {
+      PBMP_OG(1);
+    }
+#undef PBMP_OG
   }
-  hipLaunchKernelGGL(k_near_grad, dim3((N + 63) / 64), dim3(64), 0, s, N, rowptr, col, verts,
-                     tri, geo, x, lam, kappa, eps_ratio, ru, ge);
+  hipLaunchKernelGGL(k_near_grad<true>, dim3((N + 63) / 64), dim3(64), 0, s, N, rowptr, col,
+                     verts, tri, geo, x, lam, kappa, eps_ratio, ru, ge);
+  const int rows = 64 / kNearLanes;
+  hipLaunchKernelGGL(k_near_grad<false>, dim3((N + rows - 1) / rows), dim3(64), 0, s, N, rowptr,
+                     col, verts, tri, geo, x, lam, kappa, eps_ratio, ru, ge);
   hipLaunchKernelGGL(k_near_grad_reduce, g1, dim3(kB), 0, s, N, rowptr, trow, tent, ge, gc,
                      gv);
   hipLaunchKernelGGL(k_rhs_centroid_grad, g1, dim3(kB), 0, s, N, M, geo, sigma, xyz, q, p, Q,

@@ -1123,6 +1123,8 @@ __global__ __launch_bounds__(64) void k_p2p_grad_tasks(int ntask, const int *__r
                                                        double *__restrict__ part) {
   constexpr int kTileG = 64;
   __shared__ __align__(16) double sh[kTileG * 16];
+  __shared__ double etab[64];
+  const Screen<double> sc = make_screen(kappa, etab);
   const int task = xcd_task(ntask);
   if (task < 0) return;
   const int t0 = tasks[4 * task], t1 = tasks[4 * task + 1];
@@ -1147,7 +1149,7 @@ __global__ __launch_bounds__(64) void k_p2p_grad_tasks(int ntask, const int *__r
           for (int q = 0; q < NF; ++q) {
             const double R[3] = {c[0] - r[3 * q], c[1] - r[3 * q + 1], c[2] - r[3 * q + 2]};
             double gR[3], gn[3];
-            op_pair(R, r + 9, kappa, l1 * r[14], l1 * r[13], l2k * r[14], l2 * r[13], gR, gn);
+            op_pair(R, r + 9, sc, l1 * r[14], l1 * r[13], l2k * r[14], l2 * r[13], gR, gn);
             for (int d = 0; d < 3; ++d) g[d] += gR[d];
           }
         }
@@ -1295,6 +1297,8 @@ __global__ __launch_bounds__(64) void k_p2pT_grad_tasks(int ntask, const int *__
                                                         double kappa, double eps_ratio,
                                                         double *__restrict__ part) {
   __shared__ double sh[64 * 5];
+  __shared__ double etab[64];
+  const Screen<double> sc = make_screen(kappa, etab);
   const int task = xcd_task(ntask);
   if (task < 0) return;
   const int B = tasks[4 * task], lb = tasks[4 * task + 1], le = tasks[4 * task + 2];
@@ -1327,7 +1331,7 @@ __global__ __launch_bounds__(64) void k_p2pT_grad_tasks(int ntask, const int *__
           for (int q = 0; q < NF; ++q) {
             const double R[3] = {r[0] - rec[3 * q], r[1] - rec[3 * q + 1], r[2] - rec[3 * q + 2]};
             double gR[3], gn[3];
-            const double f = op_pair(R, rec + 9, kappa, r[3] * rec[14], r[3] * rec[13],
+            const double f = op_pair(R, rec + 9, sc, r[3] * rec[14], r[3] * rec[13],
                                      r[4] * rec[14], eps_ratio * r[4] * rec[13], gR, gn);
             for (int d = 0; d < 3; ++d) {
               acc[3 * q + d] -= gR[d];

@@ -264,7 +264,7 @@ __device__ __forceinline__ void panel_columns(const T *r, T px, T py, T pz, T z1
 // (the pair's share of lambda_x . A x; with the panel's packed strengths
 // s_K, s_V in place of phi_j, dphi_j the weight and area are included).
 // Returns f, df/dR, df/dn.
-__device__ inline double op_pair(const double R[3], const double n[3], double kappa,
+__device__ inline double op_pair(const double R[3], const double n[3], const Screen<double> &sc,
                                  double a1, double a2, double a3, double a4, double gR[3],
                                  double gn[3]) {
   const double rr = R[0] * R[0] + R[1] * R[1] + R[2] * R[2];
@@ -272,9 +272,10 @@ __device__ inline double op_pair(const double R[3], const double n[3], double ka
     for (int d = 0; d < 3; ++d) gR[d] = gn[d] = 0.0;
     return 0.0;
   }
-  const double ri = rsqrt_fp64(rr);
-  const double r = rr * ri, ri3 = ri * ri * ri, ri5 = ri3 * ri * ri;
-  const double e = exp_fp64(-kappa * r);
+  double r;
+  const double ri = rsqrt_fp64(rr, r), kappa = sc.kappa;
+  const double ri3 = ri * ri * ri, ri5 = ri3 * ri * ri;
+  const double e = sc.exp<true>(r);
   const double nR = n[0] * R[0] + n[1] * R[1] + n[2] * R[2];
   const double ky = (1.0 + kappa * r) * e;
   const double f = a1 * nR * ri3 - a2 * ri - a3 * nR * ky * ri3 + a4 * e * ri;
