@@ -74,8 +74,8 @@ template <class T>
 __device__ inline void coarse_panel(int nf, const T *rec, T px, T py, T pz, const Screen<T> &sc,
                                     double wA, double out[4]) {
   T vl, kl, vy, ky, nR;
-  if (nf == 3) panel_sums<3, true>(rec, px, py, pz, sc, vl, kl, vy, ky, nR);
-  else panel_sums<1, true>(rec, px, py, pz, sc, vl, kl, vy, ky, nR);
+  if (nf == 3) panel_sums<3>(rec, px, py, pz, sc, vl, kl, vy, ky, nR);
+  else panel_sums<1>(rec, px, py, pz, sc, vl, kl, vy, ky, nR);
   out[0] = wA * (double)vl;
   out[1] = wA * (double)(nR * kl);
   out[2] = wA * (double)vy;

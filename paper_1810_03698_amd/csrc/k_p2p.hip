@@ -85,18 +85,21 @@ __global__ __launch_bounds__(kBlock) void k_p2p(const T *__restrict__ src, int N
     const v2 *g = reinterpret_cast<const v2 *>(src + (size_t)jt * 16);
     for (int e = threadIdx.x; e < nj * PER; e += kBlock) reinterpret_cast<v2 *>(sh)[e] = g[e];
     __syncthreads();
-    T a[TPT][2];
+    T a[TPT][2][kAcc<T, NF>];
 #pragma unroll
-    for (int k = 0; k < TPT; ++k) a[k][0] = a[k][1] = T(0);
+    for (int k = 0; k < TPT; ++k)
+      for (int c = 0; c < 2; ++c)
+        for (int q = 0; q < kAcc<T, NF>; ++q) a[k][c][q] = T(0);
     for (int jj = wave; jj < nj; jj += kWaves) {
       const T *r = sh + 16 * jj;
 #pragma unroll
       for (int k = 0; k < TPT; ++k)
-        panel_rows<NF, FLOOR>(r, px[k], py[k], pz[k], sc, a[k][0], a[k][1]);
+        panel_rows<NF, FLOOR>(r, px[k], py[k], pz[k], sc, a[k]);
     }
 #pragma unroll
     for (int k = 0; k < TPT; ++k)
-      for (int c = 0; c < 2; ++c) S[k][c] += (double)a[k][c];
+      for (int c = 0; c < 2; ++c)
+        for (int q = 0; q < kAcc<T, NF>; ++q) S[k][c] += (double)a[k][c][q];
   }
   if (wave > 0)
 #pragma unroll
@@ -190,19 +193,21 @@ __global__ __launch_bounds__(kBlock) void k_p2p_transpose(
       r[5] = (T)(eps_ratio * z[N + i]);
     }
     __syncthreads();
-    T a[TPT][2];
+    T a[TPT][2][kAcc<T, NF>];
 #pragma unroll
-    for (int k = 0; k < TPT; ++k) a[k][0] = a[k][1] = T(0);
+    for (int k = 0; k < TPT; ++k)
+      for (int c = 0; c < 2; ++c)
+        for (int q = 0; q < kAcc<T, NF>; ++q) a[k][c][q] = T(0);
     for (int e = wave; e < ni; e += kWaves) {
       const T *r = sh + kRec * e;
 #pragma unroll
       for (int k = 0; k < TPT; ++k)
-        panel_columns<NF, FLOOR>(rec[k], r[0], r[1], r[2], r[3], r[4], r[5], sc,
-                                 a[k][0], a[k][1]);
+        panel_columns<NF, FLOOR>(rec[k], r[0], r[1], r[2], r[3], r[4], r[5], sc, a[k]);
     }
 #pragma unroll
     for (int k = 0; k < TPT; ++k)
-      for (int c = 0; c < 2; ++c) S[k][c] += (double)a[k][c];
+      for (int c = 0; c < 2; ++c)
+        for (int q = 0; q < kAcc<T, NF>; ++q) S[k][c] += (double)a[k][c][q];
   }
   if (wave > 0)
 #pragma unroll

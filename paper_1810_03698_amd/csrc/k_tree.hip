@@ -436,18 +436,21 @@ __device__ void p2p_task_body(const T *__restrict__ src, const T *__restrict__ t
         __syncthreads();
         stage_records<T, kTileT>(src + (size_t)jt * 16, sh, nj, lane);
         __syncthreads();
-        T a[TPT][2];
+        T a[TPT][2][kAcc<T, NF>];
 #pragma unroll
-        for (int k = 0; k < TPT; ++k) a[k][0] = a[k][1] = T(0);
+        for (int k = 0; k < TPT; ++k)
+          for (int c = 0; c < 2; ++c)
+            for (int q = 0; q < kAcc<T, NF>; ++q) a[k][c][q] = T(0);
         for (int jj = active ? gi : nj; jj < nj; jj += G) {
           const T *r = sh + 16 * jj;
 #pragma unroll
           for (int k = 0; k < TPT; ++k)
-            panel_rows<NF, FLOOR>(r, px[k], py[k], pz[k], sc, a[k][0], a[k][1]);
+            panel_rows<NF, FLOOR>(r, px[k], py[k], pz[k], sc, a[k]);
         }
 #pragma unroll
         for (int k = 0; k < TPT; ++k)
-          for (int c = 0; c < 2; ++c) S[k][c] += (double)a[k][c];
+          for (int c = 0; c < 2; ++c)
+            for (int q = 0; q < kAcc<T, NF>; ++q) S[k][c] += (double)a[k][c][q];
       }
     }
     if (G > 1) {
@@ -780,19 +783,21 @@ __device__ void p2pT_body(const T *__restrict__ src, const T *__restrict__ tgt,
           sh[8 * lane + 5] = (T)(eps_ratio * z[N + i]);
         }
         __syncthreads();
-        T a[SPT][2];
+        T a[SPT][2][kAcc<T, NF>];
 #pragma unroll
-        for (int k = 0; k < SPT; ++k) a[k][0] = a[k][1] = T(0);
+        for (int k = 0; k < SPT; ++k)
+          for (int c = 0; c < 2; ++c)
+            for (int q = 0; q < kAcc<T, NF>; ++q) a[k][c][q] = T(0);
         for (int e = active ? gi : nt; e < nt; e += G) {
           const T *r = sh + 8 * e;
 #pragma unroll
           for (int k = 0; k < SPT; ++k)
-            panel_columns<NF, FLOOR>(rec[k], r[0], r[1], r[2], r[3], r[4], r[5], sc,
-                                     a[k][0], a[k][1]);
+            panel_columns<NF, FLOOR>(rec[k], r[0], r[1], r[2], r[3], r[4], r[5], sc, a[k]);
         }
 #pragma unroll
         for (int k = 0; k < SPT; ++k)
-          for (int c = 0; c < 2; ++c) S[k][c] += (double)a[k][c];
+          for (int c = 0; c < 2; ++c)
+            for (int q = 0; q < kAcc<T, NF>; ++q) S[k][c] += (double)a[k][c][q];
       }
     }
     if (G > 1) {
