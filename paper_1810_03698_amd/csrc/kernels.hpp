@@ -44,8 +44,8 @@ void launch_pack_strengths(hipStream_t s, int N, int nf, double eps_ratio,
 // floor_r2: FP32 pairs closer than 1e-4 A add nothing (needed only for the
 // one-node rule, or panels small enough for a node and a centroid to
 // coincide in FP32).
-// nchunk: source chunks, direct_chunks(fp64, N).
-int direct_chunks(bool fp64, int N);
+// nchunk: source chunks, direct_chunks(N).
+int direct_chunks(int N);
 void launch_p2p_direct(hipStream_t s, bool fp64, int nf, int N, int Nt,
                        const double *src64, const float *src32,
                        const double *geo, const float *tgt32, double kappa,

@@ -462,7 +462,7 @@ void Runtime::alloc_work() {
   const int n = 2 * N;
   const int m = o.gmres_restart;
   // direct-product chunking: enough blocks to fill the device
-  p2p_chunks_ = direct_chunks(fp64(), N);
+  p2p_chunks_ = direct_chunks(N);
   int slots = p2p_chunks_;
   if (tree_active_) slots = std::max({slots, tree_->max_slots, tree_->max_slots_T});
   part_.alloc((size_t)slots * 4 * N);
