@@ -27,6 +27,27 @@ constexpr double kInv4Pi = 0.07957747154594767;
 constexpr int kBlock = 256;
 constexpr int kTile = 128;  // panels per LDS tile
 
+// x = the caller's vector gathered into the internal panel order, and its
+// strengths packed (as k_pack_strengths): a product's input in one launch
+__global__ void k_gather_pack(int N, int nf, double eps_ratio, const int *__restrict__ perm,
+                              const double *__restrict__ geo, const double *__restrict__ user,
+                              double *__restrict__ x, double *__restrict__ src64,
+                              float *__restrict__ src32) {
+  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= N) return;
+  const double ph = user[perm[j]], dp = user[N + perm[j]];
+  x[j] = ph;
+  x[N + j] = dp;
+  const double wA = geo[6 * (size_t)N + j] * kInv4Pi / nf;  // equal-weight rules
+  const double sv = wA * dp, sk = wA * ph;
+  src64[16 * (size_t)j + 13] = sv;
+  src64[16 * (size_t)j + 14] = sk;
+  src64[16 * (size_t)j + 15] = eps_ratio * sv;
+  src32[16 * (size_t)j + 13] = (float)sv;
+  src32[16 * (size_t)j + 14] = (float)sk;
+  src32[16 * (size_t)j + 15] = (float)(eps_ratio * sv);
+}
+
 __global__ void k_pack_strengths(int N, int nf, double eps_ratio,
                                  const double *__restrict__ geo,
                                  const double *__restrict__ x,
@@ -106,7 +127,7 @@ constexpr int kFinLanes = 8;
 __global__ __launch_bounds__(kBlock) void k_finish(
     int N, int nchunk, const double *__restrict__ part, const int *__restrict__ rowptr,
     const int *__restrict__ col, const double *__restrict__ val, const double *__restrict__ x,
-    double eps_ratio, double *__restrict__ y) {
+    double eps_ratio, const int *__restrict__ perm, double *__restrict__ y) {
   const int t = blockIdx.x * kBlock + (int)threadIdx.x;
   const int i = t / kFinLanes, u = t % kFinLanes;
   const int il = min(i, N - 1);
@@ -125,8 +146,9 @@ __global__ __launch_bounds__(kBlock) void k_finish(
     for (int k = 0; k < 2; ++k) S[k] += __shfl_xor(S[k], w, kFinLanes);
   if (i >= N || u != 0) return;
   const double ph = x[i];
-  y[i] = 0.5 * ph + S[0];
-  y[N + i] = 0.5 * ph + S[1];
+  const int o = perm ? perm[i] : i;
+  y[o] = 0.5 * ph + S[0];
+  y[N + o] = 0.5 * ph + S[1];
 }
 
 // Transposed far-field sums: targets are the far-field nodes of panel j
@@ -198,7 +220,8 @@ __global__ __launch_bounds__(kBlock) void k_p2p_transpose(
 __global__ __launch_bounds__(kBlock) void k_finish_transpose(
     int N, int nchunk, const double *__restrict__ part, const int *__restrict__ trow,
     const int *__restrict__ tcol, const int *__restrict__ tent, const double *__restrict__ val,
-    const double *__restrict__ z, double eps_ratio, double *__restrict__ y) {
+    const double *__restrict__ z, double eps_ratio, const int *__restrict__ perm,
+    double *__restrict__ y) {
   const int t = blockIdx.x * kBlock + (int)threadIdx.x;
   const int j = t / kFinLanes, u = t % kFinLanes;
   const int jl = min(j, N - 1);
@@ -216,11 +239,20 @@ __global__ __launch_bounds__(kBlock) void k_finish_transpose(
   for (int w = 1; w < kFinLanes; w <<= 1)
     for (int k = 0; k < 2; ++k) S[k] += __shfl_xor(S[k], w, kFinLanes);
   if (j >= N || u != 0) return;
-  y[j] = 0.5 * z[j] + 0.5 * z[N + j] + S[0];
-  y[N + j] = S[1];
+  const int o = perm ? perm[j] : j;
+  y[o] = 0.5 * z[j] + 0.5 * z[N + j] + S[0];
+  y[N + o] = S[1];
 }
 
 }  // namespace
+
+void launch_gather_pack(hipStream_t s, int N, int nf, double eps_ratio, const int *perm,
+                        const double *geo, const double *user, double *x, double *src64,
+                        float *src32) {
+  hipLaunchKernelGGL(k_gather_pack, dim3((N + 255) / 256), dim3(256), 0, s, N, nf, eps_ratio,
+                     perm, geo, user, x, src64, src32);
+  PBMP_HIP(hipGetLastError());
+}
 
 void launch_pack_strengths(hipStream_t s, int N, int nf, double eps_ratio,
                            const double *geo, const double *x, double *src64,
@@ -268,10 +300,10 @@ void launch_p2p_direct(hipStream_t s, bool fp64, int nf, int N, int Nt,
 
 void launch_finish(hipStream_t s, int N, int nchunk, const double *part,
                    const int *rowptr, const int *col, const double *val,
-                   const double *x, double eps_ratio, double *y) {
+                   const double *x, double eps_ratio, const int *perm, double *y) {
   const int rows = kBlock / kFinLanes;
   hipLaunchKernelGGL(k_finish, dim3((N + rows - 1) / rows), dim3(kBlock), 0, s, N,
-                     nchunk, part, rowptr, col, val, x, eps_ratio, y);
+                     nchunk, part, rowptr, col, val, x, eps_ratio, perm, y);
   PBMP_HIP(hipGetLastError());
 }
 
@@ -280,7 +312,8 @@ void launch_transpose(hipStream_t s, bool fp64, int nf, int N,
                       const double *geo, const float *tgt32, const double *z,
                       double kappa, int nchunk, double *part,
                       const int *trow, const int *tcol, const int *tent,
-                      const double *val, double eps_ratio, double *y, bool floor_r2) {
+                      const double *val, double eps_ratio, const int *perm, double *y,
+                      bool floor_r2) {
   const int chunk = (N + nchunk - 1) / nchunk;
   const dim3 grid((N + 63) / 64, nchunk);
 #define PBMP_P2PT(T, NFV, FL)                                                                 \
@@ -298,7 +331,7 @@ void launch_transpose(hipStream_t s, bool fp64, int nf, int N,
   PBMP_HIP(hipGetLastError());
   const int rows = kBlock / kFinLanes;
   hipLaunchKernelGGL(k_finish_transpose, dim3((N + rows - 1) / rows), dim3(kBlock), 0, s,
-                     N, nchunk, part, trow, tcol, tent, val, z, eps_ratio, y);
+                     N, nchunk, part, trow, tcol, tent, val, z, eps_ratio, perm, y);
   PBMP_HIP(hipGetLastError());
 }
 

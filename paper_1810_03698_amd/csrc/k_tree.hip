@@ -645,7 +645,7 @@ __global__ __launch_bounds__(kFinBlock) void k_finish_slots(
     int N, const int *__restrict__ tslots, const double *__restrict__ part,
     const int *__restrict__ rowptr, const int *__restrict__ col,
     const double *__restrict__ val, const double *__restrict__ x, double eps_ratio,
-    double *__restrict__ y) {
+    const int *__restrict__ perm, double *__restrict__ y) {
   const int t = blockIdx.x * kFinBlock + (int)threadIdx.x;
   const int i = t / kFinLanes, u = t % kFinLanes;
   const bool live = i < N;
@@ -670,8 +670,9 @@ __global__ __launch_bounds__(kFinBlock) void k_finish_slots(
   }
   if (!live || u != 0) return;
   const double ph = x[i];
-  y[i] = 0.5 * ph + S[0];
-  y[N + i] = 0.5 * ph + S[1];
+  const int o = perm ? perm[i] : i;
+  y[o] = 0.5 * ph + S[0];
+  y[N + o] = 0.5 * ph + S[1];
 }
 
 template <class T, int P>
@@ -1025,26 +1026,37 @@ __global__ __launch_bounds__(64) void k_l2p(const int *__restrict__ leaves,
 }
 
 // (A^T z) from the transposed partial slots, the transposed near/self
-// correction and the identity terms
-__global__ void k_finish_T_slots(int N, const int *__restrict__ tslotsT,
-                                 const double *__restrict__ part, const int *__restrict__ trow,
-                                 const int *__restrict__ tcol, const int *__restrict__ tent,
-                                 const double *__restrict__ val, const double *__restrict__ z,
-                                 double eps_ratio, double *__restrict__ y) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= N) return;
+// correction and the identity terms; lanes per row as in k_finish_slots
+__global__ __launch_bounds__(kFinBlock) void k_finish_T_slots(
+    int N, const int *__restrict__ tslotsT, const double *__restrict__ part,
+    const int *__restrict__ trow, const int *__restrict__ tcol, const int *__restrict__ tent,
+    const double *__restrict__ val, const double *__restrict__ z, double eps_ratio,
+    const int *__restrict__ perm, double *__restrict__ y) {
+  const int t = blockIdx.x * kFinBlock + (int)threadIdx.x;
+  const int j = t / kFinLanes, u = t % kFinLanes;
+  const int jl = min(j, N - 1);
   double S[2] = {0.0, 0.0};
-  const int ns = tslotsT[j];
-  for (int c = 0; c < ns; ++c)
-    for (int k = 0; k < 2; ++k) S[k] += part[((size_t)c * 2 + k) * N + j];
-  for (int t = trow[j]; t < trow[j + 1]; ++t) {
-    const int i = tcol[t];
-    const size_t e = tent[t];
-    S[0] += val[4 * e + 1] * z[i] - val[4 * e + 3] * z[N + i];
-    S[1] += eps_ratio * val[4 * e + 2] * z[N + i] - val[4 * e] * z[i];
+  const int ns = tslotsT[jl];
+  for (int c = u; c < ns; c += kFinLanes)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) S[k] += part[((size_t)c * 2 + k) * N + jl];
+  const int e1 = trow[jl + 1];
+  for (int e = trow[jl] + u; e < e1; e += kFinLanes) {
+    const int i = tcol[e];
+    const double *v = val + 4 * (size_t)tent[e];
+    const double z1 = z[i], z2 = z[N + i];
+    S[0] += v[1] * z1 - v[3] * z2;
+    S[1] += eps_ratio * v[2] * z2 - v[0] * z1;
   }
-  y[j] = 0.5 * z[j] + 0.5 * z[N + j] + S[0];
-  y[N + j] = S[1];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    S[k] += __shfl_xor(S[k], 1, kFinLanes);
+    S[k] += __shfl_xor(S[k], 2, kFinLanes);
+  }
+  if (j >= N || u != 0) return;
+  const int o = perm ? perm[j] : j;
+  y[o] = 0.5 * z[j] + 0.5 * z[N + j] + S[0];
+  y[N + o] = S[1];
 }
 
 template <class T, int P>
@@ -1746,10 +1758,10 @@ void tree_apply(Tree &t, hipStream_t s, bool fp64, int nf, int N, const double *
 
 void launch_finish_slots(hipStream_t s, int N, const int *tslots, const double *part,
                          const int *rowptr, const int *col, const double *val,
-                         const double *x, double eps_ratio, double *y) {
+                         const double *x, double eps_ratio, const int *perm, double *y) {
   const int rows_per_block = kFinBlock / kFinLanes;
   hipLaunchKernelGGL(k_finish_slots, dim3((N + rows_per_block - 1) / rows_per_block),
-                     dim3(kFinBlock), 0, s, N, tslots, part, rowptr, col, val, x, eps_ratio, y);
+                     dim3(kFinBlock), 0, s, N, tslots, part, rowptr, col, val, x, eps_ratio, perm, y);
   PBMP_HIP(hipGetLastError());
 }
 
@@ -1778,15 +1790,16 @@ void tree_apply_transpose(Tree &t, hipStream_t s, bool fp64, int nf, int N, cons
                           const double *src64, const float *src32, const float *tgt32,
                           const double *z, double kappa, double *part, const int *trow,
                           const int *tcol, const int *tent, const double *val, double eps_ratio,
-                          double *y, bool floor_r2) {
+                          const int *perm, double *y, bool floor_r2) {
   if (fp64)
     tree_T_far_p<double>(t, s, nf, N, geo, src64, src64, geo, z, kappa, 0.0, eps_ratio, part,
                          floor_r2);
   else
     tree_T_far_p<float>(t, s, nf, N, geo, src64, src32, tgt32, z, (float)kappa,
                         (float)(-kappa * 1.4426950408889634), eps_ratio, part, floor_r2);
-  hipLaunchKernelGGL(k_finish_T_slots, dim3((N + 255) / 256), dim3(256), 0, s, N,
-                     t.d_tslotsT.p, part, trow, tcol, tent, val, z, eps_ratio, y);
+  const int rows = kFinBlock / kFinLanes;
+  hipLaunchKernelGGL(k_finish_T_slots, dim3((N + rows - 1) / rows), dim3(kFinBlock), 0, s, N,
+                     t.d_tslotsT.p, part, trow, tcol, tent, val, z, eps_ratio, perm, y);
   PBMP_HIP(hipGetLastError());
 }
 

@@ -38,6 +38,11 @@ void launch_pack_strengths(hipStream_t s, int N, int nf, double eps_ratio,
                            const double *geo, const double *x, double *src64,
                            float *src32);
 
+// x = user gathered with perm (both blocks of N) and its strengths packed.
+void launch_gather_pack(hipStream_t s, int N, int nf, double eps_ratio, const int *perm,
+                        const double *geo, const double *user, double *x, double *src64,
+                        float *src32);
+
 // Direct far-field sums over all panels of the source range, per target:
 // part[(chunk*2 + k)*Nt + i], the far field of the two rows of y = A x:
 // k = 0: K_L - V_L, k = 1: eps V_Y - K_Y.
@@ -52,10 +57,11 @@ void launch_p2p_direct(hipStream_t s, bool fp64, int nf, int N, int Nt,
                        int nchunk, double *part, bool floor_r2 = true);
 
 // y = A x from the far partials (summed over nchunk chunks in order), the
-// near/self CSR correction and the identity terms (eq. integral_eq).
+// near/self CSR correction and the identity terms (eq. integral_eq).  Row i
+// goes to y[perm[i]] where perm is not null (here and below).
 void launch_finish(hipStream_t s, int N, int nchunk, const double *part,
                    const int *rowptr, const int *col, const double *val,
-                   const double *x, double eps_ratio, double *y);
+                   const double *x, double eps_ratio, const int *perm, double *y);
 
 // z -> A^T z (direct): transposed far sums and the transposed near/self
 // correction (trow/tcol/tent: for column j the rows i and entry ids).
@@ -64,7 +70,8 @@ void launch_transpose(hipStream_t s, bool fp64, int nf, int N,
                       const double *geo, const float *tgt32, const double *z,
                       double kappa, int nchunk, double *part,
                       const int *trow, const int *tcol, const int *tent,
-                      const double *val, double eps_ratio, double *y, bool floor_r2);
+                      const double *val, double eps_ratio, const int *perm, double *y,
+                      bool floor_r2);
 
 // Right-hand side f[N] (eq. rhs_multipole) from sites (xyz[3M], q[M],
 // p[3M], Q9[9M]); fp64 selects FP64 pair terms, else FP32 pair terms with
@@ -187,7 +194,7 @@ void tree_apply_transpose(Tree &t, hipStream_t s, bool fp64, int nf, int N, cons
                           const double *src64, const float *src32, const float *tgt32,
                           const double *z, double kappa, double *part, const int *trow,
                           const int *tcol, const int *tent, const double *val, double eps_ratio,
-                          double *y, bool floor_r2);
+                          const int *perm, double *y, bool floor_r2);
 // Far-field part of the mesh adjoint with the treecode: d/d(collocation
 // points) gc [3N] and d/d(far nodes, normals, areas) gy [9N], gn [3N],
 // gA [N] of lambda . A x (assigned, not accumulated); part: the product's
@@ -199,6 +206,6 @@ void tree_mesh_adjoint_far(Tree &t, hipStream_t s, int nf, int N, const double *
 void launch_finish_slots(hipStream_t s, int N, const int *tslots,
                          const double *part, const int *rowptr, const int *col,
                          const double *val, const double *x, double eps_ratio,
-                         double *y);
+                         const int *perm, double *y);
 
 }  // namespace pbmp

@@ -44,6 +44,22 @@ std::vector<T> fetch(const T *p, size_t n, int where, hipStream_t s) {
   return h;
 }
 
+// whether [p, p + bytes) lies in one allocation of the current device that
+// kernels can address
+bool device_span(const void *p, size_t bytes) {
+  hipPointerAttribute_t a;
+  int dev = 0;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  const bool ok =
+      hipPointerGetAttributes(&a, p) == hipSuccess && a.type == hipMemoryTypeDevice &&
+      hipGetDevice(&dev) == hipSuccess && a.device == dev &&
+      hipMemGetAddressRange(&base, &size, const_cast<void *>(p)) == hipSuccess &&
+      (const char *)p + bytes <= (const char *)base + size && (uintptr_t)p % sizeof(double) == 0;
+  if (!ok) (void)hipGetLastError();
+  return ok;
+}
+
 bool finite_all(const std::vector<double> &v) {
   for (double x : v)
     if (!std::isfinite(x)) return false;
@@ -606,7 +622,7 @@ void Runtime::build_site_lists() {
 }
 
 // -------------------------------------------------------------- operator
-void Runtime::apply(const double *x, double *y, bool f64, bool packed) {
+void Runtime::apply(const double *x, double *y, bool f64, bool packed, const int *perm) {
   const int N = N_;
   const bool use64 = f64 || fp64();
   const double *val = (use64 && !fp64()) ? nval64_.p : nval_.p;
@@ -618,14 +634,14 @@ void Runtime::apply(const double *x, double *y, bool f64, bool packed) {
     tree_apply(*tree_, s_, use64, ru_.nf, N, geo_.p, src64_.p, src32_.p,
                tgt32_.p, o.kappa, o.eps_in / o.eps_out, part_.p, clock, floor_r2_);
     launch_finish_slots(s_, N, tree_->d_tslots.p, part_.p, nrow_.p, ncol_.p,
-                        val, x, o.eps_in / o.eps_out, y);
+                        val, x, o.eps_in / o.eps_out, perm, y);
   } else {
     hipEvent_t e0 = clock.on ? clock.begin(s_) : nullptr;
     launch_p2p_direct(s_, use64, ru_.nf, N, N, src64_.p, src32_.p, geo_.p,
                       tgt32_.p, o.kappa, p2p_chunks_, part_.p, floor_r2_);
     if (clock.on) clock.end(s_, e0, KernelClock::P2P, (double)N * N * ru_.nf);
     launch_finish(s_, N, p2p_chunks_, part_.p, nrow_.p, ncol_.p, val, x,
-                  o.eps_in / o.eps_out, y);
+                  o.eps_in / o.eps_out, perm, y);
   }
   clock.on = timed;
   ++matvecs_;
@@ -1044,16 +1060,34 @@ void Runtime::matvec_user(const double *x, double *y, int transpose, int where) 
     stern_matvec_user(x, y, where);
     return;
   }
-  to_internal(x, io_a_.p, 2, where);
+  // The kernels gather from and scatter to the caller's vectors themselves
+  // (three launches for a small direct product; the two permutations and two
+  // device copies were half of its time).  Vectors that are not whole device
+  // allocations of this process go through copies, which report them.
+  PBMP_REQUIRE(x != nullptr, PBMP_EARG, "null input");
+  PBMP_REQUIRE(y != nullptr, PBMP_EARG, "null output");
+  const size_t bytes = sizeof(double) * 2 * (size_t)N_;
+  const bool in_place = where == PBMP_DEVICE && device_span(x, bytes) && device_span(y, bytes);
+  if (!in_place)
+    PBMP_HIP(hipMemcpyAsync(tmp_.p, x, bytes,
+                            where == PBMP_DEVICE ? hipMemcpyDeviceToDevice
+                                                 : hipMemcpyHostToDevice, s_));
+  double *out = in_place ? y : io_b_.p;
   auto t0 = clk::now();
-  if (transpose) apply_transpose(io_a_.p, io_b_.p);
-  else apply(io_a_.p, io_b_.p);
+  launch_gather_pack(s_, N_, ru_.nf, o.eps_in / o.eps_out, d_perm_.p, geo_.p,
+                     in_place ? x : tmp_.p, io_a_.p, src64_.p, src32_.p);
+  if (transpose) apply_transpose(io_a_.p, out, false, d_perm_.p);
+  else apply(io_a_.p, out, false, true, d_perm_.p);
   if (clock.on) {
     sync();
     clock.matvec_ms += ms_since(t0);
     clock.matvec_calls += 1;
   }
-  to_user(io_b_.p, y, 2, where);
+  if (!in_place)
+    PBMP_HIP(hipMemcpyAsync(y, out, bytes,
+                            where == PBMP_DEVICE ? hipMemcpyDeviceToDevice
+                                                 : hipMemcpyDeviceToHost, s_));
+  sync();
 }
 
 void Runtime::rhs_user(const double *p, double *f, int where) {

@@ -136,8 +136,11 @@ class Runtime {
   // y = A x (internal order, device)
   // y = A x (transpose: A^T x); f64 forces the FP64 far field in mixed mode
   // packed: the strengths of x are already in the source records
-  void apply(const double *x, double *y, bool f64 = false, bool packed = false);
-  void apply_transpose(const double *x, double *y, bool f64 = false);
+  // perm (may be null): y in the order perm gives, e.g. the caller's
+  void apply(const double *x, double *y, bool f64 = false, bool packed = false,
+             const int *perm = nullptr);
+  void apply_transpose(const double *x, double *y, bool f64 = false,
+                       const int *perm = nullptr);
   void precond_T(const double *u, double *z);
   // GMRES on A x = b (device, internal order), x holds the initial guess.
   int gmres(const double *b, double *x, bool transpose, int *iters);
