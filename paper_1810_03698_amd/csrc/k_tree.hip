@@ -488,7 +488,7 @@ __global__ __launch_bounds__(64) void k_p2p_tasks(int ntask, const int *__restri
   const int t0 = tasks[4 * task], t1 = tasks[4 * task + 1];
   const int lb = tasks[4 * task + 2], le = tasks[4 * task + 3];
   const int slot = slots[task];
-  const LaneSplit ls = lane_split(t1 - t0);
+  const LaneSplit ls = lane_split(t1 - t0, kMaxTPT);
   switch (ls.tpt) {
 #define PBMP_BODY(K)                                                                        \
   p2p_task_body<T, NF, K, FLOOR>(src, tgt, N, t0, t1, ranges, lb, le, sc, slot, part, sh, ls.G, \
@@ -839,26 +839,19 @@ __global__ __launch_bounds__(64) void k_p2pT_tasks(int ntask, const int *__restr
   const int B = tasks[4 * task], lb = tasks[4 * task + 1], le = tasks[4 * task + 2];
   const int slot = tasks[4 * task + 3];
   const int s0 = range[2 * B], s1 = range[2 * B + 1];
-  // split for the sources (at most two panels per lane: records stay in registers)
-  const int ns = s1 - s0;
-  int G = 1, spt = min(2, (ns + 63) / 64);
-  float be = (float)ns / (64.0f * spt * ((ns + 64 * spt - 1) / (64 * spt)));
-  for (int g = 2; g <= 16; ++g) {
-    const int L = 64 / g, tp = (ns + L - 1) / L;
-    if (tp > 2) continue;
-    const float e = (float)(g * ns) / (64.0f * tp);
-    if (e > be) {
-      be = e;
-      G = g;
-      spt = tp;
-    }
+  // up to three panels per lane (two, three, four: 452, 368, 365 us in FP64 and
+  // 195, 156, 162 us in FP32 on 30420 panels: lane fill against registers)
+  constexpr int kMax = 3;
+  const LaneSplit ls = lane_split(s1 - s0, kMax);
+#define PBMP_BODY(K)                                                                           \
+  p2pT_body<T, NF, K, FLOOR>(src, tgt, z, geo, N, s0, s1, subs, lb, le, sc, eps_ratio, slot, part, \
+                             sh, ls.G, ls.L)
+  switch (ls.tpt) {
+    case 1: PBMP_BODY(1); break;
+    case 2: PBMP_BODY(2); break;
+    default: PBMP_BODY(kMax); break;
   }
-  if (spt == 1)
-    p2pT_body<T, NF, 1, FLOOR>(src, tgt, z, geo, N, s0, s1, subs, lb, le, sc, eps_ratio, slot,
-                        part, sh, G, 64 / G);
-  else
-    p2pT_body<T, NF, 2, FLOOR>(src, tgt, z, geo, N, s0, s1, subs, lb, le, sc, eps_ratio, slot,
-                        part, sh, G, 64 / G);
+#undef PBMP_BODY
 }
 
 // M2P^T: per task (box B, target sub-ranges) the partial local coefficients
@@ -897,10 +890,11 @@ __global__ __launch_bounds__(64) void k_m2pT_tasks(int ntask, const int *__restr
   });
 }
 
-// L_B, Cartesian [Laplace | Yukawa], from the partials of B's tasks (fixed
-// order, through the transposed map of k_harmonics); zero without tasks
+// L_B, Cartesian [Laplace | Yukawa], from the partials of B's tasks (four
+// interleaved runs of them, added in order; through the transposed map of
+// harmonic_words); zero without tasks
 template <int P>
-__global__ __launch_bounds__(128) void k_l_reduce(const int *__restrict__ count,
+__global__ __launch_bounds__(512) void k_l_reduce(const int *__restrict__ count,
                                                   const int *__restrict__ off,
                                                   const double *__restrict__ Lpart,
                                                   const int *__restrict__ koff,
@@ -908,19 +902,25 @@ __global__ __launch_bounds__(128) void k_l_reduce(const int *__restrict__ count,
                                                   const double *__restrict__ kc,
                                                   double *__restrict__ Lb) {
   constexpr int NK = Orders<P>::NK, NS = Orders<P>::NS;
+  static_assert(NS <= 128, "a lane per word");
+  __shared__ double run[4][NS];
   __shared__ double h[NS];
   const int B = blockIdx.x, t0 = off[B], nt = count[2 * B + 1];
-  for (int e = threadIdx.x; e < NS; e += 128) {
+  const int e = (int)threadIdx.x & 127, r = (int)threadIdx.x >> 7;
+  if (e < NS) {
     double v = 0.0;
-    for (int t = t0; t < t0 + nt; ++t) v += Lpart[(size_t)t * NS + e];
-    h[e] = v;
+#pragma unroll 4
+    for (int t = t0 + r; t < t0 + nt; t += 4) v += Lpart[(size_t)t * NS + e];
+    run[r][e] = v;
   }
   __syncthreads();
-  for (int k = threadIdx.x; k < NK; k += 128) {
+  if (r == 0 && e < NS) h[e] = run[0][e] + run[1][e] + run[2][e] + run[3][e];
+  __syncthreads();
+  for (int k = threadIdx.x; k < NK; k += 512) {
     double a = 0.0, b = 0.0;
-    for (int e = koff[k]; e < koff[k + 1]; ++e) {
-      a += kc[2 * e] * h[kpos[e]];
-      b += kc[2 * e + 1] * h[kpos[e] + 1];
+    for (int q = koff[k]; q < koff[k + 1]; ++q) {
+      a += kc[2 * q] * h[kpos[q]];
+      b += kc[2 * q + 1] * h[kpos[q] + 1];
     }
     Lb[(size_t)B * 2 * NK + k] = a;
     Lb[(size_t)B * 2 * NK + NK + k] = b;
@@ -947,19 +947,20 @@ void launch_locals(Tree &t, hipStream_t s, const T *tgt, const double *z, int N,
     }
 #undef PBMP_ML
   }
-  hipLaunchKernelGGL(k_l_reduce<P>, dim3(t.nbox), dim3(128), 0, s, t.d_m2pT_count.p,
+  hipLaunchKernelGGL(k_l_reduce<P>, dim3(t.nbox), dim3(512), 0, s, t.d_m2pT_count.p,
                      t.d_m2pT_off.p, t.d_Lpart.p, t.d_koff.p, t.d_kpos.p, t.d_kc.p, t.d_L.p);
 }
 
 // L2P at the leaves: every node takes the local expansions of all boxes
 // on its leaf's path to the root, each about its own centre (the direct
 // counterpart of shifting them down level by level), lanes over the leaf's
-// panels, FP64.  Boxes that no leaf accepted carry zero coefficients and
-// are skipped.
+// panels and a wave per node, FP64 (latency bound: one wave for all nodes took
+// 31 us on 30420 panels).  Boxes that no leaf accepted carry zero coefficients
+// and are skipped.
 constexpr int kMaxChain = 24;
 
 template <int P, int NF>
-__global__ __launch_bounds__(64) void k_l2p(const int *__restrict__ leaves,
+__global__ __launch_bounds__(64 * NF) void k_l2p(const int *__restrict__ leaves,
                                             const int *__restrict__ range,
                                             const int *__restrict__ parent,
                                             const int *__restrict__ ntask,
@@ -976,6 +977,7 @@ __global__ __launch_bounds__(64) void k_l2p(const int *__restrict__ leaves,
   __shared__ double lc[kMaxChain][3];
   __shared__ int chain[kMaxChain];
   __shared__ int nchain;
+  __shared__ double red[NF][64][2];
   const int B = leaves[blockIdx.x];
   if (threadIdx.x == 0) {
     int n = 0;
@@ -985,22 +987,24 @@ __global__ __launch_bounds__(64) void k_l2p(const int *__restrict__ leaves,
   }
   __syncthreads();
   const int nc = nchain;
-  for (int e = threadIdx.x; e < nc * 2 * NK; e += 64) {
+  for (int e = threadIdx.x; e < nc * 2 * NK; e += 64 * NF) {
     const int a = e / (2 * NK), k = e % (2 * NK);
     // the two sums a node takes: K_L - K_Y and eps V_Y - V_L
     const double *Lc = Lb + (size_t)chain[a] * 2 * NK;
     lp[a][k] = k < NK ? Lc[k] - Lc[NK + k] : eps_ratio * Lc[k] - Lc[k - NK];
   }
-  for (int e = threadIdx.x; e < nc * 3; e += 64) lc[e / 3][e % 3] = center[3 * chain[e / 3] + e % 3];
+  for (int e = threadIdx.x; e < nc * 3; e += 64 * NF) lc[e / 3][e % 3] = center[3 * chain[e / 3] + e % 3];
   __syncthreads();
-  for (int j = range[2 * B] + (int)threadIdx.x; j < range[2 * B + 1]; j += 64) {
-    const double *r = src64 + 16 * (size_t)j;
-    const double n[3] = {r[9], r[10], r[11]};
+  const int lane = (int)threadIdx.x & 63, q = (int)threadIdx.x >> 6;
+  for (int jb = range[2 * B]; jb < range[2 * B + 1]; jb += 64) {
+    const int j = jb + lane;
     double out[2] = {0.0, 0.0};
-    for (int a = 0; a < nc; ++a) {
-      for (int q = 0; q < NF; ++q) {
-        const double h[3] = {r[3 * q] - lc[a][0], r[3 * q + 1] - lc[a][1],
-                             r[3 * q + 2] - lc[a][2]};
+    if (j < range[2 * B + 1]) {
+      const double *r = src64 + 16 * (size_t)j;
+      const double n[3] = {r[9], r[10], r[11]};
+      const double y[3] = {r[3 * q], r[3 * q + 1], r[3 * q + 2]};
+      for (int a = 0; a < nc; ++a) {
+        const double h[3] = {y[0] - lc[a][0], y[1] - lc[a][1], y[2] - lc[a][2]};
         double mono[NC];
         mono[0] = 1.0;
 #pragma unroll
@@ -1019,9 +1023,18 @@ __global__ __launch_bounds__(64) void k_l2p(const int *__restrict__ leaves,
         }
       }
     }
-    const double wA = geo[6 * (size_t)N + j] * kInv4PiT / NF;
-    const int slot = tslotsT[j] - 1;
-    for (int k = 0; k < 2; ++k) part[((size_t)slot * 2 + k) * N + j] = wA * out[k];
+    __syncthreads();
+    for (int c = 0; c < 2; ++c) red[q][lane][c] = out[c];
+    __syncthreads();
+    if (q == 0 && j < range[2 * B + 1]) {
+      const double wA = geo[6 * (size_t)N + j] * kInv4PiT / NF;
+      const int slot = tslotsT[j] - 1;
+      for (int c = 0; c < 2; ++c) {
+        double v = red[0][lane][c];
+        for (int w = 1; w < NF; ++w) v += red[w][lane][c];
+        part[((size_t)slot * 2 + c) * N + j] = wA * v;
+      }
+    }
   }
 }
 
@@ -1077,7 +1090,7 @@ void tree_T_far(Tree &t, hipStream_t s, int nf, int N, const double *geo,
   // M2P^T with per-box sums, L2P at the leaves
   launch_locals<T, P>(t, s, tgt, z, N, kappa, nk);
   if (nf == 3)
-    hipLaunchKernelGGL((k_l2p<P, 3>), dim3(t.nleaf), dim3(64), 0, s, t.d_leaves.p,
+    hipLaunchKernelGGL((k_l2p<P, 3>), dim3(t.nleaf), dim3(192), 0, s, t.d_leaves.p,
                        t.d_range.p, t.d_parent.p, t.d_m2pT_count.p, t.d_center.p, t.d_L.p,
                        src64, geo, t.d_tslotsT.p, N, eps_ratio, part);
   else

@@ -23,18 +23,18 @@ struct LaneSplit {
   int G, L, tpt;
 };
 
-// Lanes of a one-wave P2P task for nt targets: G groups of L = 64 / G lanes,
-// tpt targets per lane, maximising the useful fraction G nt / (64 tpt) with
-// tpt <= PBMP_P2P_MAXTPT (ties: fewer groups; more than 64 * MAXTPT
-// targets take several passes with G = 1)
-__host__ __device__ inline LaneSplit lane_split(int nt) {
-  const int t1 = (nt + 63) / 64;
-  LaneSplit best{1, 64, t1 < PBMP_P2P_MAXTPT ? t1 : PBMP_P2P_MAXTPT};
-  float be = (float)nt / (64.0f * best.tpt * ((nt + 64 * best.tpt - 1) / (64 * best.tpt)));
+// Lanes of a one-wave P2P task for nt targets (or sources, transposed): G groups
+// of L = 64 / G lanes, tpt targets per lane, maximising the useful fraction
+// G nt / (64 tpt) with tpt <= maxtpt (ties: fewer groups; more than 64 maxtpt
+// targets take several passes of equal size with G = 1)
+__host__ __device__ inline LaneSplit lane_split(int nt, int maxtpt) {
+  const int passes = (nt + 64 * maxtpt - 1) / (64 * maxtpt);
+  LaneSplit best{1, 64, (nt + 64 * passes - 1) / (64 * passes)};
+  float be = (float)nt / (64.0f * best.tpt * passes);
   for (int G = 2; G <= 16 * PBMP_P2P_GROUPS; ++G) {
     const int L = 64 / G;
     const int tpt = (nt + L - 1) / L;
-    if (tpt > PBMP_P2P_MAXTPT) continue;
+    if (tpt > maxtpt) continue;
     const float e = (float)(G * nt) / (64.0f * tpt);
     if (e > be) {
       be = e;
