@@ -139,6 +139,8 @@ __global__ __launch_bounds__(kGradBlock) void k_op_grad_source(
     const double t = grad_sum(ay[k], red);
     if (out) gy[9 * j + k] = w * A * t;
   }
+  if (out)  // the readout's part is added to all nine
+    for (int k = 3 * NF; k < 9; ++k) gy[9 * j + k] = 0.0;
   for (int d = 0; d < 3; ++d) {
     const double t = grad_sum(an[d], red);
     if (out) gn[3 * j + d] = w * A * t;
@@ -187,7 +189,10 @@ __global__ __launch_bounds__(64) void k_near_grad(
     } else {
       panel_rule_t<D>(v, n, A, c, ru.nn, ru.nb, ru.nw, kappa, fine);
     }
-    panel_rule_t<D>(v, n, A, c, ru.nf, ru.fb, ru.fw, kappa, coarse);
+    if (SELF && ru.nf == 1)  // the only node is the target: the product has no term
+      coarse[0] = coarse[1] = coarse[2] = coarse[3] = D(0.0);
+    else
+      panel_rule_t<D>(v, n, A, c, ru.nf, ru.fb, ru.fw, kappa, coarse);
     const D E = a1 * (fine[1] - coarse[1]) - a2 * (fine[0] - coarse[0]) -
                 a3 * (fine[3] - coarse[3]) + a4 * (fine[2] - coarse[2]);
     for (int k = 0; k < 12; ++k) ge[12 * (size_t)e + k] = E.d[k];
