@@ -52,7 +52,7 @@ TRAFFIC = {
         "write_scale": 1.0, "sha": "d7b0216f1432cb9e"},
 }
 TRAFFIC_SOURCES = {
-    "treecode": ["k_tree.hip", "pair.hpp", "tree.hpp", "k_treebuild.hip"],
+    "treecode": ["k_tree.hip", "harmonic.hpp", "pair.hpp", "tree.hpp", "k_treebuild.hip"],
     "direct": ["k_p2p.hip", "pair.hpp"],
 }
 
@@ -94,15 +94,16 @@ CAL_SCF = (1e-2, 1e-3, 1e-4)
 
 
 def _m2p_flops(order):
-    """FLOP per (target, box) pair of the implemented M2P evaluation, not
-    counting products with 1, terms with 0 or additions to 0.  Per
-    coefficient k != 0 of the Laplace/Yukawa recurrences, which run to
-    degree P + 1 (n1, n2 = number of k_i >= 1, >= 2): 6 n1 - 3 for the three
-    sums over the first-lower coefficients, 3 (n2 - 1) for the three over
-    the second-lower ones, and 5 (|k| = 1), 7 (no k_i >= 2) or 13 to combine
-    them; 8 per coefficient of degree <= P for the four moment dot products
-    and 4 per coefficient of degree P + 1 (double layer only); 14 for the
-    pair set-up.  P = 4: 1546, P = 5: 2451."""
+    """FLOP per (target, box) pair of an M2P evaluation by the Cartesian
+    recurrences (the work the harmonic form replaces), not counting products
+    with 1, terms with 0 or additions to 0. Per coefficient k != 0 of the
+    Laplace/Yukawa recurrences, which run to degree P + 1 (n1, n2 = number of
+    k_i >= 1, >= 2): 6 n1 - 3 for the three sums over the first-lower
+    coefficients, 3 (n2 - 1) for the three over the second-lower ones, and 5
+    (|k| = 1), 7 (no k_i >= 2) or 13 to combine them; 8 per coefficient of
+    degree <= P for the four moment dot products and 4 per coefficient of
+    degree P + 1 (double layer only); 14 for the pair set-up. P = 4: 1546, P =
+    5: 2451."""
     total = 14
     for s in range(order + 2):
         for i in range(s, -1, -1):
@@ -115,6 +116,21 @@ def _m2p_flops(order):
                 n2 = sum(e >= 2 for e in k)
                 total += 6 * n1 - 3 + (3 * (n2 - 1) if n2 else 0)
                 total += 5 if s == 1 else (7 if n2 == 0 else 13)
+    return total
+
+
+def _m2p_flops_harmonic(order):
+    """FLOP per (target, box) pair of the implemented M2P evaluation, the
+    series regrouped by solid harmonics of degree <= L = P + 1: 17 for the
+    pair set-up and the unit vector; per harmonic (l, m >= 1) 8 to add its two
+    parts to both kernels, 2 (l > m) for the parts and 3 (l > m + 1) for the
+    recurrence; 6 per m >= 2 for the azimuthal factors; per (l, 0) 2 (l >= 1)
+    and 3 (l >= 2); 7 L + 3 for the two radial sums.  P = 4: 259, P = 5: 347."""
+    L = order + 1
+    total = 17 + 7 * L + 3 + 6 * (L - 1) + 2 * L + 3 * (L - 1)
+    for m in range(1, L + 1):
+        for l in range(m, L + 1):
+            total += 8 + (2 if l > m else 0) + (3 if l > m + 1 else 0)
     return total
 
 
@@ -408,7 +424,7 @@ def main():
         per_launch = ALG_FLOP_PER_PAIR * st["p2p_pairs"] / max(1, st["p2p_launches"])
     else:
         name, avg_ms = "m2p", m2p_avg
-        per_launch = _m2p_flops(order) * st["m2p_pairs"] / max(1, st["m2p_launches"])
+        per_launch = _m2p_flops_harmonic(order) * st["m2p_pairs"] / max(1, st["m2p_launches"])
     achieved = per_launch / (avg_ms * 1e-3) / 1e12
     # the far field runs in FP32 in mixed precision and in FP64 otherwise
     peak = PEAK_FP32_VECTOR if args.precision == "mixed" else PEAK_FP64_VECTOR
@@ -426,9 +442,10 @@ def main():
                 "p2p_pairs_per_launch": st["p2p_pairs"] / max(1, st["p2p_launches"]),
                 "m2p_pairs_per_launch": st["m2p_pairs"] / max(1, st["m2p_launches"]),
                 "p2p_tflops_alg": ALG_FLOP_PER_PAIR * st["p2p_pairs"] / max(1e-30, st["p2p_ms"]) / 1e9,
-                "m2p_tflops_alg": _m2p_flops(order) * st["m2p_pairs"]
+                "m2p_tflops_alg": _m2p_flops_harmonic(order) * st["m2p_pairs"]
                 / max(1e-30, st["m2p_ms"]) / 1e9,
-                "m2p_flop_per_pair": _m2p_flops(order)}
+                "m2p_flop_per_pair": _m2p_flops_harmonic(order),
+                "m2p_flop_per_pair_recurrences": _m2p_flops(order)}
     executed = {"p2p_pairs_per_s": st["p2p_pairs"] / elapsed,
                 "m2p_target_box_pairs_per_s": st["m2p_pairs"] / elapsed,
                 "p2p_pairs_per_product": st["p2p_pairs"] / max(1, st["p2p_launches"]),

@@ -17,7 +17,9 @@
 // h^(|k|-1), so its series is carried one degree further and both layers
 // are truncated at degree P in h.  Moments are formed in FP64: those of the
 // leaves from their nodes, those of the accepted boxes above the leaves
-// from the leaf moments by exact binomial shifts.
+// from the leaf moments by exact binomial shifts.  The products evaluate the
+// two series regrouped by solid harmonics (harmonic.hpp), from words made of
+// a box's finished moments; the recurrences serve the vertex gradient.
 #include <cmath>
 
 #include <type_traits>
@@ -30,7 +32,6 @@
 namespace pbmp {
 
 namespace {
-
 
 // Multi-indices |k| <= P ordered by degree, then x exponent descending,
 // then y exponent descending; m1/m2: positions of k - e_i and k - 2 e_i.

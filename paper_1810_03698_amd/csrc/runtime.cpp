@@ -650,8 +650,8 @@ void Runtime::apply(const double *x, double *y, bool f64, bool packed, const int
 // ----------------------------------------------------------------- GMRES
 // Right-preconditioned restarted GMRES with classical Gram-Schmidt applied
 // twice, the true residual recomputed at every restart.  The Arnoldi steps
-// run on the device; each step's Hessenberg column is copied to pinned host
-// memory and rotated there (Givens).  The host launches the next step
+// run on the device; each step's kernels write its Hessenberg column to pinned
+// host memory, where it is rotated (Givens).  The host launches the next step
 // before it has read the current one's column whenever the residual
 // estimate cannot reach the tolerance within the current step, so the
 // device never waits for the host: with r the last known residual and rho
