@@ -45,11 +45,11 @@ COPY_BYTES = 256 << 20
 # reported null).
 TRAFFIC = {
     ("treecode", "m2p", "globule_5000", "mixed"): {
-        "fetch_kib": 4612.76, "fetch_scale": 0.50008, "write_kib": 139723.00,
-        "write_scale": 1.0, "sha": "d7b0216f1432cb9e"},
+        "fetch_kib": 21633.64, "fetch_scale": 0.50008, "write_kib": 89270.93,
+        "write_scale": 1.0, "sha": "c0f878bfe186c8eb"},
     ("treecode", "p2p", "globule_5000", "mixed"): {
-        "fetch_kib": 16974.85, "fetch_scale": 0.50008, "write_kib": 198625.44,
-        "write_scale": 1.0, "sha": "d7b0216f1432cb9e"},
+        "fetch_kib": 14931.59, "fetch_scale": 0.50008, "write_kib": 99243.84,
+        "write_scale": 1.0, "sha": "c0f878bfe186c8eb"},
 }
 TRAFFIC_SOURCES = {
     "treecode": ["k_tree.hip", "harmonic.hpp", "pair.hpp", "tree.hpp", "k_treebuild.hip"],
