@@ -46,10 +46,10 @@ COPY_BYTES = 256 << 20
 TRAFFIC = {
     ("treecode", "m2p", "globule_5000", "mixed"): {
         "fetch_kib": 21633.64, "fetch_scale": 0.50008, "write_kib": 89270.93,
-        "write_scale": 1.0, "sha": "c0f878bfe186c8eb"},
+        "write_scale": 1.0, "sha": "76027f060d188f75"},
     ("treecode", "p2p", "globule_5000", "mixed"): {
         "fetch_kib": 14931.59, "fetch_scale": 0.50008, "write_kib": 99243.84,
-        "write_scale": 1.0, "sha": "c0f878bfe186c8eb"},
+        "write_scale": 1.0, "sha": "76027f060d188f75"},
 }
 TRAFFIC_SOURCES = {
     "treecode": ["k_tree.hip", "harmonic.hpp", "pair.hpp", "tree.hpp", "k_treebuild.hip"],

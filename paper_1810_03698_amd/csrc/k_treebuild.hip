@@ -680,7 +680,7 @@ void Tree::build_device(int N, int nf, const uint64_t *key, const double *geo,
   ListOut lo{};
   lo.count = cnt.p;
   hipLaunchKernelGGL(k_lists<false>, grid_for(nleaf, 64), dim3(64), 0, s, nleaf, d_leaves.p,
-                     view(), d_center.p, d_radius.p, prm.theta, kP2PTaskWork,
+                     view(), d_center.p, d_radius.p, prm.theta, p2p_task_work(N),
                      m2p_task_work(N), lo);
   PBMP_HIP(hipGetLastError());
   int tot[5];
@@ -718,7 +718,7 @@ void Tree::build_device(int N, int nf, const uint64_t *key, const double *geo,
   lo.mslot = d_m2p_slot.p;
   lo.slots_of_box = slots_of_box.p;
   hipLaunchKernelGGL(k_lists<true>, grid_for(nleaf, 64), dim3(64), 0, s, nleaf, d_leaves.p,
-                     view(), d_center.p, d_radius.p, prm.theta, kP2PTaskWork,
+                     view(), d_center.p, d_radius.p, prm.theta, p2p_task_work(N),
                      m2p_task_work(N), lo);
   d_tslots.alloc(N);
   hipLaunchKernelGGL(k_target_slots, grid_for(N), dim3(256), 0, s, N, owner.p, slots_of_box.p,
@@ -846,7 +846,7 @@ void Tree::build_transposed(int N, const int *owner, Dbuf<char> &tmp) {
     PBMP_HIP(hipStreamSynchronize(s));
   };
   Dbuf<int> p2pT_off;
-  one(d_p2p_ptr, d_p2p_box, n_p2p_entries, kP2PTaskWork, true, d_p2pT_sub, d_p2pT_task,
+  one(d_p2p_ptr, d_p2p_box, n_p2p_entries, p2p_task_work(N), true, d_p2pT_sub, d_p2pT_task,
       d_p2pT_count, p2pT_off, n_p2pT_tasks);
   one(d_m2p_ptr, d_m2p_box, n_m2p_entries, kM2PTChunkTargets, false, d_m2pT_sub, d_m2pT_task,
       d_m2pT_count, d_m2pT_off, n_m2pT_tasks);

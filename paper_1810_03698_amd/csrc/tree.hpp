@@ -50,12 +50,21 @@ constexpr int kM2PTaskBoxes = 64;
 constexpr int kM2PChunkBoxes = 16;
 constexpr int kM2PStageBytes = 8192;
 // work per task, in target-source pairs: a leaf of nt targets gets tasks of
-// about kP2PTaskWork / nt source panels (P2P) and m2p_task_work(N) / nt boxes
-// (M2P, at most kM2PTaskBoxes), so that tasks take about the same time
-#ifndef PBMP_P2P_WORK
-#define PBMP_P2P_WORK 12288
-#endif
-constexpr int kP2PTaskWork = PBMP_P2P_WORK;
+// about p2p_task_work(N) / nt source panels (P2P) and m2p_task_work(N) / nt
+// boxes (M2P, at most kM2PTaskBoxes), so that tasks take about the same time.
+//
+// P2P: a surface of N panels has some 3500 N panel pairs in leaves of 300 and
+// the chip holds some 5000 waves of the kernel (LDS), so 12288 pairs per task
+// leave 20480 panels barely one task per wave and 28880 a second round half
+// full; smaller tasks fill it and shorten the tail until their slots cost the
+// finish kernel more (whole products at 4096, 6144, 8192, 12288 pairs: 20480
+// panels in FP32 191, 195, 193, 207 us; 28880 252, 251, 258, 263 us; 30420
+// transposed in FP64 413, 418, 427, 440 us; 60500 in FP32 355, 349, 345, 352 us
+// and transposed in FP64 811, 737, 713, 718 us; 144500, kernels alone, 1346,
+// 1322, 1310, 1297 us).  Below 14336 panels it is 2048 (5120 panels in leaves of
+// 50 at 1024, 2048, 4096, 12288: 95, 97, 107, 116 us in FP32, of 300 in FP64 138,
+// 136, 134, 150 us).
+inline int p2p_task_work(int N) { return N / 7 < 2048 ? 2048 : N / 7 > 12288 ? 12288 : N / 7; }
 // A surface of N panels has 100-200 N M2P pairs: N / 48 per task gives the
 // largest ones some 8000 tasks (eight waves per SIMD, short tail) without more
 // partial-sum slots than that needs (144500 panels: N / 24, 48, 96 took 163,
