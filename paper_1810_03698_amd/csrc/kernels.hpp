@@ -46,9 +46,9 @@ void launch_gather_pack(hipStream_t s, int N, int nf, double eps_ratio, const in
 // Direct far-field sums over all panels of the source range, per target:
 // part[(chunk*2 + k)*Nt + i], the far field of the two rows of y = A x:
 // k = 0: K_L - V_L, k = 1: eps V_Y - K_Y.
-// floor_r2: FP32 pairs closer than 1e-4 A add nothing (needed only for the
-// one-node rule, or panels small enough for a node and a centroid to
-// coincide in FP32).
+// floor_r2: pairs closer than 1e-4 A (FP32) or 1e-10 A (FP64) add nothing
+// (needed only for the one-node rule, sheets in contact, or panels small enough
+// for a node and a centroid to coincide in FP32).
 // nchunk: source chunks, direct_chunks(N).
 int direct_chunks(int N);
 void launch_p2p_direct(hipStream_t s, bool fp64, int nf, int N, int Nt,

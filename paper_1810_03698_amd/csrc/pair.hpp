@@ -11,15 +11,17 @@ namespace pbmp {
 
 // FP32 cut-off on r^2 (r < 1e-4 A): such a pair adds nothing.  Pairs that
 // close only occur between a panel and itself (the one-node rule puts the
-// node on the centroid) or a near neighbour, and the near correction removes
-// exactly the value the product added, so skipping them is exact; it keeps
-// coincident FP32 points finite without 1/r-sized terms in FP32 sums.
+// node on the centroid), a near neighbour, or a panel of another sheet in
+// contact, and the near correction removes exactly the value the product added,
+// so skipping them is exact; it keeps coincident FP32 points finite without
+// 1/r-sized terms in FP32 sums.
 constexpr float kMinR2f = 1e-8f;
-// The FP64 products skip pairs closer than 1e-10 A: only a one-node rule's
-// node on its own panel's centroid comes that close (the node and the
-// centroid are computed with different roundings, so they need not
-// coincide exactly), since a node is at least a sixth of an altitude from
-// every other panel's centroid.
+// The FP64 products skip pairs closer than 1e-10 A: a one-node rule's node on
+// its own panel's centroid (the node and the centroid are computed with
+// different roundings, so they need not coincide exactly), or a node on a
+// centroid of another sheet in contact; from every other centroid of its own
+// sheet a node is at least a sixth of an altitude away.  A mesh where no node
+// comes near either cut-off takes the kernels without the test (FLOOR false).
 constexpr double kMinR2d = 1e-20;
 
 // 1/sqrt(rr) in FP64: the hardware estimate y0 (1 - rr y0^2 = e, |e| < 2^-23

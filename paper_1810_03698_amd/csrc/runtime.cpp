@@ -116,6 +116,57 @@ struct Grid {
 
 }  // namespace
 
+namespace {
+
+// Whether a far node of any panel lies within `dist` of another panel's
+// centroid.  Centroids hashed by cells of 16 dist, so that a node looks into
+// one or two of them (5120 panels 0.6 ms, 81920 11 ms); geo is the SoA [7N] geometry.
+bool node_meets_centroid(int N, const std::vector<double> &geo, const std::vector<double> &verts,
+                         const std::vector<int> &tri, const RuleArgs &ru, double dist) {
+  const double side = 16.0 * dist;
+  size_t size = 64;
+  while (size < 2 * (size_t)N) size *= 2;
+  auto slot = [&](int64_t a, int64_t b, int64_t c) {
+    uint64_t h = (uint64_t)a * 0x9E3779B97F4A7C15ull + (uint64_t)b * 0xC2B2AE3D27D4EB4Full +
+                 (uint64_t)c * 0x165667B19E3779F9ull;
+    h ^= h >> 32;
+    return (size_t)(h * 0x9E3779B97F4A7C15ull >> 20) & (size - 1);
+  };
+  auto cell = [&](double x) { return (int64_t)std::floor(x / side); };
+  std::vector<int> head(size, -1), next(N);
+  for (int i = 0; i < N; ++i) {
+    const size_t h = slot(cell(geo[i]), cell(geo[N + i]), cell(geo[2 * (size_t)N + i]));
+    next[i] = head[h];
+    head[h] = i;
+  }
+  for (int j = 0; j < N; ++j)
+    for (int q = 0; q < ru.nf; ++q) {
+      double y[3];
+      int64_t lo[3], hi[3];
+      for (int d = 0; d < 3; ++d) {
+        y[d] = 0.0;
+        for (int k = 0; k < 3; ++k) y[d] += ru.fb[q][k] * verts[3 * (size_t)tri[3 * (size_t)j + k] + d];
+        lo[d] = cell(y[d] - dist);
+        hi[d] = cell(y[d] + dist);
+      }
+      for (int64_t a = lo[0]; a <= hi[0]; ++a)
+        for (int64_t b = lo[1]; b <= hi[1]; ++b)
+          for (int64_t c = lo[2]; c <= hi[2]; ++c)
+            for (int i = head[slot(a, b, c)]; i >= 0; i = next[i]) {
+              if (i == j) continue;
+              double r2 = 0.0;
+              for (int d = 0; d < 3; ++d) {
+                const double x = geo[(size_t)d * N + i] - y[d];
+                r2 += x * x;
+              }
+              if (r2 <= dist * dist) return true;
+            }
+    }
+  return false;
+}
+
+}  // namespace
+
 // ------------------------------------------------------------ clock
 hipEvent_t KernelClock::begin(hipStream_t s) {
   hipEvent_t e;
@@ -362,12 +413,14 @@ void Runtime::set_mesh(int64_t nv, const double *verts, int64_t nt,
   for (int j = 0; j < N; ++j)
     PBMP_REQUIRE(h_geo_[6 * (size_t)N + j] > 1e-12, PBMP_EMESH,
                  "panel with area <= 1e-12 A^2");
-  // The three far nodes are interior: a node lies at least (smallest
-  // altitude)/6 from its panel's boundary, hence from every other panel's
-  // centroid, and a third of a median from its own.  When that exceeds 1e-4 A
-  // plus the FP32 rounding of the coordinates, no FP32 pair distance can
-  // fall below the cut-off and the product may skip the test.  The one-node
-  // rule puts the node on its own centroid, so it always needs the test.
+  // Whether the products have to test for a node on its target (kMinR2f,
+  // kMinR2d).  The three far nodes are interior: a node lies at least (smallest
+  // altitude)/6 from its panel's boundary, hence from the centroid of every
+  // other panel of its sheet, and a third of a median from its own.  When that
+  // exceeds 1e-4 A plus the FP32 rounding of the coordinates, and no node comes
+  // that close to a centroid of another sheet in contact, no pair distance of
+  // either precision can fall below the cut-off.  The one-node rule puts the
+  // node on its own centroid, so it always needs the test.
   {
     double min_alt = 1e300, max_abs = 0.0;
     for (int j = 0; j < N; ++j) {
@@ -384,10 +437,11 @@ void Runtime::set_mesh(int64_t nv, const double *verts, int64_t nt,
       }
       min_alt = std::min(min_alt, 2.0 * h_geo_[6 * (size_t)N + j] / std::sqrt(len2));
     }
+    const double dist = 1e-4 + 1e-6 * max_abs;
     // (also where kappa r could leave the range of the FP64 exponential's
     // unguarded argument reduction)
-    floor_r2_ = o.gauss_far == 1 || !(min_alt / 6.0 > 1e-4 + 1e-6 * max_abs) ||
-                !(o.kappa * 4.0 * max_abs < 1e6);
+    floor_r2_ = o.gauss_far == 1 || !(min_alt / 6.0 > dist) || !(o.kappa * 4.0 * max_abs < 1e6) ||
+                node_meets_centroid(N, h_geo_, h_verts_, h_tri_, ru_, dist);
   }
   build_near_lists();
   // --- tree

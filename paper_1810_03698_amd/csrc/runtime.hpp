@@ -103,7 +103,7 @@ class Runtime {
   Dbuf<int> trow_, tcol_;  // transposed near structure (entry ids)
   Dbuf<int> tent_;
   bool tree_active_ = false;
-  bool floor_r2_ = true;  // FP32 distance cut-off needed (one-node rule, tiny panels)
+  bool floor_r2_ = true;  // distance cut-off needed (one-node rule, tiny panels, sheets in contact)
   std::unique_ptr<Tree> tree_;
 
   // ---- sites ----

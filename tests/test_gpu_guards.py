@@ -1,0 +1,73 @@
+"""Products where a guard of the pair terms decides: sheets in contact whose far
+nodes fall on other panels' centroids.
+
+Tolerances: as for the kernel edges, 1e-12 (FP64) and 2e-5 (FP32 far field) of
+the largest entry.
+"""
+
+import numpy as np
+import pytest
+
+from oracle import bie
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"fp64": 1e-12, "mixed": 2e-5}
+
+
+def _solver(verts, tris, **kw):
+    from paper_1810_03698_amd import Solver
+    args = dict(eps_in=1.0, eps_out=80.0, kappa=0.125, mode="direct", precision="fp64")
+    args.update(kw)
+    s = Solver(**args)
+    s.set_mesh(verts, tris)
+    return s
+
+
+def _worst(got, ref):
+    return np.abs(got - ref).max() / np.abs(ref).max()
+
+
+# A tetrahedron and another on top of the same face.  The second one's face is
+# cut at the midpoints of two edges: a corner triangle, whose centroid is the
+# first one's far node (2/3, 1/6, 1/6), and two more, whose centroids are nobody's
+# node in either rule.
+_FACE = np.array([[0.0, 0.0, 0.0], [4.0, 0.0, 0.0], [1.0, 3.5, 0.0]])
+
+
+def _touching(corners, below, above):
+    v0, v1, v2 = corners
+    m1, m2 = 0.5 * (v0 + v1), 0.5 * (v0 + v2)
+    verts = np.array([v0, v1, v2, below, v0, v1, v2, m1, m2, above])
+    tris = np.array([[0, 1, 2], [1, 0, 3], [2, 1, 3], [0, 2, 3],
+                     [4, 8, 7], [7, 8, 6], [7, 6, 5],
+                     [4, 7, 9], [7, 5, 9], [5, 6, 9], [6, 8, 9], [8, 4, 9]], dtype=np.int32)
+    return verts, tris
+
+
+def _touching_mesh(kind):
+    """Dyadic coordinates, in which node and centroid may agree to the bit, or the
+    same turned and shifted, in which they differ by rounding."""
+    verts, tris = _touching(_FACE, np.array([1.5, 1.0, -3.0]), np.array([1.75, 1.25, 3.0]))
+    if kind == "turned":
+        q, _ = np.linalg.qr(np.random.default_rng(12).normal(size=(3, 3)))
+        q *= np.sign(np.linalg.det(q))
+        verts = verts @ q.T + np.array([0.7, -1.3, 2.1])
+    return verts, tris
+
+
+@pytest.mark.parametrize("mode", ["direct", "treecode"])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("kind", ["dyadic", "turned"])
+def test_products_on_sheets_in_contact(kind, precision, mode):
+    verts, tris = _touching_mesh(kind)
+    m = bie.Mesh(verts, tris, 0.125)
+    node = (m.verts[tris[0]] * [[2 / 3], [1 / 6], [1 / 6]]).sum(0)
+    assert np.linalg.norm(m.cen - node, axis=1).min() < 1e-14
+    A = bie.dense_system(m, 1.0, 80.0)
+    # all pairs directly in treecode mode too
+    s = _solver(verts, tris, precision=precision, mode=mode, theta=0.05, leaf_panels=8)
+    rng = np.random.default_rng(2)
+    x, z = rng.normal(size=2 * m.N), rng.normal(size=2 * m.N)
+    assert _worst(s.matvec(x), A @ x) < TOL[precision]
+    assert _worst(s.matvec(z, transpose=True), A.T @ z) < TOL[precision]
