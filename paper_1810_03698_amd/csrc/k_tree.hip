@@ -20,8 +20,8 @@
 // from the leaf moments by exact binomial shifts.  The products evaluate the
 // two series regrouped by solid harmonics (harmonic.hpp), from words made of
 // a box's finished moments; the recurrences serve the vertex gradient.
+#include <algorithm>
 #include <cmath>
-
 #include <type_traits>
 
 #include "harmonic.hpp"
@@ -1677,7 +1677,8 @@ void tree_upload_harmonics(Tree &t, double kappa, hipStream_t s) {
       const Col &cq = cols[q];
       ld dfact = 1.0L;  // (2l - 1)!!
       for (int u = 2 * cq.l - 1; u > 1; u -= 2) dfact *= u;
-      const ld kap = std::pow((ld)kappa, 2 * cq.j);
+      // finite in double; beyond 1e40 every e^{-kappa r} vanishes
+      const ld kap = std::pow((ld)std::min(kappa, 1e40), 2 * cq.j);
       for (int k = 0; k < dim; ++k) {
         const ld v = A[(size_t)q * 2 * dim + dim + k];
         if (std::fabs(v) < 1e-12L) continue;  // the true ones are simple fractions

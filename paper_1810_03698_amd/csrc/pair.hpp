@@ -127,6 +127,7 @@ __device__ __forceinline__ Screen<double> make_screen(double kappa, double *lds_
   return Screen<double>{kappa, kappa * -92.33248261689366, 1e5 / kappa, lds_table};
 }
 __device__ __forceinline__ Screen<float> make_screen(float kappa, double *) {
+  kappa = fminf(kappa, 1e18f);  // e^{-kappa r} = 0 beyond the cut-off; kappa / r stays finite
   Screen<float> sc{kappa, kappa * -1.44269504f};
   // kappa in a vector register: an FMA with a scalar operand issues at two
   // thirds of the rate (direct product of 19220 panels 570 -> 534 us)

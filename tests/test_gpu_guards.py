@@ -1,18 +1,22 @@
 """Products where a guard of the pair terms decides: sheets in contact whose far
-nodes fall on other panels' centroids.
+nodes fall on other panels' centroids, and screening so strong that
+e^{-kappa r} vanishes.
 
 Tolerances: as for the kernel edges, 1e-12 (FP64) and 2e-5 (FP32 far field) of
-the largest entry.
+the largest entry; A and A^T of one set of rounded pair terms agree to 1e-13
+and 1e-6 of |z| |x|.
 """
 
 import numpy as np
 import pytest
 
 from oracle import bie
+from synth import icosphere
 
 pytestmark = pytest.mark.gpu
 
 TOL = {"fp64": 1e-12, "mixed": 2e-5}
+TOL_T = {"fp64": 1e-13, "mixed": 1e-6}
 
 
 def _solver(verts, tris, **kw):
@@ -71,3 +75,24 @@ def test_products_on_sheets_in_contact(kind, precision, mode):
     x, z = rng.normal(size=2 * m.N), rng.normal(size=2 * m.N)
     assert _worst(s.matvec(x), A @ x) < TOL[precision]
     assert _worst(s.matvec(z, transpose=True), A.T @ z) < TOL[precision]
+
+
+@pytest.mark.parametrize("order", [4, 6])
+@pytest.mark.parametrize("kappa", [0.0, 40.0, 1e7, 1e30])
+def test_tree_product_screening_range(kappa, order):
+    """kappa^order beyond the FP32 range, times e^{-kappa r} = 0."""
+    from oracle import treecode
+    verts, tris = icosphere(4, radius=4.0)
+    rng = np.random.default_rng(order)
+    verts = verts + rng.normal(scale=1e-4, size=verts.shape)
+    m = bie.Mesh(verts, tris, kappa)
+    x, z = rng.normal(size=2 * m.N), rng.normal(size=2 * m.N)
+    rows = np.sort(rng.choice(m.N, 96, replace=False))
+    ref = treecode.Treecode(m, 0.6, order, 40).matvec(x, 1.0, 80.0, rows=rows)
+    for precision in ("fp64", "mixed"):
+        s = _solver(verts, tris, mode="treecode", theta=0.6, order_P=order, leaf_panels=40,
+                    precision=precision, kappa=kappa)
+        y, yt = s.matvec(x), s.matvec(z, transpose=True)
+        assert _worst(np.concatenate([y[:m.N][rows], y[m.N:][rows]]), ref) < TOL[precision]
+        off = abs(z @ y - yt @ x) / (np.linalg.norm(z) * np.linalg.norm(x))
+        assert off < TOL_T[precision]
