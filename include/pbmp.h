@@ -179,7 +179,11 @@ int pbmp_set_options(pbmp_ctx *c, const pbmp_options *o);
  * closed, 2-manifold, consistently oriented with positive enclosed volume
  * and that every panel area exceeds 1e-12 A^2 (PBMP_EMESH otherwise), and
  * prepares panel geometry, near-singular lists and the tree.  Invalidates
- * previously set sites' surface data and any previous solution. */
+ * previously set sites' surface data and any previous solution.  A Stern
+ * layer (pbmp_set_stern) stays and is coupled to the new surface; where it does
+ * not fit (treecode mode, or a surface that it does not enclose) pbmp_solve and
+ * pbmp_matvec return PBMP_ESTATE until the layer or the mesh is set again or
+ * the layer is removed. */
 int pbmp_set_mesh(pbmp_ctx *c, int64_t nv, const double *verts, int64_t nt,
                   const int32_t *tris, int where);
 

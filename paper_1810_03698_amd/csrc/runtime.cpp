@@ -394,6 +394,13 @@ void Runtime::set_mesh(int64_t nv, const double *verts, int64_t nt,
   h_tri_.resize(3 * (size_t)N);
   for (int i = 0; i < N; ++i)
     for (int k = 0; k < 3; ++k) h_tri_[3 * i + k] = ht[3 * perm_[i] + k];
+  if (outer_) {
+    // the layer is coupled to the new surface below, where it fits; the mesh is
+    // prepared for the solution's constants, which are those without a layer
+    o.kappa = kappa_ext_;
+    o.eps_out = eps_out_ext_;
+    stern_coupled_ = false;
+  }
   N_ = N;
   Nv_ = Nv;
   warm_ok_ = false;
@@ -457,6 +464,7 @@ void Runtime::set_mesh(int64_t nv, const double *verts, int64_t nt,
     tree_->build_device(N, ru_.nf, keys_.p, geo_.p, src64_.p, s_);
   }
   alloc_work();
+  if (outer_ && !tree_active_ && outer_->encloses(*this)) couple_stern();
   sync();
   t_setup_ms_ = ms_since(t0);
   setup_reported_ = false;
@@ -1010,6 +1018,7 @@ int Runtime::scf(bool solvent, double *mu, int *gm_warn) {
 
 int Runtime::solve(pbmp_result *r) {
   PBMP_REQUIRE(N_ > 0 && M_ > 0, PBMP_ESTATE, "set_mesh and set_sites must precede solve");
+  require_coupled();
   PBMP_REQUIRE(r != nullptr, PBMP_EARG, "null result");
   auto t0 = clk::now();
   gmres_iters_ = 0;
@@ -1111,6 +1120,7 @@ void Runtime::matvec_user(const double *x, double *y, int transpose, int where) 
   PBMP_REQUIRE(where == PBMP_HOST || where == PBMP_DEVICE, PBMP_EARG, "bad where");
   if (outer_) {
     PBMP_REQUIRE(!transpose, PBMP_ESTATE, "no transposed product with a Stern layer");
+    require_coupled();
     stern_matvec_user(x, y, where);
     return;
   }

@@ -161,6 +161,11 @@ class Runtime {
   Dbuf<double> gV_, gw_, gz_, gax_;      // general GMRES work
   void point_lists(const std::vector<double> &pts, int M, std::vector<int> &row,
                    std::vector<int> &col) const;
+  bool stern_coupled_ = false;  // the layer fits the mesh that is there now
+  void couple_stern();
+  void require_coupled() const;
+  bool encloses(const Runtime &in);
+  std::vector<double> centroids() const;
   void set_probe(int M, const std::vector<double> &pts);
   void probe(const double *x, bool f64, double *out4);
   void apply_stern(const double *X, double *Y, bool f64);

@@ -54,6 +54,7 @@ void Runtime::set_stern(int64_t nv, const double *verts, int64_t nt, const int32
       o.kappa = kappa_ext_;
       o.eps_out = eps_out_ext_;
       outer_.reset();
+      stern_coupled_ = false;
       build_near_lists();
     }
     warm_ok_ = false;
@@ -75,39 +76,59 @@ void Runtime::set_stern(int64_t nv, const double *verts, int64_t nt, const int32
   std::unique_ptr<Runtime> outer(new Runtime(oo));
   outer->set_mesh(nv, verts, nt, tris, where);
   // the molecular surface must lie inside the outer one
-  const int N1 = N_, N2 = outer->N_;
-  std::vector<double> c1(3 * (size_t)N1), c2(3 * (size_t)N2);
-  for (int i = 0; i < N1; ++i)
-    for (int d = 0; d < 3; ++d) c1[3 * i + d] = h_geo_[(size_t)d * N1 + i];
-  for (int j = 0; j < N2; ++j)
-    for (int d = 0; d < 3; ++d) c2[3 * j + d] = outer->h_geo_[(size_t)d * N2 + j];
-  {
-    Dbuf<double> pts, wind;
-    pts.upload(c1.data(), c1.size(), s_);
-    wind.alloc(N1);
-    launch_winding(s_, N2, N1, outer->verts_.p, outer->tri_.p, pts.p, wind.p);
-    std::vector<double> hw(N1);
-    wind.download(hw.data(), N1, s_);
-    sync();
-    for (int i = 0; i < N1; ++i)
-      PBMP_REQUIRE(hw[i] > 0.5, PBMP_EMESH,
-                   "the Stern surface must enclose the molecular surface");
-  }
+  PBMP_REQUIRE(outer->encloses(*this), PBMP_EMESH,
+               "the Stern surface must enclose the molecular surface");
   outer_ = std::move(outer);
   eps_stern_ = eps_stern;
+  couple_stern();
+}
+
+// centroids [N][3] in internal order
+std::vector<double> Runtime::centroids() const {
+  std::vector<double> c(3 * (size_t)N_);
+  for (int i = 0; i < N_; ++i)
+    for (int d = 0; d < 3; ++d) c[3 * (size_t)i + d] = h_geo_[(size_t)d * N_ + i];
+  return c;
+}
+
+// whether the other surface's collocation points lie inside this one
+bool Runtime::encloses(const Runtime &in) {
+  Dbuf<double> pts, wind;
+  const std::vector<double> c = in.centroids();
+  pts.upload(c.data(), c.size(), s_);
+  wind.alloc(in.N_);
+  launch_winding(s_, N_, in.N_, verts_.p, tri_.p, pts.p, wind.p);
+  std::vector<double> w(in.N_);
+  wind.download(w.data(), w.size(), s_);
+  sync();
+  return *std::min_element(w.begin(), w.end()) > 0.5;
+}
+
+// The parts that depend on both surfaces, for the mesh and the layer that are
+// there now (pbmp_set_stern, and pbmp_set_mesh under a layer).
+void Runtime::couple_stern() {
+  const int N1 = N_, N2 = outer_->N_;
   // inner surface: Laplace on both sides, ratio eps_in / eps_stern
   o.kappa = 0.0;
-  o.eps_out = eps_stern;
+  o.eps_out = eps_stern_;
   build_near_lists();
-  outer_->set_probe(N1, c1);
-  set_probe(N2, c2);
+  outer_->set_probe(N1, centroids());
+  set_probe(N2, outer_->centroids());
   const size_t n = 2 * (size_t)N1 + 2 * (size_t)N2;
   sX_.alloc(n);
   sB_.alloc(n);
   sY_.alloc(n);
   sT_.alloc(2 * (size_t)N1);
+  stern_coupled_ = true;
+  ax_holds_x_ = gax_holds_x_ = false;
   warm_ok_ = false;
   solved_ = false;
+}
+
+void Runtime::require_coupled() const {
+  PBMP_REQUIRE(!outer_ || stern_coupled_, PBMP_ESTATE,
+               "the Stern layer does not fit the mesh (treecode mode, or not enclosed): "
+               "set or remove the layer, or the mesh, again");
 }
 
 void Runtime::apply_stern(const double *X, double *Y, bool f64) {

@@ -198,7 +198,7 @@ class Solver:
         if rc != 0:
             raise PbmpError(rc, self.lib.pbmp_last_error(None).decode())
         self.ctx = ctx
-        self.nt = self.nv = self.m = 0
+        self.nt = self.nv = self.m = self.nt2 = 0
         # advanced by every call that replaces the state a backward
         # differentiates (mesh, sites, Stern layer, solve), so that a caller
         # holding an earlier solve's number can tell that it is gone
@@ -227,7 +227,7 @@ class Solver:
         self.state_id += 1
         self._check(self.lib.pbmp_set_mesh(self.ctx, nv, v.ptr, nt, t.ptr,
                                            _common_where([v, t])))
-        self.nt, self.nv, self.nt2 = nt, nv, 0
+        self.nt, self.nv = nt, nv  # a Stern layer (nt2 panels) stays
 
     def set_options(self, **kw):
         """Change solver settings between solves (gmres_restart, gmres_tol,
@@ -295,7 +295,7 @@ class Solver:
         return out
 
     def matvec(self, x, transpose=False, out=None):
-        n = 2 * self.nt + 2 * getattr(self, "nt2", 0)
+        n = 2 * self.nt + 2 * self.nt2
         a = _Arg(x, np.float64, n)
         if out is None:
             out = np.empty(n) if a.where == HOST else _empty_like_torch(x)

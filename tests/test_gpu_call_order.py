@@ -1,0 +1,85 @@
+"""What one call leaves behind for the next: a Stern layer over a new mesh.
+
+A call whose inputs are the same gives the same bits, whatever ran in between:
+every kernel adds in a fixed order.
+"""
+
+import numpy as np
+import pytest
+
+from oracle import stern
+from synth import icosphere, random_multipoles, sites_in_ball
+
+pytestmark = pytest.mark.gpu
+
+
+def _sites(m=8, radius=2.0):
+    rng = np.random.default_rng(4)
+    return (sites_in_ball(rng, m, radius=radius, min_sep=0.8),) + random_multipoles(rng, m)
+
+
+def _solver(verts, tris, sites=None, **kw):
+    from paper_1810_03698_amd import Solver
+    args = dict(eps_in=1.0, eps_out=80.0, kappa=0.125, mode="direct", precision="fp64")
+    args.update(kw)
+    s = Solver(**args)
+    s.set_mesh(verts, tris)
+    if sites is not None:
+        s.set_sites(*sites)
+    return s
+
+
+def test_tree_keeps_the_screening_of_its_context():
+    """A mesh set under a Stern layer, whose inner region has no ions, and the
+    layer taken off: the products are those of a context that never had one."""
+    small, big = icosphere(2, 3.0), icosphere(5, 4.0)
+    outer = icosphere(2, 6.0)
+    s = _solver(*small, mode="auto")
+    s.set_stern(*outer, 80.0)
+    s.set_mesh(*big)
+    s.set_stern(None, None, 80.0)
+    x = np.random.default_rng(2).normal(size=2 * len(big[1]))
+    t = _solver(*big, mode="auto")
+    for transpose in (False, True):
+        assert np.array_equal(s.matvec(x, transpose=transpose), t.matvec(x, transpose=transpose))
+
+
+@pytest.mark.parametrize("level", [1, 2, 3])
+def test_stern_layer_over_a_new_mesh(level):
+    """The layer stays where it is and couples to the surface that is there now,
+    also one of another size."""
+    outer = icosphere(2, 6.0)
+    v, t = icosphere(level, 3.5)
+    v = v + [0.3, -0.2, 0.1]
+    s = _solver(*icosphere(2, 4.0))
+    s.set_stern(*outer, 60.0)
+    s.set_mesh(v, t)
+    ref = _solver(v, t)
+    ref.set_stern(*outer, 60.0)
+    x = np.random.default_rng(3).normal(size=2 * len(t) + 2 * len(outer[1]))
+    y = s.matvec(x)
+    assert np.array_equal(y, ref.matvec(x))
+    o = stern.SternBemSolvent(v, t, *outer, 1.0, 60.0, 80.0, 0.125).apply(x)
+    assert np.abs(y - o).max() < 1e-12 * np.abs(o).max()
+    for a in (s, ref):
+        a.set_sites(*_sites())
+    assert s.solve(outputs=False)["dG"] == ref.solve(outputs=False)["dG"]
+
+
+def test_stern_layer_that_no_longer_encloses():
+    """The mesh is set, a coupled call is refused, and a mesh that fits or the
+    layer's removal makes the context whole again."""
+    from paper_1810_03698_amd import PbmpError
+    s = _solver(*icosphere(2, 4.0))
+    s.set_stern(*icosphere(2, 6.0), 60.0)
+    wide = icosphere(2, 8.0)
+    s.set_mesh(*wide)
+    s.set_sites(*_sites())
+    x = np.ones(2 * s.nt + 2 * s.nt2)
+    for call in (lambda: s.matvec(x), lambda: s.solve(outputs=False)):
+        with pytest.raises(PbmpError) as e:
+            call()
+        assert e.value.code == -6
+    s.set_stern(None, None, 60.0)
+    x = x[:2 * s.nt]
+    assert np.array_equal(s.matvec(x), _solver(*wide).matvec(x))
