@@ -65,8 +65,8 @@ void Runtime::apply_transpose(const double *x, double *y, bool f64, const int *p
   const double *val = (use64 && !fp64()) ? nval64_.p : nval_.p;
   if (use_tree())
     tree_apply_transpose(*tree_, s_, use64, ru_.nf, N_, geo_.p, src64_.p, src32_.p, tgt32_.p,
-                         x, o.kappa, part_.p, trow_.p, tcol_.p, tent_.p, val,
-                         o.eps_in / o.eps_out, perm, y, floor_r2_);
+                         x, part_.p, trow_.p, tcol_.p, tent_.p, val, o.eps_in / o.eps_out,
+                         perm, y, floor_r2_);
   else
     launch_transpose(s_, use64, ru_.nf, N_, src64_.p, src32_.p, geo_.p, tgt32_.p, x, o.kappa,
                      p2p_chunks_, part_.p, trow_.p, tcol_.p, tent_.p, val,

@@ -401,8 +401,8 @@ void launch_mesh_adjoint(hipStream_t s, int N, int M, int nf, const double *src6
   // far-rule operator entries: with the treecode's lists and expansions
   // (the derivative of the treecode operator), else every pair directly
   if (tree) {
-    tree_mesh_adjoint_far(*tree, s, nf, N, geo, src64, lam, kappa, eps_ratio, part, partT, gc,
-                          gy, gn, gA);
+    tree_mesh_adjoint_far(*tree, s, nf, N, geo, src64, lam, eps_ratio, part, partT, gc, gy, gn,
+                          gA);
   } else {
     const dim3 gg((N + kGradLanes - 1) / kGradLanes);
 #define PBMP_OG(NF)                                                                         \

@@ -1574,8 +1574,9 @@ template <int L> static void harmonic_positions(std::vector<int> &pos) {
                             : Harm<L>::group(l, -m) + 2);
 }
 
-void tree_upload_harmonics(Tree &t, double kappa, hipStream_t s) {
+void tree_upload_harmonics(Tree &t, hipStream_t s) {
   using ld = long double;
+  const double kappa = t.prm.kappa;
   const int L = t.prm.order + 1, D = L + 1;
   auto at = [&](int i, int j, int k) { return (i * D + j) * D + k; };
   using Poly = std::vector<ld>;
@@ -1732,7 +1733,8 @@ void tree_upload_harmonics(Tree &t, double kappa, hipStream_t s) {
 
 void tree_apply(Tree &t, hipStream_t s, bool fp64, int nf, int N, const double *geo,
                 const double *src64, const float *src32, const float *tgt32,
-                double kappa, double eps_ratio, double *part, KernelClock &clk, bool floor_r2) {
+                double eps_ratio, double *part, KernelClock &clk, bool floor_r2) {
+  const double kappa = t.prm.kappa;
   hipEvent_t e0 = clk.on ? clk.begin(s) : nullptr;
   launch_moments(t, s, nf, src64, fp64, eps_ratio);
   PBMP_HIP(hipGetLastError());
@@ -1781,9 +1783,10 @@ void launch_finish_slots(hipStream_t s, int N, const int *tslots, const double *
 }
 
 void tree_mesh_adjoint_far(Tree &t, hipStream_t s, int nf, int N, const double *geo,
-                           const double *src64, const double *lam, double kappa,
-                           double eps_ratio, double *part, double *partT, double *gc,
-                           double *gy, double *gn, double *gA) {
+                           const double *src64, const double *lam, double eps_ratio,
+                           double *part, double *partT, double *gc, double *gy, double *gn,
+                           double *gA) {
+  const double kappa = t.prm.kappa;
   switch (t.prm.order) {
 #define PBMP_MA(P)                                                                          \
   case P:                                                                                   \
@@ -1803,9 +1806,10 @@ void tree_mesh_adjoint_far(Tree &t, hipStream_t s, int nf, int N, const double *
 
 void tree_apply_transpose(Tree &t, hipStream_t s, bool fp64, int nf, int N, const double *geo,
                           const double *src64, const float *src32, const float *tgt32,
-                          const double *z, double kappa, double *part, const int *trow,
-                          const int *tcol, const int *tent, const double *val, double eps_ratio,
+                          const double *z, double *part, const int *trow, const int *tcol,
+                          const int *tent, const double *val, double eps_ratio,
                           const int *perm, double *y, bool floor_r2) {
+  const double kappa = t.prm.kappa;
   if (fp64)
     tree_T_far_p<double>(t, s, nf, N, geo, src64, src64, geo, z, kappa, 0.0, eps_ratio, part,
                          floor_r2);

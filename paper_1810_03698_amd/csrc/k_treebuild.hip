@@ -790,7 +790,7 @@ void Tree::build_device(int N, int nf, const uint64_t *key, const double *geo,
   d_mom64.alloc((size_t)nbox * nmom);
   PBMP_HIP(hipMemsetAsync(d_mom64.p, 0, sizeof(double) * nbox * nmom, s));
   tree_upload_exponents(*this, s);
-  tree_upload_harmonics(*this, prm.kappa, s);
+  tree_upload_harmonics(*this, s);
   PBMP_HIP(hipStreamSynchronize(s));
 }
 

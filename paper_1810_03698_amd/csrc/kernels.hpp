@@ -185,14 +185,14 @@ struct KernelClock;
 // accepted boxes, into part[slot][2][N] (the two rows of y = A x).
 void tree_apply(Tree &t, hipStream_t s, bool fp64, int nf, int N,
                 const double *geo, const double *src64, const float *src32,
-                const float *tgt32, double kappa, double eps_ratio, double *part,
-                KernelClock &clk, bool floor_r2);
+                const float *tgt32, double eps_ratio, double *part, KernelClock &clk,
+                bool floor_r2);
 // finish with a per-target number of partial slots
 // A^T z with the treecode (transposed P2P, M2P^T + L2L + L2P, transposed
 // near/self correction)
 void tree_apply_transpose(Tree &t, hipStream_t s, bool fp64, int nf, int N, const double *geo,
                           const double *src64, const float *src32, const float *tgt32,
-                          const double *z, double kappa, double *part, const int *trow,
+                          const double *z, double *part, const int *trow,
                           const int *tcol, const int *tent, const double *val, double eps_ratio,
                           const int *perm, double *y, bool floor_r2);
 // Far-field part of the mesh adjoint with the treecode: d/d(collocation
@@ -200,9 +200,9 @@ void tree_apply_transpose(Tree &t, hipStream_t s, bool fp64, int nf, int N, cons
 // gA [N] of lambda . A x (assigned, not accumulated); part: the product's
 // forward slots [max_slots][4][N], partT: [max_slots_T][13][N]
 void tree_mesh_adjoint_far(Tree &t, hipStream_t s, int nf, int N, const double *geo,
-                           const double *src64, const double *lam, double kappa,
-                           double eps_ratio, double *part, double *partT, double *gc,
-                           double *gy, double *gn, double *gA);
+                           const double *src64, const double *lam, double eps_ratio,
+                           double *part, double *partT, double *gc, double *gy, double *gn,
+                           double *gA);
 void launch_finish_slots(hipStream_t s, int N, const int *tslots,
                          const double *part, const int *rowptr, const int *col,
                          const double *val, const double *x, double eps_ratio,

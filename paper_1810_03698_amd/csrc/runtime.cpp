@@ -694,7 +694,7 @@ void Runtime::apply(const double *x, double *y, bool f64, bool packed, const int
   if (!packed) launch_pack_strengths(s_, N, ru_.nf, o.eps_in / o.eps_out, geo_.p, x, src64_.p, src32_.p);
   if (use_tree()) {
     tree_apply(*tree_, s_, use64, ru_.nf, N, geo_.p, src64_.p, src32_.p,
-               tgt32_.p, o.kappa, o.eps_in / o.eps_out, part_.p, clock, floor_r2_);
+               tgt32_.p, o.eps_in / o.eps_out, part_.p, clock, floor_r2_);
     launch_finish_slots(s_, N, tree_->d_tslots.p, part_.p, nrow_.p, ncol_.p,
                         val, x, o.eps_in / o.eps_out, perm, y);
   } else {

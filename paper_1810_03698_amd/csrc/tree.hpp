@@ -85,7 +85,8 @@ constexpr int kShiftLeaves = 16;
 constexpr int kM2PTChunkTargets = 512;
 
 struct TreeParams {
-  double theta = 0.5, kappa = 0.0;
+  double theta = 0.5;
+  double kappa = 0.0;  // the only one of a tree: its tables hold powers of it
   int order = 4;
   int leaf = 300;
 };
@@ -169,6 +170,6 @@ void morton_order_device(hipStream_t s, int N, const double *verts, const int *t
 // upload the multi-index exponent table of the chosen order (d_monos)
 void tree_upload_exponents(Tree &t, hipStream_t s);
 // tables and buffers of the harmonic form for the chosen order and kappa
-void tree_upload_harmonics(Tree &t, double kappa, hipStream_t s);
+void tree_upload_harmonics(Tree &t, hipStream_t s);
 
 }  // namespace pbmp
