@@ -1479,6 +1479,9 @@ void tree_mesh_adjoint_far_p(Tree &t, hipStream_t s, int nf, int N, const double
                              const double *src64, const double *lam, double kappa,
                              double eps_ratio, double *part, double *partT, double *gc,
                              double *gy, double *gn, double *gA) {
+  // the moments of the strengths that the records hold now: those in d_mom64 are
+  // the last product's, whatever vector that was
+  launch_moments_p<P>(t, s, nf, src64, true, eps_ratio);
   // target side: direct pairs and expansions into the forward slots
   const int nbp = ((t.n_p2p_tasks + 7) / 8) * 8;
   if (nf == 3)

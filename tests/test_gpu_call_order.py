@@ -1,4 +1,5 @@
-"""What one call leaves behind for the next: a Stern layer over a new mesh.
+"""What one call leaves behind for the next: products between a solve and its
+backward, and a Stern layer over a new mesh.
 
 A call whose inputs are the same gives the same bits, whatever ran in between:
 every kernel adds in a fixed order.
@@ -27,6 +28,28 @@ def _solver(verts, tris, sites=None, **kw):
     if sites is not None:
         s.set_sites(*sites)
     return s
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("between", ["matvec", "transposed", "rhs"])
+def test_backward_differentiates_the_solve(between, precision):
+    """...whatever vectors other calls have worked on since (treecode mode: its
+    moments are those of the last product)."""
+    verts, tris = icosphere(3, 4.0)
+    s = _solver(verts, tris, _sites(), mode="treecode", leaf_panels=40, precision=precision)
+    s.solve(outputs=False)
+    ref = s.backward(1.0)
+    s.solve(outputs=False)
+    x = np.random.default_rng(1).normal(size=2 * len(tris))
+    if between == "matvec":
+        s.matvec(x)
+    elif between == "transposed":
+        s.matvec(x, transpose=True)
+    else:
+        s.rhs(np.ones((8, 3)))
+    got = s.backward(1.0)
+    for k in ("xyz", "q", "d", "Q9", "verts"):
+        assert np.array_equal(got[k], ref[k]), (k, np.abs(got[k] - ref[k]).max())
 
 
 def test_tree_keeps_the_screening_of_its_context():
