@@ -623,6 +623,7 @@ void Runtime::set_sites(int64_t m, const double *xyz, const double *q,
   Eperm_.alloc(3 * (size_t)M);
   Eind_.alloc(3 * (size_t)M);
   reac_.alloc(10 * (size_t)M);
+  sf_.alloc(10 * (size_t)M);
   ind_.alloc(10 * (size_t)M);
   vac_perm_.alloc(10 * (size_t)M);
   vac_ind_.alloc(10 * (size_t)M);
@@ -1168,8 +1169,9 @@ void Runtime::site_fields_user(const double *x, double *out, int where) {
   PBMP_REQUIRE(N_ > 0 && M_ > 0, PBMP_ESTATE, "no mesh or sites");
   PBMP_REQUIRE(out != nullptr, PBMP_EARG, "null output");
   to_internal(x, io_a_.p, 2, where);
-  readout(io_a_.p, true, reac_.p);
-  PBMP_HIP(hipMemcpyAsync(out, reac_.p, sizeof(double) * 10 * M_,
+  // (not into reac_, the solution's data that a backward reads)
+  readout(io_a_.p, true, sf_.p);
+  PBMP_HIP(hipMemcpyAsync(out, sf_.p, sizeof(double) * 10 * M_,
                           where == PBMP_DEVICE ? hipMemcpyDeviceToDevice
                                                : hipMemcpyDeviceToHost, s_));
   sync();

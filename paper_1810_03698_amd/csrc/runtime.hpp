@@ -116,7 +116,7 @@ class Runtime {
   Dbuf<double> part_, rpart_;
   int p2p_chunks_ = 1, ro_chunks_ = 1;
   Dbuf<double> V_, w_, z_, ax_, b_, x_, partial_, norm_, ybuf_, tmp_;
-  Dbuf<double> mu_d_, mu_v_, Eperm_, Eind_, reac_, ind_, p_, f_, e_;
+  Dbuf<double> mu_d_, mu_v_, Eperm_, Eind_, reac_, sf_, ind_, p_, f_, e_;
   Dbuf<double> io_a_, io_b_;  // permutation staging
   Dbuf<double> vac_perm_, vac_ind_;  // vacuum-state potential data [10M]
   bool solved_ = false;

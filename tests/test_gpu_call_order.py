@@ -1,5 +1,5 @@
-"""What one call leaves behind for the next: products between a solve and its
-backward, and a Stern layer over a new mesh.
+"""What one call leaves behind for the next: products and site readouts between a
+solve and its backward, and a Stern layer over a new mesh.
 
 A call whose inputs are the same gives the same bits, whatever ran in between:
 every kernel adds in a fixed order.
@@ -31,7 +31,7 @@ def _solver(verts, tris, sites=None, **kw):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
-@pytest.mark.parametrize("between", ["matvec", "transposed", "rhs"])
+@pytest.mark.parametrize("between", ["matvec", "transposed", "site_fields", "rhs"])
 def test_backward_differentiates_the_solve(between, precision):
     """...whatever vectors other calls have worked on since (treecode mode: its
     moments are those of the last product)."""
@@ -45,6 +45,8 @@ def test_backward_differentiates_the_solve(between, precision):
         s.matvec(x)
     elif between == "transposed":
         s.matvec(x, transpose=True)
+    elif between == "site_fields":
+        s.site_fields(x)
     else:
         s.rhs(np.ones((8, 3)))
     got = s.backward(1.0)
