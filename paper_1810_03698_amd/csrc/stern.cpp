@@ -168,10 +168,12 @@ int Runtime::gmres_stern(const double *b, double *x, int *iters) {
 }
 
 void Runtime::stern_matvec_user(const double *x, double *y, int where) {
+  // sX_ is the last solution (warm start): the vectors of this product are those
+  // that a solve writes before it reads them
   const int N1 = N_;
-  to_internal(x, sX_.p, 2, where);
-  outer_->to_internal(x + 2 * (size_t)N1, sX_.p + 2 * (size_t)N1, 2, where);
-  apply_stern(sX_.p, sY_.p, false);
+  to_internal(x, sB_.p, 2, where);
+  outer_->to_internal(x + 2 * (size_t)N1, sB_.p + 2 * (size_t)N1, 2, where);
+  apply_stern(sB_.p, sY_.p, false);
   to_user(sY_.p, y, 2, where);
   outer_->to_user(sY_.p + 2 * (size_t)N1, y + 2 * (size_t)N1, 2, where);
 }

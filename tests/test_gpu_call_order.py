@@ -108,3 +108,19 @@ def test_stern_layer_that_no_longer_encloses():
     s.set_stern(None, None, 60.0)
     x = x[:2 * s.nt]
     assert np.array_equal(s.matvec(x), _solver(*wide).matvec(x))
+
+
+def test_warm_start_with_a_stern_layer_after_a_product():
+    """A warm solve starts from the last solve's solution, not from a vector
+    that a product was applied to since."""
+    kw = dict(gmres_tol=1e-10, scf_tol_debye=1e-9, warm_start=True)
+    out = []
+    for product in (False, True):
+        s = _solver(*icosphere(2, 4.0), **kw)
+        s.set_stern(*icosphere(2, 5.5), 60.0)
+        s.set_sites(*_sites())
+        s.solve(outputs=False)
+        if product:
+            s.matvec(np.random.default_rng(5).normal(size=2 * s.nt + 2 * s.nt2))
+        out.append(s.solve(outputs=False)["dG"])
+    assert out[0] == out[1]
