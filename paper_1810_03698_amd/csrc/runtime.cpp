@@ -1021,13 +1021,23 @@ int Runtime::solve(pbmp_result *r) {
   PBMP_REQUIRE(N_ > 0 && M_ > 0, PBMP_ESTATE, "set_mesh and set_sites must precede solve");
   require_coupled();
   PBMP_REQUIRE(r != nullptr, PBMP_EARG, "null result");
+  const int w = r->where;
+  PBMP_REQUIRE(w == PBMP_HOST || w == PBMP_DEVICE, PBMP_EARG, "bad result.where");
   auto t0 = clk::now();
   gmres_iters_ = 0;
   matvecs_ = 0;
   t_matvec_ms_ = 0.0;
   int warn = 0, gm_warn = 0;
-  int it_v = scf(false, mu_v_.p, &gm_warn);
-  int it_d = scf(true, mu_d_.p, &gm_warn);
+  // a solve that throws leaves no solution, and none to start warm from
+  solved_ = false;
+  int it_v = 0, it_d = 0;
+  try {
+    it_v = scf(false, mu_v_.p, &gm_warn);
+    it_d = scf(true, mu_d_.p, &gm_warn);
+  } catch (...) {
+    warm_ok_ = ax_holds_x_ = gax_holds_x_ = false;
+    throw;
+  }
   if (it_v < 0 || it_d < 0) warn = PBMP_WSCF;
   if (gm_warn && !warn) warn = gm_warn;
   // energy (eq. energy_multipole_polarizable with d in place of p; the
@@ -1067,8 +1077,6 @@ int Runtime::solve(pbmp_result *r) {
   r->t_setup_ms = setup_reported_ ? 0.0 : t_setup_ms_;
   setup_reported_ = true;
   // outputs in user order / units
-  const int w = r->where;
-  PBMP_REQUIRE(w == PBMP_HOST || w == PBMP_DEVICE, PBMP_EARG, "bad result.where");
   if (r->phi || r->dphidn) {
     // physical: 4 pi times the integral-equation normalisation
     launch_permute(s_, N_, 2, d_perm_.p, x_.p, io_a_.p, false);

@@ -1,5 +1,5 @@
 """What one call leaves behind for the next: products and site readouts between a
-solve and its backward, and a Stern layer over a new mesh.
+solve and its backward, calls that fail, and a Stern layer over a new mesh.
 
 A call whose inputs are the same gives the same bits, whatever ran in between:
 every kernel adds in a fixed order.
@@ -124,3 +124,19 @@ def test_warm_start_with_a_stern_layer_after_a_product():
             s.matvec(np.random.default_rng(5).normal(size=2 * s.nt + 2 * s.nt2))
         out.append(s.solve(outputs=False)["dG"])
     assert out[0] == out[1]
+
+
+def test_failed_solve_leaves_nothing_to_differentiate():
+    """Over-relaxed dipoles run to infinity: the backward is refused, and a solve
+    with the old settings starts afresh."""
+    from paper_1810_03698_amd import PbmpError
+    s = _solver(*icosphere(1, 4.0), _sites(), scf_maxit=20000, warm_start=True)
+    ref = s.solve(outputs=False)
+    s.set_options(scf_omega=1.999, warm_start=False)
+    bad = s.solve(outputs=False)
+    assert bad["status"] == 2
+    with pytest.raises(PbmpError) as e:
+        s.backward(1.0)
+    assert e.value.code == -6
+    s.set_options(scf_omega=0.7, warm_start=True)
+    assert s.solve(outputs=False)["dG"] == ref["dG"]
