@@ -177,7 +177,8 @@ int pbmp_set_options(pbmp_ctx *c, const pbmp_options *o);
  * solvent (section "The boundary integral formulation": n points out of the
  * molecule).  The library copies both arrays, checks that the mesh is
  * closed, 2-manifold, consistently oriented with positive enclosed volume
- * and that every panel area exceeds 1e-12 A^2 (PBMP_EMESH otherwise), and
+ * and that every panel area exceeds 1e-12 A^2 (PBMP_EMESH otherwise; after a
+ * failure in the area check or later the context has no mesh), and
  * prepares panel geometry, near-singular lists and the tree.  Invalidates
  * previously set sites' surface data and any previous solution.  A Stern
  * layer (pbmp_set_stern) stays and is coupled to the new surface; where it does

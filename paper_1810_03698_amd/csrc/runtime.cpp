@@ -379,6 +379,18 @@ void Runtime::set_mesh(int64_t nv, const double *verts, int64_t nt,
            A[2] * (B[0] * C[1] - B[1] * C[0]);
   }
   PBMP_REQUIRE(vol > 0, PBMP_EMESH, "enclosed volume not positive (inward orientation)");
+  // from here on the old mesh is being replaced: a call that throws leaves none,
+  // not arrays of two sizes
+  struct Unset {
+    Runtime &rt;
+    bool on = true;
+    ~Unset() {
+      if (!on) return;
+      rt.N_ = rt.M_ = 0;
+      rt.solved_ = rt.warm_ok_ = rt.tree_active_ = false;
+      rt.tree_.reset();
+    }
+  } unset{*this};
   // --- Morton order of the centroids (device radix sort)
   verts_.upload(hv.data(), hv.size(), s_);
   {
@@ -466,6 +478,7 @@ void Runtime::set_mesh(int64_t nv, const double *verts, int64_t nt,
   alloc_work();
   if (outer_ && !tree_active_ && outer_->encloses(*this)) couple_stern();
   sync();
+  unset.on = false;
   t_setup_ms_ = ms_since(t0);
   setup_reported_ = false;
 }

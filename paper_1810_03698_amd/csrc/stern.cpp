@@ -108,6 +108,7 @@ bool Runtime::encloses(const Runtime &in) {
 // there now (pbmp_set_stern, and pbmp_set_mesh under a layer).
 void Runtime::couple_stern() {
   const int N1 = N_, N2 = outer_->N_;
+  stern_coupled_ = false;
   // inner surface: Laplace on both sides, ratio eps_in / eps_stern
   o.kappa = 0.0;
   o.eps_out = eps_stern_;

@@ -140,3 +140,25 @@ def test_failed_solve_leaves_nothing_to_differentiate():
     assert e.value.code == -6
     s.set_options(scf_omega=0.7, warm_start=True)
     assert s.solve(outputs=False)["dG"] == ref["dG"]
+
+
+def test_failed_set_mesh_leaves_no_mesh():
+    """A mesh that is refused for a panel without area takes the place of the
+    one before it: nothing is left to apply."""
+    from paper_1810_03698_amd import PbmpError
+    verts, tris = icosphere(2, 4.0)
+    s = _solver(verts, tris)
+    big = icosphere(3, 4.0)
+    flat = big[0].copy()
+    a, b, c = big[1][7]
+    flat[a] = 0.5 * (flat[b] + flat[c])
+    with pytest.raises(PbmpError) as e:
+        s.set_mesh(flat, big[1])
+    assert e.value.code == -2
+    for call in (lambda: s.matvec(np.ones(2 * len(tris))), lambda: s.set_sites(*_sites())):
+        with pytest.raises(PbmpError) as e:
+            call()
+        assert e.value.code == -6
+    s.set_mesh(verts, tris)
+    x = np.ones(2 * len(tris))
+    assert np.array_equal(s.matvec(x), _solver(verts, tris).matvec(x))
