@@ -18,11 +18,6 @@
 // Harmonics: Y_lm = Q_lm(z) Re or Im (x + iy)^m with the monic Q: Q_mm = 1,
 // Q_{l+1,m} = z Q_lm - (l^2 - m^2)/(4 l^2 - 1) Q_{l-1,m}.
 //
-// Where e^{-kappa r} vanishes the powers of kappa beside it may have overflowed
-// (FP32 words and tau_l from kappa of some 1e5 on), so such a pair adds nothing to
-// the Yukawa row instead of 0 times infinity; where it does not, kappa |xi| <
-// kappa r is at most some hundreds and nothing overflows.
-//
 // A box's words: groups of four (cosine: Laplace, Yukawa; sine: Laplace,
 // Yukawa) for m >= 1, m outer, then pairs (Laplace, Yukawa) for m = 0.
 #pragma once
@@ -116,7 +111,7 @@ __device__ __forceinline__ void harmonic_m2p(const T *M, const T (&D)[TPT][3],
       t0 = t1;
       t1 = t2;
     }
-    acc[k][1] += ek[k] > T(0) ? ek[k] * ri[k] * sy : T(0);
+    acc[k][1] += ek[k] * ri[k] * sy;
   }
 }
 
@@ -136,12 +131,11 @@ __device__ __forceinline__ void harmonic_m2p_T(const T (&D)[3], T ri, T ek, T ka
     for (int l = 1; l <= L; ++l) gl[l] = gl[l - 1] * ri;
   }
   if constexpr (FAM != 0) {
-    const T kap = ek > T(0) ? kappa : T(0);
     gy[0] = w2 * ek * ri;
-    gy[1] = gy[0] * (ri + kap);
+    gy[1] = gy[0] * (ri + kappa);
 #pragma unroll
     for (int l = 1; l < L; ++l)
-      gy[l + 1] = ri * gy[l] + kap * kap * T(1.0 / (4 * l * l - 1)) * gy[l - 1];
+      gy[l + 1] = ri * gy[l] + kappa * kappa * T(1.0 / (4 * l * l - 1)) * gy[l - 1];
   }
   auto add = [&](int pos, int l, T y) {
     if constexpr (FAM == 2) {

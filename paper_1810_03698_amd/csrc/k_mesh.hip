@@ -94,7 +94,7 @@ __global__ void k_near_values(int fp64, int N, const int *__restrict__ rowptr,
                               double *__restrict__ diag) {
   __shared__ double etab[64];
   const Screen<double> s64 = make_screen(kappa, etab);
-  const Screen<float> s32 = make_screen((float)kappa, nullptr);
+  const Screen<float> s32 = make_screen(kappa32(kappa), nullptr);
   __syncthreads();
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= N) return;

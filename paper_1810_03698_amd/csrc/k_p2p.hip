@@ -286,12 +286,12 @@ void launch_p2p_direct(hipStream_t s, bool fp64, int nf, int N, int Nt,
   const dim3 grid((Nt + 63) / 64, nchunk);
 #define PBMP_P2P(T, NFV, FL)                                                                  \
   hipLaunchKernelGGL((k_p2p<T, NFV, FL>), grid, dim3(kBlock), 0, s, src, N, tgt, Nt, chunk,    \
-                     (T)kappa, part)
+                     kap, part)
   if (fp64) {
-    const double *src = src64, *tgt = geo;
+    const double *src = src64, *tgt = geo, kap = kappa;
     PBMP_P2P_RULE(double, PBMP_P2P);
   } else {
-    const float *src = src32, *tgt = tgt32;
+    const float *src = src32, *tgt = tgt32, kap = kappa32(kappa);
     PBMP_P2P_RULE(float, PBMP_P2P);
   }
 #undef PBMP_P2P
@@ -318,12 +318,12 @@ void launch_transpose(hipStream_t s, bool fp64, int nf, int N,
   const dim3 grid((N + 63) / 64, nchunk);
 #define PBMP_P2PT(T, NFV, FL)                                                                 \
   hipLaunchKernelGGL((k_p2p_transpose<T, NFV, FL>), grid, dim3(kBlock), 0, s, N, src, tgt,    \
-                     geo, z, chunk, (T)kappa, eps_ratio, part)
+                     geo, z, chunk, kap, eps_ratio, part)
   if (fp64) {
-    const double *src = src64, *tgt = geo;
+    const double *src = src64, *tgt = geo, kap = kappa;
     PBMP_P2P_RULE(double, PBMP_P2PT);
   } else {
-    const float *src = src32, *tgt = tgt32;
+    const float *src = src32, *tgt = tgt32, kap = kappa32(kappa);
     PBMP_P2P_RULE(float, PBMP_P2PT);
   }
 #undef PBMP_P2PT

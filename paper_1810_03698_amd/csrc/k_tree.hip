@@ -22,6 +22,7 @@
 // a box's finished moments; the recurrences serve the vertex gradient.
 #include <algorithm>
 #include <cmath>
+
 #include <type_traits>
 
 #include "harmonic.hpp"
@@ -1681,8 +1682,7 @@ void tree_upload_harmonics(Tree &t, hipStream_t s) {
       const Col &cq = cols[q];
       ld dfact = 1.0L;  // (2l - 1)!!
       for (int u = 2 * cq.l - 1; u > 1; u -= 2) dfact *= u;
-      // finite in double; beyond 1e40 every e^{-kappa r} vanishes
-      const ld kap = std::pow((ld)std::min(kappa, 1e40), 2 * cq.j);
+      const ld kap = std::pow((ld)kappa, 2 * cq.j);
       for (int k = 0; k < dim; ++k) {
         const ld v = A[(size_t)q * 2 * dim + dim + k];
         if (std::fabs(v) < 1e-12L) continue;  // the true ones are simple fractions
@@ -1738,26 +1738,35 @@ void tree_apply(Tree &t, hipStream_t s, bool fp64, int nf, int N, const double *
                 const double *src64, const float *src32, const float *tgt32,
                 double eps_ratio, double *part, KernelClock &clk, bool floor_r2) {
   const double kappa = t.prm.kappa;
+  // The harmonic form holds kappa^2j (words) and kappa^l (radial factors) apart
+  // from e^{-kappa r}, which vanishes long before their product's kappa^(P+1)
+  // leaves the FP32 range; infinity times that zero would be NaN.  Beyond 1e10
+  // (kappa of 27 at P 6, 100 at P 4, above any electrolyte's 3 per A) the
+  // expansions are evaluated in FP64, where kappa <= kMaxKappa keeps them finite:
+  // a test of e^{-kappa r} per pair took the product of 144500 panels in mixed
+  // precision from 905 to 914 us.
+  const bool m2p64 = fp64 || std::pow(kappa, t.prm.order + 1) > 1e10;
   hipEvent_t e0 = clk.on ? clk.begin(s) : nullptr;
-  launch_moments(t, s, nf, src64, fp64, eps_ratio);
+  launch_moments(t, s, nf, src64, m2p64, eps_ratio);
   PBMP_HIP(hipGetLastError());
   if (clk.on) clk.end(s, e0, KernelClock::P2M, 0.0);
 
-  const float nk32 = (float)(-kappa * 1.4426950408889634);
   e0 = clk.on ? clk.begin(s) : nullptr;
   const int nbp = ((t.n_p2p_tasks + 7) / 8) * 8;
 #define PBMP_TP(TT, NFV, FL, SRC, TGT)                                                   \
   hipLaunchKernelGGL((k_p2p_tasks<TT, NFV, FL>), dim3(nbp), dim3(64), 0, s, t.n_p2p_tasks, \
                      t.d_p2p_task.p, t.d_p2p_slot.p, t.d_p2p_src.p, SRC, TGT, N,           \
-                     (TT)kappa, part)
+                     kap, part)
 #define PBMP_TPR(TT, SRC, TGT)                            \
   if (nf == 3 && floor_r2) PBMP_TP(TT, 3, true, SRC, TGT); \
   else if (nf == 3) PBMP_TP(TT, 3, false, SRC, TGT);       \
   else if (floor_r2) PBMP_TP(TT, 1, true, SRC, TGT);       \
   else PBMP_TP(TT, 1, false, SRC, TGT)
   if (fp64) {
+    const double kap = kappa;
     PBMP_TPR(double, src64, geo);
   } else {
+    const float kap = kappa32(kappa);
     PBMP_TPR(float, src32, tgt32);
   }
 #undef PBMP_TPR
@@ -1767,10 +1776,11 @@ void tree_apply(Tree &t, hipStream_t s, bool fp64, int nf, int N, const double *
 
   if (t.n_m2p_tasks > 0 && t.n_m2p_entries > 0) {
     e0 = clk.on ? clk.begin(s) : nullptr;
-    if (fp64)
+    if (m2p64)
       launch_m2p<double>(t, s, t.d_harm64.p, geo, N, kappa, 0.0, part);
     else
-      launch_m2p<float>(t, s, t.d_harm32.p, tgt32, N, (float)kappa, nk32, part);
+      launch_m2p<float>(t, s, t.d_harm32.p, tgt32, N, (float)kappa,
+                        (float)(-kappa * 1.4426950408889634), part);
     PBMP_HIP(hipGetLastError());
     if (clk.on) clk.end(s, e0, KernelClock::M2P, t.m2p_pairs);
   }
@@ -1817,7 +1827,8 @@ void tree_apply_transpose(Tree &t, hipStream_t s, bool fp64, int nf, int N, cons
     tree_T_far_p<double>(t, s, nf, N, geo, src64, src64, geo, z, kappa, 0.0, eps_ratio, part,
                          floor_r2);
   else
-    tree_T_far_p<float>(t, s, nf, N, geo, src64, src32, tgt32, z, (float)kappa,
+    // (the transposed radial factors start from e^{-kappa r}: kappa^2 finite is enough)
+    tree_T_far_p<float>(t, s, nf, N, geo, src64, src32, tgt32, z, kappa32(kappa),
                         (float)(-kappa * 1.4426950408889634), eps_ratio, part, floor_r2);
   const int rows = kFinBlock / kFinLanes;
   hipLaunchKernelGGL(k_finish_T_slots, dim3((N + rows - 1) / rows), dim3(kFinBlock), 0, s, N,

@@ -470,7 +470,7 @@ void Runtime::set_mesh(int64_t nv, const double *verts, int64_t nt,
   if (tree_active_) {
     tree_.reset(new Tree());
     tree_->prm.theta = o.theta;
-    tree_->prm.kappa = o.kappa;
+    tree_->prm.kappa = std::min(o.kappa, kMaxKappa);
     tree_->prm.order = o.order_P;
     tree_->prm.leaf = o.leaf_panels;
     tree_->build_device(N, ru_.nf, keys_.p, geo_.p, src64_.p, s_);

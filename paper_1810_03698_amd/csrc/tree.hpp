@@ -84,9 +84,13 @@ constexpr int kShiftLeaves = 16;
 // target panels per M2P^T task (adjoint product)
 constexpr int kM2PTChunkTargets = 512;
 
+// Beyond this e^{-kappa r} vanishes at every distance that the pair cut-offs
+// leave, and (kMaxKappa)^7, the highest power at order 6, is finite in FP64.
+constexpr double kMaxKappa = 1e20;
+
 struct TreeParams {
   double theta = 0.5;
-  double kappa = 0.0;  // the only one of a tree: its tables hold powers of it
+  double kappa = 0.0;  // the only one of a tree (its tables hold powers of it), <= kMaxKappa
   int order = 4;
   int leaf = 300;
 };
