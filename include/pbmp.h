@@ -195,7 +195,8 @@ int pbmp_set_mesh(pbmp_ctx *c, int64_t nv, const double *verts, int64_t nt,
  * to 1e-10 |Q|, else PBMP_EARG), polarisabilities alpha [m] (>= 0) and
  * polarisation groups group [m] (NULL: every site its own group; permanent
  * fields between sites of one group are excluded from the polarising field).
- * Requires a mesh; every site must lie inside it (PBMP_ESITE). */
+ * Requires a mesh; every site must lie inside it (PBMP_ESITE).  Input that is
+ * refused leaves the old sites and their solution in place. */
 int pbmp_set_sites(pbmp_ctx *c, int64_t m, const double *xyz, const double *q,
                    const double *d, const double *Q9, const double *alpha,
                    const int32_t *group, int where);

@@ -611,8 +611,22 @@ void Runtime::set_sites(int64_t m, const double *xyz, const double *q,
       PBMP_REQUIRE(dx * dx + dy * dy + dz * dz > 0, PBMP_EARG, "coincident sites");
       if (M > 4096) break;  // pairwise check only for small inputs
     }
+  // inside test, before anything of the old sites is touched
+  {
+    Dbuf<double> pts, wind;
+    pts.upload(hx.data(), hx.size(), s_);
+    wind.alloc(M);
+    launch_winding(s_, N_, M, verts_.p, tri_.p, pts.p, wind.p);
+    std::vector<double> hw(M);
+    wind.download(hw.data(), M, s_);
+    sync();
+    for (int l = 0; l < M; ++l)
+      PBMP_REQUIRE(hw[l] > 0.5, PBMP_ESITE,
+                   "site " + std::to_string(l) + " lies outside the surface");
+  }
   if (M != M_) warm_ok_ = false;
-  M_ = M;
+  solved_ = false;
+  M_ = 0;  // no sites, should an allocation fail half way
   h_sxyz_ = hx;
   sxyz_.upload(hx.data(), hx.size(), s_);
   sq_.upload(hq.data(), hq.size(), s_);
@@ -620,17 +634,7 @@ void Runtime::set_sites(int64_t m, const double *xyz, const double *q,
   sQ_.upload(hQ.data(), hQ.size(), s_);
   salpha_.upload(ha.data(), ha.size(), s_);
   sgroup_.upload(hg.data(), hg.size(), s_);
-  // inside test
-  Dbuf<double> wind;
-  wind.alloc(M);
-  launch_winding(s_, N_, M, verts_.p, tri_.p, sxyz_.p, wind.p);
-  std::vector<double> hw(M);
-  wind.download(hw.data(), M, s_);
-  sync();
-  for (int l = 0; l < M; ++l)
-    PBMP_REQUIRE(hw[l] > 0.5, PBMP_ESITE,
-                 "site " + std::to_string(l) + " lies outside the surface");
-  build_site_lists();
+  build_site_lists(M);
   mu_d_.alloc(3 * (size_t)M);
   mu_v_.alloc(3 * (size_t)M);
   Eperm_.alloc(3 * (size_t)M);
@@ -647,7 +651,7 @@ void Runtime::set_sites(int64_t m, const double *xyz, const double *q,
   e_.alloc(10);
   ro_chunks_ = readout_chunks(N_, M);
   rpart_.alloc((size_t)ro_chunks_ * M * 10);
-  solved_ = false;
+  M_ = M;
 }
 
 // panels j with |p_l - c_j| < eta sqrt(A_j) for the points p (AoS) as CSR
@@ -677,8 +681,8 @@ void Runtime::point_lists(const std::vector<double> &pts, int M, std::vector<int
   }
 }
 
-void Runtime::build_site_lists() {
-  const int N = N_, M = M_;
+void Runtime::build_site_lists(int M) {
+  const int N = N_;
   std::vector<int> row, col;
   point_lists(h_sxyz_, M, row, col);
   // per panel: the sites for which it is near (transposed lists)
@@ -1148,8 +1152,9 @@ void Runtime::matvec_user(const double *x, double *y, int transpose, int where) 
   }
   // The kernels gather from and scatter to the caller's vectors themselves
   // (three launches for a small direct product; the two permutations and two
-  // device copies were half of its time).  Vectors that are not whole device
-  // allocations of this process go through copies, which report them.
+  // device copies were half of its time).  Vectors that do not lie inside one
+  // allocation of the current device, or not on 8 bytes, go through copies,
+  // which report what is no memory at all.
   PBMP_REQUIRE(x != nullptr, PBMP_EARG, "null input");
   PBMP_REQUIRE(y != nullptr, PBMP_EARG, "null output");
   const size_t bytes = sizeof(double) * 2 * (size_t)N_;

@@ -131,7 +131,7 @@ class Runtime {
   void sync();
   void build_near_lists();
   void near_values();
-  void build_site_lists();
+  void build_site_lists(int M);
   void alloc_work();
   // y = A x (internal order, device)
   // y = A x (transpose: A^T x); f64 forces the FP64 far field in mixed mode

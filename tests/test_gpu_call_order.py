@@ -162,3 +162,22 @@ def test_failed_set_mesh_leaves_no_mesh():
     s.set_mesh(verts, tris)
     x = np.ones(2 * len(tris))
     assert np.array_equal(s.matvec(x), _solver(verts, tris).matvec(x))
+
+
+def test_failed_set_sites_leaves_the_old_ones():
+    """Sites refused for one outside the surface, more of them than before: the
+    solution of the old sites is still there to differentiate and to repeat."""
+    from paper_1810_03698_amd import PbmpError
+    s = _solver(*icosphere(2, 4.0), _sites())
+    ref = s.solve()
+    g = s.backward(1.0)
+    more = [np.array(a) for a in _sites(40, 2.5)]
+    more[0][39] = [0.0, 0.0, 6.0]
+    with pytest.raises(PbmpError) as e:
+        s.set_sites(*more)
+    assert e.value.code == -3
+    got = s.backward(1.0)
+    for k in ("xyz", "q", "d", "Q9", "verts"):
+        assert np.array_equal(got[k], g[k]), k
+    again = s.solve()
+    assert again["dG"] == ref["dG"] and np.array_equal(again["mu_diss"], ref["mu_diss"])
