@@ -23,7 +23,7 @@ constexpr double kFourPi = 12.566370614359172;
 // with fewer waves than SIMDs).  The multipoles are staged in T, once per
 // block instead of once per pair; the differences are formed in FP64 and the
 // sums kept there.  Bound by VALU issue, the FP64 differences and sums about
-// 40 % of it: 1376 -> 650 us on 144500 panels and 5000 sites, 202 -> 37 us on
+// 40 % of it: 1376 -> 595 us on 144500 panels and 5000 sites, 202 -> 37 us on
 // 28880 and 1000 (mixed precision).
 constexpr int kSiteTile = 128;
 constexpr int kRhsVal = 12;  // q px py pz Qxx Qxy Qxz Qyy Qyz Qzz per site
@@ -534,9 +534,13 @@ void launch_rhs(hipStream_t s, bool fp64, int N, int M, const double *geo,
                 const double *xyz, const double *q, const double *p,
                 const double *Q9, double eps_in, double *f) {
   const double scale = kInv4Pi / eps_in;
-  // two panels per lane share the reads of a site where that still leaves
-  // four blocks per CU
-  const int tpt = N > 128 * 1024 ? 2 : 1;
+  // Two panels per lane share the reads of a site but halve the blocks: worth it
+  // from some four blocks per CU of FP64 pairs, which issue for longer, and only
+  // beyond sixteen in FP32 (one against two panels per lane, sites at the density
+  // of an inside; FP64: 40500 panels 154 and 172 us, 50000 255 and 241, 60500 350
+  // and 322, 144500 2.61 and 2.61 ms, 288000 15.7 and 14.2; FP32: 60500 236 and 246
+  // us, 144500 1.62 and 1.79 ms, 233280 5.78 and 6.00, 255380 7.11 and 6.77).
+  const int tpt = N > (fp64 ? 45000 : 245000) ? 2 : 1;
   const dim3 grid((N + 64 * tpt - 1) / (64 * tpt));
 #define PBMP_RHS(T, TPT)                                                                      \
   hipLaunchKernelGGL((k_rhs<T, TPT>), grid, dim3(256), 0, s, N, M, geo, xyz, q, p, Q9, scale, f)
