@@ -1,18 +1,20 @@
 // Far-field source-target (P2P) sums of the boundary-integral operator
 // (section "The treecode algorithm": the product is an N-body problem with
 // the Gauss nodes as sources and the collocation points as targets), and the
-// step that turns the four operator sums into y = A x (eq. integral_eq).
+// step that adds the partial rows and the near/self correction to y = A x
+// (eq. integral_eq).
 //
 // Layout: one target per lane, source panels staged through LDS in tiles;
 // the lanes of a wave read the same panel record (LDS broadcast).  A panel
 // record is 16 words: three far-field nodes, the unit normal, the plane
-// offset n.y and the strengths s_V, s_K, eps s_V.  Because the
-// nodes of a flat panel share its plane, n.(x - y_q) = n.x - n.y0 for all q.
+// offset n.y (the site readout's) and the strengths s_V, s_K, eps s_V.
+// The nodes of a flat panel share its plane, so n.R for R = x - y_q is the same
+// for all q; the products take it from the first node's difference vector.
 //
-// Per (target, node) pair the four kernels need one reciprocal square root
-// and one exponential:  V_L += 1/r, V_Y += e^{-kr}/r, K_L += 1/r^3,
-// K_Y += (1 + kr) e^{-kr}/r^3; the panel's sums are then weighted by s_V and
-// s_K n.R.  FP32 variant: per-tile FP32 sums folded into FP64 accumulators.
+// Per (target, node) pair one reciprocal square root and one exponential give
+// both rows of y = A x, the layers combined per node (pair.hpp):
+//   (s_K n.R / r^2 - s_V) / r   and   (eps s_V - s_K n.R (1/r + k) / r) e^{-kr} / r.
+// FP32 variant: per-tile FP32 sums folded into FP64 accumulators.
 #include <algorithm>
 #include <cmath>
 

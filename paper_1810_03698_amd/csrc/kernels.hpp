@@ -187,7 +187,6 @@ void tree_apply(Tree &t, hipStream_t s, bool fp64, int nf, int N,
                 const double *geo, const double *src64, const float *src32,
                 const float *tgt32, double eps_ratio, double *part, KernelClock &clk,
                 bool floor_r2);
-// finish with a per-target number of partial slots
 // A^T z with the treecode (transposed P2P, M2P^T + L2L + L2P, transposed
 // near/self correction)
 void tree_apply_transpose(Tree &t, hipStream_t s, bool fp64, int nf, int N, const double *geo,
@@ -203,6 +202,7 @@ void tree_mesh_adjoint_far(Tree &t, hipStream_t s, int nf, int N, const double *
                            const double *src64, const double *lam, double eps_ratio,
                            double *part, double *partT, double *gc, double *gy, double *gn,
                            double *gA);
+// finish with a per-target number of partial slots
 void launch_finish_slots(hipStream_t s, int N, const int *tslots,
                          const double *part, const int *rowptr, const int *col,
                          const double *val, const double *x, double eps_ratio,

@@ -93,7 +93,8 @@ __device__ const double kExp2Table[64] = {
 // Screening constants of the pair kernels.  FP64: e^{-kappa r} =
 // 2^(n/64) 2^(f/64) with n + f = -64 kappa r / ln 2, |f| <= 1/2: 2^(n/64) from
 // the 64-entry table (a copy in LDS, one gather) and a shift of the exponent,
-// 2^(f/64) by its Taylor series to degree 5 (remainder below 4e-17); 11
+// 2^(f/64) by its Taylor series to degree 5 (remainder below 4e-17), the
+// table-driven method of P. T. P. Tang (ACM TOMS 15, 1989); 11
 // operations where the series over |x| <= ln 2 / 2 to degree 13 takes 20.
 // Results below the smallest subnormal come out as zero; WIDE bounds the
 // argument for kappa r beyond the integers of the reduction (1e7).

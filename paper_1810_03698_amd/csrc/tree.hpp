@@ -63,7 +63,11 @@ constexpr int kM2PStageBytes = 8192;
 // and transposed in FP64 811, 737, 713, 718 us; 144500, kernels alone, 1346,
 // 1322, 1310, 1297 us).  Below 14336 panels it is 2048 (5120 panels in leaves of
 // 50 at 1024, 2048, 4096, 12288: 95, 97, 107, 116 us in FP32, of 300 in FP64 138,
-// 136, 134, 150 us).
+// 136, 134, 150 us).  Where a round of tasks just overflows the chip the larger
+// ones win: 14580 transposed, N / 7 against 12288 pairs, 206 against 162 us in FP32.
+// The vertex gradient runs on the same tasks; its whole share of a backward pass
+// takes 3.0 ms at N / 7 and 4.1 at 12288 pairs on 8820 panels, 4.0 and 4.5 on 20480,
+// 5.4 and 5.4 on 28880, 9.3 and 9.4 on 60500.
 inline int p2p_task_work(int N) { return N / 7 < 2048 ? 2048 : N / 7 > 12288 ? 12288 : N / 7; }
 // A surface of N panels has 100-200 N M2P pairs: N / 48 per task gives the
 // largest ones some 8000 tasks (eight waves per SIMD, short tail) without more
@@ -135,7 +139,7 @@ class Tree {
   int n_p2pT_tasks = 0, n_m2pT_tasks = 0, max_slots_T = 1;
   Dbuf<double> d_Lpart, d_L;  // local coefficients: per M2P^T task (harmonic), per box [2][ncoefK]
   // moment tasks: the panels of every leaf in slices of at most
-  // mom_chunk_panels(P); task = (box, s0, s1); a box's slices are consecutive
+  // kMomChunkPanels; task = (box, s0, s1); a box's slices are consecutive
   int n_mom_tasks = 0;
   Dbuf<int> d_mom_task, d_mom_first, d_mom_count;
   Dbuf<double> d_mom_part;  // [n_mom_tasks][nmom]
