@@ -189,10 +189,9 @@ __global__ __launch_bounds__(64) void k_near_grad(
     } else {
       panel_rule_t<D>(v, n, A, c, ru.nn, ru.nb, ru.nw, kappa, fine);
     }
-    if (SELF && ru.nf == 1)  // the only node is the target: the product has no term
-      coarse[0] = coarse[1] = coarse[2] = coarse[3] = D(0.0);
-    else
-      panel_rule_t<D>(v, n, A, c, ru.nf, ru.fb, ru.fw, kappa, coarse);
+    // (no term where a node is the target, as in the product: the one-node rule's
+    // own panel, sheets in contact)
+    panel_rule_t<D>(v, n, A, c, ru.nf, ru.fb, ru.fw, kappa, coarse, kMinR2d);
     const D E = a1 * (fine[1] - coarse[1]) - a2 * (fine[0] - coarse[0]) -
                 a3 * (fine[3] - coarse[3]) + a4 * (fine[2] - coarse[2]);
     for (int k = 0; k < 12; ++k) ge[12 * (size_t)e + k] = E.d[k];

@@ -59,17 +59,19 @@ __device__ inline void singular_panel_t(const S v[3][3], const S c[3], double ka
 }
 
 // (V_L, K_L, V_Y, K_Y) of panel v (normal n, area A) at point x with the
-// nq-node rule (b, w).
+// nq-node rule (b, w); a node closer than sqrt(min_r2) adds nothing.
 template <class S>
 __device__ inline void panel_rule_t(const S v[3][3], const S n[3], const S &A,
                                     const S x[3], int nq, const double (*b)[3],
-                                    const double *w, double kappa, S out[4]) {
+                                    const double *w, double kappa, S out[4],
+                                    double min_r2 = 0.0) {
   S vl(0.0), kl(0.0), vy(0.0), ky(0.0);
   for (int q = 0; q < nq; ++q) {
     S R[3];
     for (int d = 0; d < 3; ++d)
       R[d] = x[d] - (b[q][0] * v[0][d] + b[q][1] * v[1][d] + b[q][2] * v[2][d]);
     const S r2 = R[0] * R[0] + R[1] * R[1] + R[2] * R[2];
+    if (value_of(r2) < min_r2) continue;
     const S r = sqrt(r2);
     const S inv = 1.0 / r;
     const S inv3 = inv / r2;

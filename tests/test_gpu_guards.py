@@ -77,6 +77,37 @@ def test_products_on_sheets_in_contact(kind, precision, mode):
     assert _worst(s.matvec(z, transpose=True), A.T @ z) < TOL[precision]
 
 
+@pytest.mark.parametrize("mode", ["direct", "treecode"])
+@pytest.mark.parametrize("kind", ["dyadic", "turned"])
+def test_vertex_gradient_on_sheets_in_contact(kind, mode):
+    """Along an affine map of the whole mesh, which keeps the sheets in contact and
+    nodes on centroids, against a central difference: solves at 1e-13 leave it an
+    error of 1e-12 |dG| / h and h^2 / 6 of the third derivative, together below
+    2e-6 of the gradient's norm."""
+    verts, tris = _touching_mesh(kind)
+    rng = np.random.default_rng(5)
+    centre = verts[:4].mean(axis=0)  # of the first tetrahedron, 0.6 A from its faces
+    xyz = centre + 0.15 * rng.normal(size=(2, 3))
+    sites = (xyz, np.array([0.4, -0.1]), 0.1 * rng.normal(size=(2, 3)), np.zeros((2, 9)),
+             np.array([0.05, 0.08]))
+    B = rng.normal(size=(3, 3))
+    u = (verts - centre) @ B.T
+    u /= np.linalg.norm(u)
+    h = 2e-4
+
+    def solved(v):
+        s = _solver(v, tris, mode=mode, theta=0.05, leaf_panels=8, gmres_tol=1e-13,
+                    scf_tol_debye=1e-12, scf_maxit=500)
+        s.set_sites(*sites)
+        return s, s.solve(outputs=False)["dG"]
+
+    s, _ = solved(verts)
+    g = s.backward(1.0)["verts"]
+    assert np.isfinite(g).all()
+    fd = (solved(verts + h * u)[1] - solved(verts - h * u)[1]) / (2 * h)
+    assert abs(fd - (g * u).sum()) < 2e-6 * np.linalg.norm(g)
+
+
 @pytest.mark.parametrize("order", [4, 6])
 @pytest.mark.parametrize("kappa", [0.0, 40.0, 1e7, 1e30])
 def test_tree_product_screening_range(kappa, order):
