@@ -45,11 +45,11 @@ COPY_BYTES = 256 << 20
 # reported null).
 TRAFFIC = {
     ("treecode", "m2p", "globule_5000", "mixed"): {
-        "fetch_kib": 21633.64, "fetch_scale": 0.50008, "write_kib": 89270.93,
-        "write_scale": 1.0, "sha": "76027f060d188f75"},
+        "fetch_kib": 21690.6, "fetch_scale": 0.50008, "write_kib": 89320.9,
+        "write_scale": 1.0, "sha": "de37f7c804b477cc"},
     ("treecode", "p2p", "globule_5000", "mixed"): {
-        "fetch_kib": 14931.59, "fetch_scale": 0.50008, "write_kib": 99243.84,
-        "write_scale": 1.0, "sha": "76027f060d188f75"},
+        "fetch_kib": 14909.5, "fetch_scale": 0.50008, "write_kib": 99243.7,
+        "write_scale": 1.0, "sha": "de37f7c804b477cc"},
 }
 TRAFFIC_SOURCES = {
     "treecode": ["k_tree.hip", "harmonic.hpp", "pair.hpp", "tree.hpp", "k_treebuild.hip"],
